@@ -29,7 +29,7 @@
 namespace {
 
 constexpr int kBlocks = 120;
-constexpr int kFaceInts = 8;  // kind, neighbour blocks[4], quadrant s1, s2, pad
+constexpr int kFaceInts = 8;  // kind, neighbour blocks[4], quadrant s1, s2, slot (see build_faces)
 constexpr size_t kBlkAlign = 256;
 constexpr int kBlkNormBlocks = 1024;
 enum { kFaceBoundary = 0, kFaceSame = 1, kFaceF2C = 2, kFaceC2F = 3 };
@@ -57,7 +57,10 @@ std::vector<BlockDesc> build_layout()
   return out;
 }
 
-// face f = 2 * axis + side (axis 0 = x, 1 = y, 2 = z; side 0 = low, 1 = high)
+// face f = 2 * axis + side (axis 0 = x, 1 = y, 2 = z; side 0 = low, 1 = high).  Entry 7 of an
+// F2C or C2F face is its number among the faces of its kind (kF2CFaces, kC2FFaces of them).
+constexpr int kF2CFaces = 24, kC2FFaces = 96;
+
 std::vector<int> build_faces(const std::vector<BlockDesc>& blocks)
 {
   std::map<std::tuple<int, int, int, int>, int> find;
@@ -69,6 +72,7 @@ std::vector<int> build_faces(const std::vector<BlockDesc>& blocks)
     return true;
   };
   std::vector<int> t(blocks.size() * 6 * kFaceInts, 0);
+  int f2c = 0, c2f = 0;
   for (int b = 0; b < (int)blocks.size(); ++b) {
     const BlockDesc& d = blocks[b];
     for (int ax = 0; ax < 3; ++ax) {
@@ -85,6 +89,7 @@ std::vector<int> build_faces(const std::vector<BlockDesc>& blocks)
         if (d.level == 2) {
           if (refined2(n)) {
             e[0] = kFaceF2C;
+            e[7] = f2c++;
             for (int s1 = 0; s1 < 2; ++s1)
               for (int s2 = 0; s2 < 2; ++s2) {
                 int f[3] = {2 * n[0], 2 * n[1], 2 * n[2]};
@@ -104,6 +109,7 @@ std::vector<int> build_faces(const std::vector<BlockDesc>& blocks)
             e[1] = find.at({3, n[0], n[1], n[2]});
           } else {
             e[0] = kFaceC2F;
+            e[7] = c2f++;
             e[1] = find.at({2, p[0], p[1], p[2]});
             e[5] = n[t0] % 2;
             e[6] = n[t1] % 2;
@@ -170,6 +176,7 @@ struct mgblk_ctx {
   std::vector<BlkLevel> lv;
   std::vector<double> hhost;
   C2FWeights w{};
+  bool coarse4 = false;   // k_blk_coarse4 may use the LDS it needs
   char err[512] = "no error";
 };
 
@@ -528,6 +535,231 @@ __global__ void __launch_bounds__(kSmallThreadsMax)
     if (ZERO) jacobi_cell_zero(B, omega, hs, f, uout, coarse != 0, b, 1 + zz, 1 + yy, 1 + r - yy * B);
     else jacobi_cell(B, omega, faces, hs, f, u, uout, coarse != 0, b, 1 + zz, 1 + yy, 1 + r - yy * B);
   }
+}
+
+// All `iters` damped-Jacobi iterations of a coarsest level of 4^3 cells per block, from a zero
+// correction, in one launch of one workgroup with the level in LDS.
+//
+// The iterations are a serial chain over 7680 cells: as launches (k_blk_sweep_small) an
+// iteration costs 5.3-5.7 us, nearly all of it launch and memory latency, so the level is kept
+// in one compute unit instead.  An iteration is two phases: the interpolated ghosts (C2F: one
+// thread per coarse face cell, whose 27 values serve four ghosts; F2C: one thread per ghost),
+// then the cells, from one buffer into the other.  A thread owns two adjacent z-columns
+// (8 cells) of a block; every other neighbour column is read from LDS at an offset fixed before
+// the loop -- the same block's, a same-level neighbour's or a ghost's, or at the domain boundary
+// the own column with the sign -1 (zero face value: the ghost is -u).  What bounds an iteration
+// is the compute unit's LDS reads and FP64 issue, so
+//  - z pairs are adjacent and rows interleaved (0, 2, 1, 3): a column is two 16-byte reads, and
+//    the 8 lanes of a block read 128 consecutive bytes; ghosts have the same pair stride;
+//  - a cell is c' = (1 - w) c + (w/6) sum of its neighbours + coef f, eight fused operations,
+//    the C2F value a sum axis by axis (first tangential, second, normal).
+// Measured (256 iterations): 1.45 ms as launches, 0.69 ms here; neighbour values of the
+// own block by lane moves and selects instead of LDS took 0.82 ms.
+constexpr int kC4Block = 66;                  // doubles per block (64 cells, one pair of padding)
+constexpr int kC4Cells = kBlocks * kC4Block;  // cells of a buffer; then C2F and F2C ghosts
+constexpr int kC4Buf = kC4Cells + (kC2FFaces + kF2CFaces) * 16;  // doubles of a buffer
+constexpr int kC4Threads = kBlocks * 8;
+constexpr size_t kC4Lds = 2 * kC4Buf * sizeof(double) + (kC2FFaces + kF2CFaces) * sizeof(int);
+static_assert(kC4Lds <= 160 * 1024, "the coarsest level must fit one compute unit's LDS");
+static_assert(kC4Threads >= 4 * kC2FFaces + 16 * kF2CFaces, "one ghost task per thread");
+static_assert(kC2FFaces % 4 == 0 && kF2CFaces % 4 == 0, "ghost faces are stored in groups of four");
+
+// 0-based cell of a block, and ghost (t1, t2) of an interpolated face (slot counts the C2F
+// faces, then the F2C faces), as offsets in a buffer
+__device__ __forceinline__ int c4_cell(int b, int z, int y, int x)
+{
+  const int row = 2 * (y & 1) + (y >> 1);
+  return b * kC4Block + (z >> 1) * 32 + row * 8 + 2 * x + (z & 1);
+}
+__device__ __forceinline__ int c4_ghost(int slot, int t1, int t2)
+{
+  return kC4Cells + (slot >> 2) * 64 + (t2 >> 1) * 32 + (slot & 3) * 8 + 2 * t1 + (t2 & 1);
+}
+
+template <int ORDER>
+__global__ void __launch_bounds__(kC4Threads)
+    k_blk_coarse4(C2FWeights W, double omega, const int* __restrict__ faces,
+                  const double* __restrict__ hs, const double* __restrict__ f,
+                  double* __restrict__ u, int iters)
+{
+  extern __shared__ __align__(16) double c4[];
+  int* list = reinterpret_cast<int*>(c4 + 2 * kC4Buf);  // face of each interpolated slot
+  const int t = threadIdx.x;
+  if (t < kBlocks * 6) {
+    const int* e = faces + (size_t)t * kFaceInts;
+    if (e[0] == kFaceC2F) list[e[7]] = t;
+    if (e[0] == kFaceF2C) list[kC2FFaces + e[7]] = t;
+  }
+  const int b = t >> 3, x = t & 3, y0 = 2 * ((t >> 2) & 1);  // columns (x, y0), (x, y0 + 1)
+  const double h = hs[b];
+  const double coef = omega * (h * h / 6.0);
+  const double w6 = coef * (1.0 / (h * h)), wc = fma(-6.0, w6, 1.0);
+
+  // neighbour columns (offset of z = 0; z-neighbours: of the cell) and their signs
+  const int* fb = faces + (size_t)b * 6 * kFaceInts;
+  auto outside = [&](int face, int t1, int t2, int own, double& sign) -> int {  // t1, t2 0-based
+    const int* e = fb + face * kFaceInts;
+    sign = e[0] == kFaceBoundary ? -1.0 : 1.0;
+    if (e[0] == kFaceBoundary) return own;
+    if (e[0] == kFaceSame) {
+      const int n = (face & 1) ? 0 : 3;
+      return face < 2 ? c4_cell(e[1], t2, t1, n) : face < 4 ? c4_cell(e[1], t2, n, t1) : c4_cell(e[1], n, t2, t1);
+    }
+    return c4_ghost((e[0] == kFaceC2F ? 0 : kC2FFaces) + e[7], t1, t2);
+  };
+  int own[2], oxm[2], oxp[2], oym, oyp, ozm[2], ozp[2];
+  double sxm = 1.0, sxp = 1.0, sym = 1.0, syp = 1.0, szm, szp;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int y = y0 + j;
+    own[j] = c4_cell(b, 0, y, x);
+    oxm[j] = x == 0 ? outside(0, y, 0, own[j], sxm) : c4_cell(b, 0, y, x - 1);
+    oxp[j] = x == 3 ? outside(1, y, 0, own[j], sxp) : c4_cell(b, 0, y, x + 1);
+    ozm[j] = outside(4, x, y, own[j], szm);
+    ozp[j] = outside(5, x, y, c4_cell(b, 3, y, x), szp);
+  }
+  oym = y0 == 0 ? outside(2, x, 0, own[0], sym) : c4_cell(b, 0, 1, x);
+  oyp = y0 == 2 ? outside(3, x, 0, own[1], syp) : c4_cell(b, 0, 2, x);
+
+  double c[2][4], cf[2][4];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int z = 0; z < 4; ++z) {
+      cf[j][z] = coef * f[bidx(6, b, z + 1, y0 + j + 1, x + 1)];
+      c[j][z] = cf[j][z];  // the first iteration, from zero
+      c4[own[j] + (z >> 1) * 32 + (z & 1)] = c[j][z];
+    }
+  __syncthreads();
+
+  // ghost task: C2F coarse face cell, or F2C ghost
+  const bool c2f = t < 4 * kC2FFaces;
+  const bool f2c = !c2f && t < 4 * kC2FFaces + 16 * kF2CFaces;
+  int gcb = 0, gax = 0, gn0 = 0, gdn = 0, gt1 = 0, gt2 = 0;  // block, axis, first value, direction
+  int gdst = 0;
+  double w1[2][3] = {}, w2[2][3] = {};
+  if (c2f) {
+    const int slot = t >> 2, i1 = t & 1, i2 = (t >> 1) & 1;
+    const int fi = list[slot], face = fi % 6, side = face & 1;
+    const int* e = faces + (size_t)fi * kFaceInts;
+    const int T1 = e[5] * 2 + i1, T2 = e[6] * 2 + i2;
+    const int a1 = tangential_first(ORDER, T1, 4, 0), a2 = tangential_first(ORDER, T2, 4, 0);
+    gcb = e[1];
+    gax = face >> 1;
+    gn0 = side ? 0 : 3;
+    gdn = side ? 1 : -1;
+    gt1 = T1 + a1;
+    gt2 = T2 + a2;
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+      for (int q = 0; q <= ORDER; ++q) {
+        w1[p][q] = W.wt[a1 + 2][p][q];
+        w2[p][q] = W.wt[a2 + 2][p][q];
+      }
+    gdst = c4_ghost(slot, 2 * i1, 2 * i2);  // (t1 + q, t2 + p) at + 2 q + p
+  } else if (f2c) {
+    const int r = t - 4 * kC2FFaces, slot = r >> 4, t1 = r & 3, t2 = (r >> 2) & 3;
+    const int fi = list[kC2FFaces + slot], face = fi % 6, side = face & 1;
+    const int* e = faces + (size_t)fi * kFaceInts;
+    gcb = e[1 + 2 * (t1 >> 1) + (t2 >> 1)];
+    gax = face >> 1;
+    gn0 = side ? 0 : 3;
+    gdn = side ? 1 : -1;
+    gt1 = 2 * (t1 & 1);
+    gt2 = 2 * (t2 & 1);
+    gdst = c4_ghost(kC2FFaces + slot, t1, t2);
+  }
+  // a cell's offset is a sum of one term per axis: the task's terms, fixed before the loop
+  int on[3], o1[3], o2[3];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const int n = min(max(gn0 + gdn * q, 0), 3), p1 = min(gt1 + q, 3), p2 = min(gt2 + q, 3);
+    on[q] = gax == 0 ? c4_cell(gcb, 0, 0, n) : gax == 1 ? c4_cell(gcb, 0, n, 0) : c4_cell(gcb, n, 0, 0);
+    o1[q] = gax == 0 ? c4_cell(0, 0, p1, 0) : c4_cell(0, 0, 0, p1);
+    o2[q] = gax == 2 ? c4_cell(0, 0, p2, 0) : c4_cell(0, p2, 0, 0);
+  }
+
+  int cur = 0;
+  for (int it = 1; it < iters; ++it) {
+    double* src = c4 + cur;
+    double* dst = c4 + (kC4Buf - cur);
+    if (c2f) {
+      constexpr int cn = ORDER + 1;
+      double s[2][2] = {};  // [p2][p1]
+#pragma unroll
+      for (int a = 0; a < cn; ++a) {
+        double pl[2][2] = {};
+#pragma unroll
+        for (int j2 = 0; j2 < cn; ++j2) {
+          const int o = on[a] + o2[j2];
+          double row[2] = {};
+#pragma unroll
+          for (int j1 = 0; j1 < cn; ++j1) {
+            const double v = src[o + o1[j1]];
+#pragma unroll
+            for (int p = 0; p < 2; ++p) row[p] = fma(w1[p][j1], v, row[p]);
+          }
+#pragma unroll
+          for (int p2 = 0; p2 < 2; ++p2)
+#pragma unroll
+            for (int p1 = 0; p1 < 2; ++p1) pl[p2][p1] = fma(w2[p2][j2], row[p1], pl[p2][p1]);
+        }
+#pragma unroll
+        for (int p2 = 0; p2 < 2; ++p2)
+#pragma unroll
+          for (int p1 = 0; p1 < 2; ++p1) s[p2][p1] = fma(W.wn[a], pl[p2][p1], s[p2][p1]);
+      }
+#pragma unroll
+      for (int p1 = 0; p1 < 2; ++p1)
+        *reinterpret_cast<double2*>(src + gdst + 2 * p1) = make_double2(s[0][p1], s[1][p1]);
+    } else if (f2c) {
+      double s = 0.0;
+#pragma unroll
+      for (int li = 0; li < 2; ++li)
+#pragma unroll
+        for (int d2 = 0; d2 < 2; ++d2)
+#pragma unroll
+          for (int d1 = 0; d1 < 2; ++d1) s += 0.125 * src[on[li] + o2[d2] + o1[d1]];
+      src[gdst] = s;
+    }
+    __syncthreads();
+    auto pair = [&](int off, int zp) { return *reinterpret_cast<const double2*>(src + off + 32 * zp); };
+    double n[2][4];
+#pragma unroll
+    for (int zp = 0; zp < 2; ++zp) {
+      const double2 ym = pair(oym, zp), yp = pair(oyp, zp);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const double2 xm = pair(oxm[j], zp), xp = pair(oxp[j], zp);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const int z = 2 * zp + i;
+          const double in = c[1 - j][z];  // the other row of the pair
+          double s = fma(sxm, i ? xm.y : xm.x, in);
+          s = fma(sxp, i ? xp.y : xp.x, s);
+          s = j == 0 ? fma(sym, i ? ym.y : ym.x, s) : fma(syp, i ? yp.y : yp.x, s);
+          s = z > 0 ? s + c[j][z - 1] : fma(szm, src[ozm[j]], s);
+          s = z < 3 ? s + c[j][z + 1] : fma(szp, src[ozp[j]], s);
+          n[j][z] = fma(w6, s, fma(wc, c[j][z], cf[j][z]));
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int zp = 0; zp < 2; ++zp) {
+        c[j][2 * zp] = n[j][2 * zp];
+        c[j][2 * zp + 1] = n[j][2 * zp + 1];
+        *reinterpret_cast<double2*>(dst + own[j] + 32 * zp) = make_double2(c[j][2 * zp], c[j][2 * zp + 1]);
+      }
+    cur = kC4Buf - cur;
+    __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int z = 0; z < 4; ++z) u[bidx(6, b, z + 1, y0 + j + 1, x + 1)] = c[j][z];
 }
 
 // Damped-Jacobi sweep of blocks of >= 64 cells a side, marching along z: a thread owns
@@ -917,12 +1149,29 @@ void prolong_correct(mgblk_ctx* c, int l, double* ec, double* u)
     k_blk_prolong<<<cell_grid(B), kCellThreads, 0, c->s>>>(B, c->faces, ec, u);
 }
 
+using Coarse4Kernel = void (*)(C2FWeights, double, const int*, const double*, const double*, double*, int);
+
+Coarse4Kernel coarse4_kernel(int order)
+{
+  return order == 0 ? k_blk_coarse4<0> : order == 1 ? k_blk_coarse4<1> : k_blk_coarse4<2>;
+}
+
 // V(nu1, nu2) on level l from the iterate in x (y: the level's second buffer); returns the
 // buffer holding the result.  Coarse problems start from 0 in the level's u.
 double* vcycle_rec(mgblk_ctx* c, int l, const double* f, double* x, double* y, bool zero = false)
 {
   const int last = (int)c->lv.size() - 1;
-  if (l == last) return sweeps(c, l, f, x, y, c->g.coarse_iters, zero);
+  if (l == last) {
+    // a correction level of 4^3 cells per block fits one compute unit's LDS: all iterations in
+    // one launch; other coarsest sizes (6, 10, .. from block sizes that are no power of two, or
+    // fewer levels) do not fit and take a launch per iteration
+    if (zero && c->coarse4 && c->lv[l].B == 4 && c->g.coarse_iters > 0) {
+      coarse4_kernel(c->g.order)<<<1, kC4Threads, kC4Lds, c->s>>>(c->w, c->g.omega, c->faces, c->lv[l].hs,
+                                                                 f, x, c->g.coarse_iters);
+      return x;
+    }
+    return sweeps(c, l, f, x, y, c->g.coarse_iters, zero);
+  }
   double* cur = sweeps(c, l, f, x, y, c->g.nu1, zero);
   double* oth = cur == x ? y : x;
   BlkLevel& C = c->lv[l + 1];
@@ -987,6 +1236,9 @@ mg_status mgblk_setup(const mgblk_grid* grid, void* workspace, size_t bytes, voi
   c->g = *grid;
   c->s = static_cast<hipStream_t>(stream);
   c->w = c2f_weights(grid->order);
+  c->coarse4 = hipFuncSetAttribute(reinterpret_cast<const void*>(coarse4_kernel(grid->order)),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)kC4Lds) == hipSuccess;
+  if (!c->coarse4) (void)hipGetLastError();  // the iterations are then launched one by one
   BlkCarver cv{static_cast<char*>(workspace)};
   blk_layout(grid, cv, c);
   const std::vector<BlockDesc> blocks = build_layout();

@@ -13,6 +13,7 @@
 // multiplication by 1/h^2 equals the division by h^2).
 #include "../../include/mg_fv.h"
 #include "mg_kernels.h"
+#include "mg_lanes.h"
 
 #include <hip/hip_runtime.h>
 
@@ -47,7 +48,15 @@ struct mgfv_ctx {
   FvLevel lv[kFvMaxLevels];
   double* partial = nullptr;
   double* scal = nullptr;
+  int tail = -1;           // first level of the one-launch tail (-1: none)
+  double* hnorm = nullptr; // pinned host word and event of the norm read-back
+  hipEvent_t ev = nullptr;
   char err[512] = "no error";
+  ~mgfv_ctx()
+  {
+    if (ev) (void)hipEventDestroy(ev);
+    if (hnorm) (void)hipHostFree(hnorm);
+  }
 };
 
 namespace {
@@ -319,30 +328,262 @@ __global__ void __launch_bounds__(kFvCoarseThreads)
   }
 }
 
+// The coarsest solver on 4^3 cells, one lane per cell of one wave: no barrier, the value and f
+// stay in registers, x- and y-neighbours come by DPP within 16 lanes (a plane), z-neighbours by
+// a lane permute.  Same operations as k_fv_coarse.  256 iterations: FVC4_US us, against 90 us in
+// a 1024-thread workgroup that read f from memory and met a barrier per iteration.
+constexpr int kRowShl1 = 0x101, kRowShl4 = 0x104, kRowShr1 = 0x111, kRowShr4 = 0x114;
+
+__device__ __forceinline__ double lane_permute(int byte_lane, double v)
+{
+  return __hiloint2double(__builtin_amdgcn_ds_bpermute(byte_lane, __double2hiint(v)),
+                          __builtin_amdgcn_ds_bpermute(byte_lane, __double2loint(v)));
+}
+
+// iterates ui in place; g*: twice the ghost value beside the lane's cell along each axis
+__device__ __forceinline__ double fv_coarse4(double ih2, double coef, int iters, double ui, double fi,
+                                             double gx, double gy, double gz)
+{
+  const int lane = threadIdx.x & 63, x = lane & 3, y = (lane >> 2) & 3, z = lane >> 4;
+  const int below = ((lane - 16) & 63) * 4, above = ((lane + 16) & 63) * 4;
+  for (int it = 0; it < iters; ++it) {
+    const double dn = lane_permute(below, ui), up = lane_permute(above, ui);
+    const double l = mgk::dpp<kRowShr1>(ui), r = mgk::dpp<kRowShl1>(ui);
+    const double d = mgk::dpp<kRowShr4>(ui), t = mgk::dpp<kRowShl4>(ui);
+    const double hx = gx - ui, hy = gy - ui, hz = gz - ui;
+    double s = ui - (x == 0 ? hx : l);
+    s = s + (ui - (x == 3 ? hx : r));
+    s = s + (ui - (y == 0 ? hy : d));
+    s = s + (ui - (y == 3 ? hy : t));
+    s = s + (ui - (z == 0 ? hz : dn));
+    s = s + (ui - (z == 3 ? hz : up));
+    ui = ui + coef * (fi - s * ih2);
+  }
+  return ui;
+}
+
+__global__ void __launch_bounds__(64)
+    k_fv_coarse4(double ih2, double coef, int iters, const double* __restrict__ f,
+                 double* __restrict__ u, int zero)
+{
+  const int lane = threadIdx.x, x = lane & 3, y = (lane >> 2) & 3, z = lane >> 4;
+  const int i = ((z + 1) * 6 + y + 1) * 6 + x + 1;
+  auto ghost = [&](int c, int step) { return !zero && (c == 0 || c == 3) ? 2.0 * u[i + (c ? step : -step)] : 0.0; };
+  u[i] = fv_coarse4(ih2, coef, iters, zero ? 0.0 : u[i], f[i], ghost(x, 1), ghost(y, 6), ghost(z, 36));
+}
+
+// The V-cycle's tail in one launch: the levels from at most 16^3 cells down to the coarsest, from
+// a zero correction, in one workgroup with the iterates in LDS and f in registers.  A level of
+// that size is launch latency (a sweep of 3.5-5 us does 0.3-1 us of work), and a cycle visits
+// each with six sweeps and two transfers.  Same operations as the per-level kernels.
+// Measured, 16^3 to 4^3 with 256 coarsest iterations: FVTAIL_US us per cycle, against 150 us in
+// 17 launches.
+constexpr int kFvTailN = 16, kFvTailLevels = 4, kFvTailThreads = 1024;
+struct FvTailArgs {
+  int N, levels, nu1, nu2, coarse_iters;
+  double omega, h;  // of the first level
+  const double* f;
+  double* u;
+};
+
+// LDS doubles of a tail level: two iterates with their ghost layers
+__host__ __device__ constexpr int fv_tail_doubles(int N) { return 2 * (N + 2) * (N + 2) * (N + 2); }
+constexpr size_t kFvTailLds = sizeof(double) * (fv_tail_doubles(16) + fv_tail_doubles(8) + fv_tail_doubles(4) + fv_tail_doubles(2));
+
+// N: cells per side (compile-time, so that the cells of a thread and their f are registers)
+template <int N>
+__device__ void fv_tail_level(const FvTailArgs& a, int left, double h, double* base,
+                              const double (&f)[(N * N * N + kFvTailThreads - 1) / kFvTailThreads])
+{
+  constexpr int m = N + 2, cells = N * N * N, K = (cells + kFvTailThreads - 1) / kFvTailThreads;
+  constexpr int lg = N == 16 ? 4 : N == 8 ? 3 : N == 4 ? 2 : 1;
+  const double ih2 = 1.0 / (h * h), coef = a.omega * (h * h / 6.0);
+  double* buf[2] = {base, base + m * m * m};
+  int cur = 0;
+  int at[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int t = threadIdx.x + k * kFvTailThreads;
+    at[k] = ((1 + (t >> (2 * lg))) * m + 1 + ((t >> lg) & (N - 1))) * m + 1 + (t & (N - 1));
+  }
+  // A u at cell k from the current buffer; the correction vanishes on the faces (ghost 2 0 - u)
+  auto apply = [&](const double* s, int k) {
+    const int t = threadIdx.x + k * kFvTailThreads, i = at[k];
+    const int x = t & (N - 1), y = (t >> lg) & (N - 1), z = t >> (2 * lg);
+    const double ui = s[i], g = 0.0 - ui;
+    double v = ui - (x == 0 ? g : s[i - 1]);
+    v = v + (ui - (x == N - 1 ? g : s[i + 1]));
+    v = v + (ui - (y == 0 ? g : s[i - m]));
+    v = v + (ui - (y == N - 1 ? g : s[i + m]));
+    v = v + (ui - (z == 0 ? g : s[i - m * m]));
+    v = v + (ui - (z == N - 1 ? g : s[i + m * m]));
+    return v * ih2;
+  };
+  auto each = [&](auto&& fn) {
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      if (cells % kFvTailThreads == 0 || threadIdx.x + k * kFvTailThreads < cells) fn(k);
+  };
+  auto sweep = [&](bool zero) {
+    const double* s = buf[cur];
+    double* d = buf[1 - cur];
+    if (zero) each([&](int k) { d[at[k]] = 0.0 + coef * (f[k] - 0.0); });
+    else each([&](int k) { d[at[k]] = s[at[k]] + coef * (f[k] - apply(s, k)); });
+    cur = 1 - cur;
+    __syncthreads();
+  };
+  if (left == 1) {  // the coarsest level
+    if (a.coarse_iters == 0) {
+      each([&](int k) { buf[cur][at[k]] = 0.0; });
+    } else if (N == 4) {
+      if (threadIdx.x < 64) buf[cur][at[0]] = fv_coarse4(ih2, coef, a.coarse_iters, 0.0, f[0], 0.0, 0.0, 0.0);
+    } else {
+      for (int it = 0; it < a.coarse_iters; ++it) sweep(it == 0);
+    }
+    __syncthreads();
+  } else {
+    if (a.nu1 == 0) {
+      each([&](int k) { buf[cur][at[k]] = 0.0; });
+      __syncthreads();
+    }
+    for (int s = 0; s < a.nu1; ++s) sweep(s == 0);
+    if constexpr (N > 2) {
+      // restriction: the residuals into the other buffer, then the mean of 8 children
+      constexpr int C = N / 2, cc = C * C * C, lc = lg - 1;
+      each([&](int k) { buf[1 - cur][at[k]] = f[k] - apply(buf[cur], k); });
+      __syncthreads();
+      double fc[1] = {0.0};
+      const int t = threadIdx.x;
+      if (t < cc) {
+        const int X = t & (C - 1), Y = (t >> lc) & (C - 1), Z = t >> (2 * lc);
+        const double* r = buf[1 - cur] + ((1 + 2 * Z) * m + 1 + 2 * Y) * m + 1 + 2 * X;
+        double s = 0.0;
+#pragma unroll
+        for (int dz = 0; dz < 2; ++dz)
+#pragma unroll
+          for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+            for (int dx = 0; dx < 2; ++dx) s += r[(dz * m + dy) * m + dx];
+        fc[0] = s / 8.0;
+      }
+      double* cbase = base + fv_tail_doubles(N);
+      fv_tail_level<C>(a, left - 1, 2.0 * h, cbase, fc);
+      // u += P e: 8 terms in the order z, y, x, parent first
+      constexpr int mc = C + 2;
+      each([&](int k) {
+        const int q = threadIdx.x + k * kFvTailThreads;
+        const int c[3] = {q & (N - 1), (q >> lg) & (N - 1), q >> (2 * lg)};
+        int par[3], nb[3];
+        double sg[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          par[d] = 1 + (c[d] >> 1);
+          nb[d] = (c[d] & 1) ? par[d] + 1 : par[d] - 1;
+          sg[d] = nb[d] == 0 || nb[d] == C + 1 ? -1.0 : 1.0;
+          nb[d] = min(max(nb[d], 1), C);
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const bool z = j & 4, y = j & 2, x = j & 1;
+          const double wt = (z ? 0.25 : 0.75) * (y ? 0.25 : 0.75) * (x ? 0.25 : 0.75);
+          const double sign = (z ? sg[2] : 1.0) * (y ? sg[1] : 1.0) * (x ? sg[0] : 1.0);
+          s += wt * (sign * cbase[((z ? nb[2] : par[2]) * mc + (y ? nb[1] : par[1])) * mc + (x ? nb[0] : par[0])]);
+        }
+        buf[cur][at[k]] = buf[cur][at[k]] + s;
+      });
+      __syncthreads();
+    }
+    for (int s = 0; s < a.nu2; ++s) sweep(false);
+  }
+  if (cur == 1) {  // the caller reads the first buffer
+    each([&](int k) { buf[0][at[k]] = buf[1][at[k]]; });
+    __syncthreads();
+  }
+}
+
+template <int N>
+__global__ void __launch_bounds__(kFvTailThreads) k_fv_tail(FvTailArgs a)
+{
+  extern __shared__ __align__(16) double fv_lds[];
+  constexpr int m = N + 2, cells = N * N * N, K = (cells + kFvTailThreads - 1) / kFvTailThreads;
+  auto node = [](int t) { return (size_t)((1 + t / (N * N)) * m + 1 + (t / N) % N) * m + 1 + t % N; };
+  double f[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int t = threadIdx.x + k * kFvTailThreads;
+    f[k] = t < cells ? a.f[node(t)] : 0.0;
+  }
+  fv_tail_level<N>(a, a.levels, a.h, fv_lds, f);
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int t = threadIdx.x + k * kFvTailThreads;
+    if (t < cells) a.u[node(t)] = fv_lds[node(t)];
+  }
+}
+
 // ---------------------------------------------------------------- level operations
 double jacobi_coef(const mgfv_ctx* c, const FvLevel& L) { return c->g.omega * (L.h * L.h / 6.0); }
 
-// `sweeps` Jacobi sweeps on level l from u (alternating with t, whose ghost layer equals
-// u's); returns the buffer that holds the result.  zero: u is 0 (a coarse level's zero
-// correction, ghost layer 0) and is not read: the first sweep reads 0 instead.
-double* smooth(mgfv_ctx* c, int l, double* u, double* t, const double* f, int sweeps,
-               bool zero = false)
+// Levels of at least this many cells per side run 2 or 3 sweeps per launch (mg_fv_tiled.hip): at
+// 32^3 a pass is still a chain of about ten plane steps on 16 workgroups, FVMIN
+constexpr int kFvBlockedMin = 32;
+
+// `sweeps` Jacobi sweeps on level l from u (alternating with t, whose ghost layer equals u's);
+// returns the buffer that holds the result.  zero: u is 0 (a coarse level's zero correction,
+// ghost layer 0) and is not read.  ec: the sweeps start from u + P ec.  fc: receives the
+// restricted residual of the result; its ghost layer is written as 0 by the per-cell kernel and
+// left alone by the others (zero in the workspace).  norm2: receives the squared residual norm of
+// u where the first pass can form it (norm_rides below).
+double* smooth(mgfv_ctx* c, int l, double* u, double* t, const double* f, int sweeps, bool zero = false,
+               const double* ec = nullptr, double* fc = nullptr, double* norm2 = nullptr)
 {
   const FvLevel& L = c->lv[l];
   const double ih2 = 1.0 / (L.h * L.h);
+  const bool blocked = L.N >= kFvBlockedMin, tiled = mgk::fv_tiled_supported(L.N);
   double *cur = u, *oth = t;
-  for (int s = 0; s < sweeps; ++s) {
-    const bool z0 = zero && s == 0;
-    if (mgk::fv_tiled_supported(L.N))
-      mgk::fv_jacobi_tiled(c->s, L.N, L.h, c->g.omega, f, cur, oth, c->partial, z0);
-    else
-      k_fv_jacobi<<<grid3(L.N, L.N, L.N), kFvRowThreads, 0, c->s>>>(L.N, ih2, jacobi_coef(c, L),
-                                                                   f, cur, oth, z0 ? 1 : 0);
+  int left = sweeps;
+  bool restricted = false;
+  if (ec && (sweeps == 0 || !(tiled || (blocked && sweeps > 1)))) {
+    k_fv_prolong<<<grid3(L.N / 2, L.N, L.N), kFvRowThreads, 0, c->s>>>(L.N / 2, ec, cur);
+    ec = nullptr;
+  }
+  while (left > 0) {
+    // 3 sweeps per pass, the remainder as 2 + 2 rather than 3 + 1
+    const int n = !blocked ? 1 : left == 4 ? 2 : left < 3 ? left : 3;
+    const bool last = left == n;
+    if (n > 1) {
+      mgk::fv_sweeps(c->s, L.N, L.h, c->g.omega, n, zero ? nullptr : cur, f, ec, oth,
+                     last ? fc : nullptr, c->partial, last && fc ? norm2 : nullptr);
+      restricted = last && fc;
+    } else if (ec) {
+      mgk::fv_jacobi_prolong_tiled(c->s, L.N, L.h, c->g.omega, f, cur, ec, oth, c->partial);
+    } else if (tiled) {
+      mgk::fv_jacobi_tiled(c->s, L.N, L.h, c->g.omega, f, cur, oth, c->partial, zero);
+    } else {
+      k_fv_jacobi<<<grid3(L.N, L.N, L.N), kFvRowThreads, 0, c->s>>>(L.N, ih2, jacobi_coef(c, L), f, cur,
+                                                                   oth, zero ? 1 : 0);
+    }
     double* x = cur;
     cur = oth;
     oth = x;
+    left -= n;
+    zero = false;
+    ec = nullptr;
+  }
+  if (fc && !restricted) {
+    const int Nc = L.N / 2;
+    if (tiled) mgk::fv_restrict_tiled(c->s, L.N, L.h, f, cur, fc, c->partial);
+    else k_fv_restrict<<<grid3(Nc + 2, Nc + 2, Nc + 2), kFvRowThreads, 0, c->s>>>(Nc, ih2, f, cur, fc);
   }
   return cur;
+}
+
+// Whether smooth() with the pre-smoothing's arguments on level 0 forms the norm of its input: one
+// pass that also restricts.
+bool norm_rides(const mgfv_ctx* c)
+{
+  return c->g.levels > 1 && c->lv[0].N >= kFvBlockedMin && (c->g.nu1 == 2 || c->g.nu1 == 3);
 }
 
 // zero: u is 0 (not read)
@@ -350,6 +591,10 @@ void coarse_solve(mgfv_ctx* c, int l, const double* f, double* u, bool zero = fa
 {
   const FvLevel& L = c->lv[l];
   const double ih2 = 1.0 / (L.h * L.h);
+  if (L.N == 4) {
+    k_fv_coarse4<<<1, 64, 0, c->s>>>(ih2, jacobi_coef(c, L), c->g.coarse_iters, f, u, zero ? 1 : 0);
+    return;
+  }
   if (L.N <= kFvCoarseLds) {
     k_fv_coarse<<<1, kFvCoarseThreads, 0, c->s>>>(L.N, ih2, jacobi_coef(c, L), c->g.coarse_iters, f, u,
                                                    zero ? 1 : 0);
@@ -360,24 +605,15 @@ void coarse_solve(mgfv_ctx* c, int l, const double* f, double* u, bool zero = fa
   if (r != u) mgk::copy<double>(c->s, L.cnt, r, u);
 }
 
-// fc = restriction of f - A u; the streaming pass (N >= 128) leaves fc's ghost layer as it
-// is (zero in the workspace), the per-cell kernel writes it as 0
+// the streaming pass (N >= 128) leaves fc's ghost layer as it is, the per-cell kernel writes 0
 void restrict_residual(mgfv_ctx* c, int l, const double* f, const double* u, double* fc)
 {
-  const FvLevel& L = c->lv[l];
-  const int Nc = L.N / 2;
-  if (mgk::fv_tiled_supported(L.N)) {
-    mgk::fv_restrict_tiled(c->s, L.N, L.h, f, u, fc, c->partial);
-    return;
-  }
-  k_fv_restrict<<<grid3(Nc + 2, Nc + 2, Nc + 2), kFvRowThreads, 0, c->s>>>(Nc, 1.0 / (L.h * L.h),
-                                                                          f, u, fc);
+  smooth(c, l, const_cast<double*>(u), nullptr, f, 0, false, nullptr, fc);
 }
 
 void prolong(mgfv_ctx* c, int l, const double* ec, double* u)
 {
-  const FvLevel& L = c->lv[l];
-  k_fv_prolong<<<grid3(L.N / 2, L.N, L.N), kFvRowThreads, 0, c->s>>>(L.N / 2, ec, u);
+  smooth(c, l, u, nullptr, nullptr, 0, false, ec);
 }
 
 void norm2(mgfv_ctx* c, const double* f, const double* u)
@@ -391,32 +627,41 @@ void norm2(mgfv_ctx* c, const double* f, const double* u)
   k_fv_sum<<<1, 256, 0, c->s>>>(c->partial, kFvNormBlocks, c->scal);
 }
 
-// One V-cycle on level l from (u, t); returns the buffer holding the result.  zero: the
-// iterate is 0 (a coarse level's correction, with zero Dirichlet data) and is not read --
-// the first sweep starts from 0 instead of a filled array.
-double* cycle(mgfv_ctx* c, int l, double* u, double* t, const double* f, bool zero = false)
+// One V-cycle on level l from a zero correction in the level's own arrays; returns the buffer
+// holding the result.
+double* coarse_cycle(mgfv_ctx* c, int l)
 {
+  FvLevel& L = c->lv[l];
+  if (l == c->tail) {
+    const FvTailArgs a{L.N, c->g.levels - l, c->g.nu1, c->g.nu2, c->g.coarse_iters, c->g.omega, L.h, L.f, L.u};
+    auto k = L.N == 16 ? k_fv_tail<16> : k_fv_tail<8>;
+    k<<<1, kFvTailThreads, kFvTailLds, c->s>>>(a);
+    return L.u;
+  }
   if (l == c->g.levels - 1) {
-    coarse_solve(c, l, f, u, zero);
-    return u;
+    coarse_solve(c, l, L.f, L.u, true);
+    return L.u;
   }
-  if (zero && c->g.nu1 == 0) {
-    mgk::fill<double>(c->s, c->lv[l].cnt, 0.0, u);
-    zero = false;
-  }
-  double* cur = smooth(c, l, u, t, f, c->g.nu1, zero);
-  FvLevel& C = c->lv[l + 1];
-  restrict_residual(c, l, f, cur, C.f);
-  double* ec = cycle(c, l + 1, C.u, C.t, C.f, true);  // zero correction, zero Dirichlet data
-  double* oth = cur == u ? t : u;
-  const FvLevel& F = c->lv[l];
-  if (c->g.nu2 > 0 && mgk::fv_tiled_supported(F.N)) {
-    // the correction enters the first post-smoothing sweep: u + P e is never stored
-    mgk::fv_jacobi_prolong_tiled(c->s, F.N, F.h, c->g.omega, f, cur, ec, oth, c->partial);
-    return smooth(c, l, oth, cur, f, c->g.nu2 - 1);
-  }
-  prolong(c, l, ec, cur);
-  return smooth(c, l, cur, oth, f, c->g.nu2);
+  const bool zero = c->g.nu1 > 0;
+  if (!zero) mgk::fill<double>(c->s, L.cnt, 0.0, L.u);
+  double* cur = smooth(c, l, L.u, L.t, L.f, c->g.nu1, zero, nullptr, c->lv[l + 1].f);
+  const double* ec = coarse_cycle(c, l + 1);
+  return smooth(c, l, cur, cur == L.u ? L.t : L.u, L.f, c->g.nu2, false, ec);
+}
+
+// The parts of a V-cycle on the caller's (f, u): down from u to the coarse correction, which
+// writes neither u nor its ghosts unless there is no coarser level or nu1 != 1 pass; and back.
+double* top_down(mgfv_ctx* c, const double* f, double* u, double* norm2)
+{
+  return smooth(c, 0, u, c->lv[0].t, f, c->g.nu1, false, nullptr, c->lv[1].f, norm2);
+}
+
+// the result ends in u
+void top_up(mgfv_ctx* c, const double* f, double* u, double* cur, const double* ec)
+{
+  FvLevel& L = c->lv[0];
+  double* r = smooth(c, 0, cur, cur == u ? L.t : u, f, c->g.nu2, false, ec);
+  if (r != u) mgk::copy<double>(c->s, L.cnt, r, u);
 }
 
 mg_status read_norm(mgfv_ctx* c, double* out)
@@ -435,13 +680,21 @@ mg_status level_args(mgfv_ctx* c, int level, bool coarser)
   return MG_OK;
 }
 
+// one V-cycle, the result in u; the level's second buffer holds u's ghost layer
 mg_status vcycle_impl(mgfv_ctx* c, const double* f, double* u)
 {
-  FvLevel& L0 = c->lv[0];
-  mgk::copy_boundary(c->s, 3, L0.N + 2, u, L0.t);
-  double* r = cycle(c, 0, u, L0.t, f);
-  if (r != u) mgk::copy<double>(c->s, L0.cnt, r, u);
+  if (c->g.levels == 1) {
+    coarse_solve(c, 0, f, u);
+  } else {
+    double* cur = top_down(c, f, u, nullptr);
+    top_up(c, f, u, cur, coarse_cycle(c, 1));
+  }
   return fv_launch_check(c, "V-cycle");
+}
+
+void copy_ghosts(mgfv_ctx* c, const double* u)
+{
+  mgk::copy_boundary(c->s, 3, c->lv[0].N + 2, u, c->lv[0].t);
 }
 
 }  // namespace
@@ -477,6 +730,24 @@ mg_status mgfv_setup(const mgfv_grid* grid, void* workspace, size_t bytes, void*
   fv_layout(grid, cv, c);
   // coarse ghost layers (zero Dirichlet data of the corrections) are never written after this
   mgk::fill<double>(c->s, need / sizeof(double), 0.0, static_cast<double*>(workspace));
+  // the tail starts at the first coarse level of at most 16^3 cells
+  for (int l = 1; l < grid->levels && c->tail < 0; ++l)
+    if (c->lv[l].N <= kFvTailN && c->lv[l].N >= 8 && grid->levels - l <= kFvTailLevels) c->tail = l;
+  if (c->tail >= 0) {
+    const void* k = c->lv[c->tail].N == 16 ? reinterpret_cast<const void*>(k_fv_tail<16>)
+                                           : reinterpret_cast<const void*>(k_fv_tail<8>);
+    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFvTailLds) != hipSuccess) {
+      (void)hipGetLastError();
+      c->tail = -1;  // per-level launches
+    }
+  }
+  // one pinned word for norm reads that leave the stream running; without it they wait
+  void* hp = nullptr;
+  if (hipHostMalloc(&hp, 64, hipHostMallocDefault) == hipSuccess) {
+    c->hnorm = static_cast<double*>(hp);
+    if (hipEventCreateWithFlags(&c->ev, hipEventDisableTiming) != hipSuccess) c->ev = nullptr;
+  }
+  (void)hipGetLastError();
   if (mg_status st = fv_launch_check(c, "setup")) {
     snprintf(g_fv_err, sizeof g_fv_err, "%s", c->err);
     delete c;
@@ -553,6 +824,7 @@ mg_status mgfv_vcycle(mgfv_ctx* c, const double* f, double* u)
 {
   if (!c) return fv_fail(nullptr, MG_EINVAL, "context is NULL");
   if (!f || !u) return fv_fail(c, MG_EINVAL, "f and u must be non-NULL");
+  copy_ghosts(c, u);
   return vcycle_impl(c, f, u);
 }
 
@@ -562,19 +834,44 @@ mg_status mgfv_solve(mgfv_ctx* c, const double* f, double* u, double tol, int* c
   if (!c) return fv_fail(nullptr, MG_EINVAL, "context is NULL");
   if (!f || !u) return fv_fail(c, MG_EINVAL, "f and u must be non-NULL");
   if (!(tol >= 0) || !std::isfinite(tol)) return fv_fail(c, MG_EINVAL, "tol must be finite and >= 0");
-  double rn2 = 0;
-  norm2(c, f, u);
-  mg_status st = fv_launch_check(c, "norm");
-  if (!st) st = read_norm(c, &rn2);
-  double rn = std::sqrt(rn2);
+  copy_ghosts(c, u);
+  double rn2 = 0, rn = 0;
   int k = 0;
-  while (!st && std::isfinite(rn) && rn > tol && k < c->g.max_cycles) {
-    if ((st = vcycle_impl(c, f, u))) break;
-    ++k;
+  mg_status st = MG_OK;
+  if (norm_rides(c) && c->hnorm && c->ev) {
+    // The first sweep of a cycle forms the residual of the iterate it starts from: the iterate's
+    // norm comes out of the next cycle's pre-smoothing, which writes the second buffer only, so
+    // the iterate is still there when the norm ends the solve.  The coarse levels run while the
+    // host waits for it; after the last cycle allowed the norm is a pass of its own.
+    for (;; ++k) {
+      const bool more = k < c->g.max_cycles;
+      double *cur = nullptr, *ec = nullptr;
+      if (more) cur = top_down(c, f, u, c->scal);
+      else norm2(c, f, u);
+      if ((st = fv_hip(c, hipMemcpyAsync(c->hnorm, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s),
+                       "reading the norm")))
+        break;
+      if ((st = fv_hip(c, hipEventRecord(c->ev, c->s), "recording the norm event"))) break;
+      if (more) ec = coarse_cycle(c, 1);
+      if ((st = fv_launch_check(c, "V-cycle"))) break;
+      if ((st = fv_hip(c, hipEventSynchronize(c->ev), "waiting for the norm"))) break;
+      rn = std::sqrt(*c->hnorm);
+      if (!more || !std::isfinite(rn) || rn <= tol) break;
+      top_up(c, f, u, cur, ec);
+    }
+  } else {
     norm2(c, f, u);
-    if ((st = fv_launch_check(c, "norm"))) break;
-    if ((st = read_norm(c, &rn2))) break;
+    st = fv_launch_check(c, "norm");
+    if (!st) st = read_norm(c, &rn2);
     rn = std::sqrt(rn2);
+    while (!st && std::isfinite(rn) && rn > tol && k < c->g.max_cycles) {
+      if ((st = vcycle_impl(c, f, u))) break;
+      ++k;
+      norm2(c, f, u);
+      if ((st = fv_launch_check(c, "norm"))) break;
+      if ((st = read_norm(c, &rn2))) break;
+      rn = std::sqrt(rn2);
+    }
   }
   if (cycles) *cycles = k;
   if (resnorm) *resnorm = rn;

@@ -181,6 +181,15 @@ void fv_jacobi_prolong_tiled(hipStream_t s, int N, double h, double omega, const
 // fc's ghost layer is not written
 void fv_restrict_tiled(hipStream_t s, int N, double h, const double* f, const double* u,
                        double* fc, double* partial);
+// Blocked passes (mg_fv_tiled.hip), 2 or 3 sweeps per launch, out of place: out = Jacobi^sweeps
+// of u (nullptr: of an identically zero u, ghost layer included) or, with ec, of u + P ec (ec:
+// coarse cells, ghost layer not read).  fc: also the restricted residual of out (coarse cells
+// only).  norm2 (with u and fc): also norm2[0] = sum over cells of (f - A u)^2, the input's
+// residual; partial: kStreamPartials doubles.  out's ghost layer is not written; a second sweep
+// reads the ghosts of u, so u and out must hold the same.
+void fv_sweeps(hipStream_t s, int N, double h, double omega, int sweeps, const double* u,
+               const double* f, const double* ec, double* out, double* fc, double* partial,
+               double* norm2);
 // out = sum over cells of (f - A u)^2 (partial: kStreamPartials doubles)
 void fv_norm2_tiled(hipStream_t s, int N, double h, const double* f, const double* u,
                     double* partial, double* out);

@@ -200,18 +200,40 @@ bool use_tiled(const mg_ctx* c, int l)
   return (c->fuse & MG_FUSE_BLOCKED) && mgk::rbgs_tiled_supported(c->g.dim, c->lv[l].n);
 }
 
+// 2D levels outside the coarse tail: the marching strips of mg_smooth_2d.hip
+bool use_strips(const mg_ctx* c) { return (c->fuse & MG_FUSE_BLOCKED) && c->g.dim == 2; }
+
+// Whether a level is smoothed out of place, alternating with its second buffer.
+bool use_blocked(const mg_ctx* c, int l) { return use_tiled(c, l) || use_strips(c); }
+
+// Whether the smoothing before a restriction can also form and restrict the residual: in 3D a
+// single 2-sweep pass with a constant coefficient, in 2D any last pass.
+template <typename T>
+bool fuses_restrict(const mg_ctx* c, int l, bool var)
+{
+  if (!(c->fuse & MG_FUSE_RESTRICT) || c->g.nu1 < 1) return false;
+  if (use_strips(c)) return true;
+  return use_tiled(c, l) && c->g.nu1 == 2 && mgk::rbgs_tiled_max_sweeps(var, sizeof(T)) == 2 &&
+         mgk::rbgs_tiled_fuses_restrict(sizeof(T), var);
+}
+
+// Whether level 0's post-smoothing can also form the residual norm of its result.
+bool fuses_norm(const mg_ctx* c) { return use_strips(c) && c->g.nu2 > 0; }
+
 // `sweeps` red-black sweeps on level l.  u holds the iterate, t is the level's second
 // buffer (same boundary values as u).  Returns the buffer that holds the result: the
-// fused kernel works out of place and alternates between u and t.  zero_guess: u is known
-// to be 0 (a coarse-grid correction) and is not read.
+// fused kernels work out of place and alternate between u and t.  zero_guess: u is known
+// to be 0 (a coarse-grid correction) and is not read.  ec: the sweeps start from u + P ec.
+// fc (fuses_restrict): receives the restricted residual of the result.  norm (fuses_norm):
+// receives the squared norm of that residual.
 template <typename T>
 T* smooth(mg_ctx* c, int l, T* u, T* t, const T* f, const T* k, int sweeps, bool zero_guess,
-          const T* ec = nullptr, T* fc = nullptr)
+          const T* ec = nullptr, T* fc = nullptr, double* norm = nullptr)
 {
   const Level& L = c->lv[l];
   const int dim = c->g.dim;
-  const bool tiled = use_tiled(c, l);
-  // the blocked pass that takes the correction is the first one: two sweeps unless only one
+  const bool tiled = use_tiled(c, l), strips = use_strips(c);
+  // the blocked 3D pass that takes the correction is the first one: two sweeps unless only one
   // is asked for (FP64 passes fuse the correction into 2-sweep passes only)
   const bool pair = sweeps >= 2 && mgk::rbgs_tiled_max_sweeps(k != nullptr, sizeof(T)) == 2;
   if (ec && (sweeps == 0 || !(c->fuse & MG_FUSE_PROLONG) ||
@@ -229,16 +251,21 @@ T* smooth(mg_ctx* c, int l, T* u, T* t, const T* f, const T* k, int sweeps, bool
     mgk::fill<T>(c->s, L.N, T(0), u);
     zero_guess = false;
   }
-  if (tiled) {
+  if (tiled || strips) {
     T* cur = u;
     T* other = t;
     int left = sweeps;
     bool zero = zero_guess;
-    const int maxsw = mgk::rbgs_tiled_max_sweeps(k != nullptr, sizeof(T));
+    const int maxsw = strips ? 2 : mgk::rbgs_tiled_max_sweeps(k != nullptr, sizeof(T));
     while (left > 0) {
       const int sw = left >= maxsw ? maxsw : left;
-      // fc: the residual restriction rides on the (single) pre-smoothing pass
-      mgk::rbgs_tiled<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, left == sw ? fc : nullptr);
+      // fc, norm: taken by the last pass
+      T* rfc = left == sw ? fc : nullptr;
+      if (strips)
+        mgk::rbgs_strips<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, rfc, c->partial,
+                            left == sw ? norm : nullptr);
+      else
+        mgk::rbgs_tiled<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, rfc);
       T* x = cur;
       cur = other;
       other = x;
@@ -256,6 +283,27 @@ T* smooth(mg_ctx* c, int l, T* u, T* t, const T* f, const T* k, int sweeps, bool
     mgk::rbgs_colour<T>(c->s, dim, L.n, L.h, k, f, u, 1);
   }
   return u;
+}
+
+template <typename T>
+T* cycle(mg_ctx* c, int l, T* u, T* t, const T* f, bool zero_guess);
+
+// The V-cycle's way down on level l < coarsest: pre-smoothing from x in u (t: the second buffer),
+// the restricted residual and the coarse correction.  Returns the smoothed iterate's buffer; the
+// correction in ec.
+template <typename T>
+T* cycle_down(mg_ctx* c, int l, T* u, T* t, const T* f, bool zero_guess, T** ec)
+{
+  const Level& L = c->lv[l];
+  const View<T> V = view<T>(c, l), C = view<T>(c, l + 1);
+  const bool fuse_r = fuses_restrict<T>(c, l, V.k != nullptr);
+  T* cur = smooth<T>(c, l, u, t, f, V.k, c->g.nu1, zero_guess, nullptr, fuse_r ? C.f : nullptr);
+  if (!fuse_r) {
+    if (use_tiled(c, l)) mgk::restrict_residual_tiled<T>(c->s, L.n, L.h, V.k, f, cur, C.f);
+    else mgk::restrict_residual<T>(c->s, c->g.dim, L.n, L.h, V.k, f, cur, C.f);
+  }
+  *ec = cycle<T>(c, l + 1, C.u, C.t, C.f, true);
+  return cur;
 }
 
 // One V(nu1,nu2)-cycle on level l for A_l x = f with x in u (or, when zero_guess, x = 0).
@@ -285,26 +333,16 @@ T* cycle(mg_ctx* c, int l, T* u, T* t, const T* f, bool zero_guess)
     mgk::coarsest_solve<T>(c->s, dim, L.n, c->ainv, f, u);
     return u;
   }
-  const View<T> C = view<T>(c, l + 1);
-  // residual + restriction inside the pre-smoothing pass: one 2-sweep pass with constant
-  // coefficients (rbgs_tiled_fuses_restrict)
-  const bool fuse_r = use_tiled(c, l) && (c->fuse & MG_FUSE_RESTRICT) && c->g.nu1 == 2 &&
-                      mgk::rbgs_tiled_max_sweeps(V.k != nullptr, sizeof(T)) == 2 &&
-                      mgk::rbgs_tiled_fuses_restrict(sizeof(T), V.k != nullptr);
-  T* cur = smooth<T>(c, l, u, t, f, V.k, c->g.nu1, zero_guess, nullptr, fuse_r ? C.f : nullptr);
-  if (!fuse_r) {
-    if (use_tiled(c, l)) mgk::restrict_residual_tiled<T>(c->s, L.n, L.h, V.k, f, cur, C.f);
-    else mgk::restrict_residual<T>(c->s, dim, L.n, L.h, V.k, f, cur, C.f);
-  }
-  T* ec = cycle<T>(c, l + 1, C.u, C.t, C.f, true);
+  T* ec = nullptr;
+  T* cur = cycle_down<T>(c, l, u, t, f, zero_guess, &ec);
   // u += P ec, fused into the first post-smoothing pass on large 3D levels (FP32)
   T* other = cur == u ? t : u;
   return smooth<T>(c, l, cur, other, f, V.k, c->g.nu2, false, ec);
 }
 
-mg_status read_scalar(mg_ctx* c, const double* dev, double* host)
+mg_status read_scalar(mg_ctx* c, const double* dev, double* host, int count = 1)
 {
-  mg_status st = hip_check(c, hipMemcpyAsync(host, dev, sizeof(double), hipMemcpyDeviceToHost, c->s),
+  mg_status st = hip_check(c, hipMemcpyAsync(host, dev, count * sizeof(double), hipMemcpyDeviceToHost, c->s),
                            "reading a norm");
   if (st) return st;
   return hip_check(c, hipStreamSynchronize(c->s), "stream synchronisation");
@@ -345,13 +383,29 @@ mg_status ir_step(mg_ctx* c, const double* f, double* u, double scale)
   return launch_check(c, "refinement step");
 }
 
-// One FP64 cycle on the caller's (f, u); the result ends in u.
-mg_status f64_cycle(mg_ctx* c, const double* f, double* u)
+// The two halves of an FP64 cycle on the caller's (f, u).  The way up leaves the result in u
+// and, with norm, the squared residual norm of the result in scal[0].
+double* f64_down(mg_ctx* c, const double* f, double* u, double** ec)
+{
+  return cycle_down<double>(c, 0, u, c->lv[0].t, f, false, ec);
+}
+
+mg_status f64_up(mg_ctx* c, const double* f, double* u, double* cur, const double* ec, bool norm)
 {
   Level& L0 = c->lv[0];
-  double* r = cycle<double>(c, 0, u, L0.t, f, false);
+  const bool ride = norm && fuses_norm(c);
+  double* r = smooth<double>(c, 0, cur, cur == u ? L0.t : u, f, L0.k, c->g.nu2, false, ec, nullptr,
+                             ride ? c->scal : nullptr);
   if (r != u) mgk::copy<double>(c->s, L0.N, r, u);
+  if (norm && !ride) norm2(c, f, u, 0, 0);
   return launch_check(c, "V-cycle");
+}
+
+// Whether the way down of the next cycle leaves u alone: one out-of-place pre-smoothing pass.
+bool down_keeps_u(const mg_ctx* c)
+{
+  return use_blocked(c, 0) && c->g.nu1 >= 1 && c->g.nu1 <= 2 &&
+         (use_strips(c) || mgk::rbgs_tiled_max_sweeps(c->g.variable, sizeof(double)) >= c->g.nu1);
 }
 
 mg_status check_ready(mg_ctx* c)
@@ -419,8 +473,7 @@ mg_status fused_ir_cycle(mg_ctx* c, const double* f, const double* u, double* uo
 {
   const Level& L0 = c->lv[0];
   const View<float> C = view<float>(c, 1);
-  const bool fuse_r = (c->fuse & MG_FUSE_RESTRICT) && c->g.nu1 == 2 &&
-                      mgk::rbgs_tiled_fuses_restrict(sizeof(float), false);
+  const bool fuse_r = fuses_restrict<float>(c, 0, false);
   float* cur = smooth<float>(c, 0, st.u, st.t, st.rhs, nullptr, c->g.nu1, true, nullptr,
                              fuse_r ? C.f : nullptr);
   if (!fuse_r) mgk::restrict_residual_tiled<float>(c->s, L0.n, L0.h, nullptr, st.rhs, cur, C.f);
@@ -557,6 +610,52 @@ mg_status solve_ir_streamed(mg_ctx* c, const double* f, double* u, double tol, d
   return finish(c, k, rel, tol, cycles, relres, st);
 }
 
+// Refinement with the per-step kernels (2D grids and 3D grids too small for the streamed
+// passes).  A step is one FP32 V-cycle on r32, u += scale e, and the residual of the new iterate
+// with its norm and the next r32; the scale of that r32 comes from the previous residual (powers
+// of two change no float result).  The norm's read-back overlaps the next cycle as in
+// solve_ir_streamed.
+mg_status solve_ir_plain(mg_ctx* c, const double* f, double* u, double tol, double bn, double rn,
+                         int* cycles, double* relres)
+{
+  Level& L0 = c->lv[0];
+  const int dim = c->g.dim;
+  const bool overlap = c->hnorm != nullptr && c->ev != nullptr;
+  double rel = rn / bn, rel_prev = NAN, scale = ir_scale(c, rn), rn2 = 0;
+  float* e = nullptr;  // the correction of a cycle already enqueued
+  int k = 0;
+  mg_status st = MG_OK;
+  if (std::isfinite(rel) && rel > tol)
+    mgk::ir_residual(c->s, dim, L0.n, L0.h, L0.k, f, u, 1.0 / scale, L0.f32, c->partial, c->scal);
+  while (std::isfinite(rel) && rel > tol && k < c->g.max_cycles) {
+    if (!e) e = cycle<float>(c, 0, L0.u32, L0.t32, L0.f32, true);
+    const double next = ir_scale(c, rn);
+    mgk::ir_update(c->s, dim, L0.n, scale, e, u);
+    mgk::ir_residual(c->s, dim, L0.n, L0.h, L0.k, f, u, 1.0 / next, L0.f32, c->partial, c->scal);
+    e = nullptr;
+    scale = next;
+    ++k;
+    if ((st = launch_check(c, "refinement step"))) break;
+    const double rho = std::isfinite(rel_prev) && rel_prev > 0 ? rel / rel_prev : 1.0;
+    const double predicted = k < c->g.max_cycles ? rel * rho : 0.0;
+    rel_prev = rel;
+    if (overlap) {
+      if ((st = read_scalar_start(c, c->scal))) break;
+      if (predicted > 4.0 * tol) {
+        e = cycle<float>(c, 0, L0.u32, L0.t32, L0.f32, true);
+        if ((st = launch_check(c, "V-cycle"))) break;
+      }
+      st = read_scalar_finish(c, &rn2);
+    } else {
+      st = read_scalar(c, c->scal, &rn2);
+    }
+    if (st) break;
+    rn = std::sqrt(rn2);
+    rel = rn / bn;
+  }
+  return finish(c, k, rel, tol, cycles, relres, st);
+}
+
 mg_status solve_impl(mg_ctx* c, const double* f, double* u, double tol, int* cycles,
                      double* relres)
 {
@@ -564,47 +663,59 @@ mg_status solve_impl(mg_ctx* c, const double* f, double* u, double tol, int* cyc
   if (!f || !u) return fail(c, MG_EINVAL, "f and u must be non-NULL");
   if (!(tol > 0) || !std::isfinite(tol)) return fail(c, MG_EINVAL, "tol must be > 0");
   Level& L0 = c->lv[0];
-  if (use_tiled(c, 0)) mgk::copy_boundary(c->s, c->g.dim, L0.n, u, L0.t);
+  const bool ir = c->g.precision == MG_F32_IR;
+  if (use_blocked(c, 0)) mgk::copy_boundary(c->s, c->g.dim, L0.n, u, L0.t);
   // FP32 refinement with the fused pass: once a previous solve gave a right-hand-side
   // scale, the first pass computes the right-hand-side norm itself
-  if (c->g.precision == MG_F32_IR && use_tiled(c, 0) && !c->g.variable && c->last_bn > 0)
+  if (ir && use_tiled(c, 0) && !c->g.variable && c->last_bn > 0)
     return solve_ir_streamed(c, f, u, tol, 0.0, cycles, relres);
-  double bn2 = 0, rn2 = 0;
-  const bool both = use_tiled(c, 0) && !c->g.variable && c->g.precision == MG_F64;
-  if (both) {
-    // residual and right-hand-side norms in one pass (each in its own pass's order)
-    mgk::resid_norm2_both_tiled(c->s, L0.n, L0.h, f, u, c->partial, c->partial_b, c->scal);
-    if (mg_status st = launch_check(c, "norm")) return st;
-    if (mg_status st = read_scalar(c, c->scal + 1, &bn2)) return st;
-    if (mg_status st = read_scalar(c, c->scal, &rn2)) return st;
-  } else {
+  double two[2] = {0, 0};  // squared norms of the residual and of the full right-hand side
+  if (ir && use_tiled(c, 0)) {
     norm2(c, f, u, 1, 1);
     if (mg_status st = launch_check(c, "norm")) return st;
-    if (mg_status st = read_scalar(c, c->scal + 1, &bn2)) return st;
-  }
-  double bn = std::sqrt(bn2);
-  if (!(bn > 0)) bn = 1.0;
-  if (c->g.precision == MG_F32_IR && use_tiled(c, 0))
+    if (mg_status st = read_scalar(c, c->scal + 1, two + 1)) return st;
+    double bn = std::sqrt(two[1]);
+    if (!(bn > 0)) bn = 1.0;
     return solve_ir_streamed(c, f, u, tol, bn, cycles, relres);
-  if (!both) {
-    norm2(c, f, u, 0, 0);
-    if (mg_status st = launch_check(c, "norm")) return st;
-    if (mg_status st = read_scalar(c, c->scal, &rn2)) return st;
   }
-  double rn = std::sqrt(rn2);
-  double rel = rn / bn;
+  if (use_tiled(c, 0) && !c->g.variable) {
+    // both in one pass (each in its own pass's order)
+    mgk::resid_norm2_both_tiled(c->s, L0.n, L0.h, f, u, c->partial, c->partial_b, c->scal);
+  } else {
+    norm2(c, f, u, 1, 1);
+    norm2(c, f, u, 0, 0);
+  }
+  if (mg_status st = launch_check(c, "norm")) return st;
+  if (mg_status st = read_scalar(c, c->scal, two, 2)) return st;
+  double bn = std::sqrt(two[1]);
+  if (!(bn > 0)) bn = 1.0;
+  if (ir) return solve_ir_plain(c, f, u, tol, bn, std::sqrt(two[0]), cycles, relres);
+  double rel = std::sqrt(two[0]) / bn, rel_prev = NAN, rn2 = 0;
+  // The norm's read-back overlaps the next cycle's way down where that leaves u alone: enqueued
+  // before the host waits when the contraction so far says another cycle will be needed, unused
+  // if the tolerance was reached after all.
+  const bool overlap = c->hnorm != nullptr && c->ev != nullptr && down_keeps_u(c);
+  double *down = nullptr, *ec = nullptr;
   int k = 0;
   mg_status st = MG_OK;
   while (std::isfinite(rel) && rel > tol && k < c->g.max_cycles) {
-    if (c->g.precision == MG_F32_IR) st = ir_step(c, f, u, ir_scale(c, rn));
-    else st = f64_cycle(c, f, u);
-    if (st) break;
+    if (!down) down = f64_down(c, f, u, &ec);
+    if ((st = f64_up(c, f, u, down, ec, true))) break;
+    down = nullptr;
     ++k;
-    norm2(c, f, u, 0, 0);
-    if ((st = launch_check(c, "norm"))) break;
-    if ((st = read_scalar(c, c->scal, &rn2))) break;
-    rn = std::sqrt(rn2);
-    rel = rn / bn;
+    const double rho = std::isfinite(rel_prev) && rel_prev > 0 ? rel / rel_prev : 1.0;
+    const double predicted = k < c->g.max_cycles ? rel * rho : 0.0;
+    rel_prev = rel;
+    if (overlap && predicted > 4.0 * tol) {
+      if ((st = read_scalar_start(c, c->scal))) break;
+      down = f64_down(c, f, u, &ec);
+      if ((st = launch_check(c, "V-cycle"))) break;
+      st = read_scalar_finish(c, &rn2);
+    } else {
+      st = read_scalar(c, c->scal, &rn2);
+    }
+    if (st) break;
+    rel = std::sqrt(rn2) / bn;
   }
   return finish(c, k, rel, tol, cycles, relres, st);
 }
@@ -629,7 +740,8 @@ mg_status smooth_impl(mg_ctx* c, int level, const T* f, T* u, int sweeps)
   // the level's second buffer holds the Dirichlet data of u while the fused kernel
   // alternates between the two
   T* t = V.t;
-  if (use_tiled(c, level)) {
+  const bool blocked = use_blocked(c, level);
+  if (blocked) {
     if (sizeof(T) == 8)
       mgk::copy_boundary(c->s, c->g.dim, L.n, reinterpret_cast<const double*>(u),
                          reinterpret_cast<double*>(t));
@@ -638,6 +750,9 @@ mg_status smooth_impl(mg_ctx* c, int level, const T* f, T* u, int sweeps)
   }
   T* r = smooth<T>(c, level, u, t, f, V.k, sweeps, false);
   if (r != u) mgk::copy<T>(c->s, L.N, r, u);
+  // corrections have zero Dirichlet data: the second buffer gets its zero boundary back (level
+  // 0's FP64 one takes u's at every solve)
+  if (blocked && (level > 0 || sizeof(T) == 4)) mgk::zero_boundary<T>(c->s, c->g.dim, L.n, t);
   return launch_check(c, "smoothing");
 }
 
@@ -745,9 +860,8 @@ mg_status mg_setup(const mg_grid* grid, void* workspace, size_t bytes, void* str
   mg_ctx* c = new (std::nothrow) mg_ctx;
   if (!c) return fail(nullptr, MG_ENOMEM, "host allocation of the context failed");
   mg_status st = init_ctx(c, grid, workspace, need, static_cast<hipStream_t>(stream));
-  // one pinned host word for overlapped norm reads (FP32 refinement); without it the solve
-  // reads synchronously
-  if (!st && grid->precision == MG_F32_IR) {
+  // one pinned host word for overlapped norm reads; without it the solve reads synchronously
+  if (!st) {
     void* hp = nullptr;
     if (hipHostMalloc(&hp, 64, hipHostMallocDefault) == hipSuccess) {
       c->hnorm = static_cast<double*>(hp);
@@ -777,14 +891,16 @@ mg_status mg_vcycle(mg_ctx* c, const double* f, double* u)
   if (mg_status st = check_ready(c)) return st;
   if (!f || !u) return fail(c, MG_EINVAL, "f and u must be non-NULL");
   Level& L0 = c->lv[0];
-  if (use_tiled(c, 0)) mgk::copy_boundary(c->s, c->g.dim, L0.n, u, L0.t);
+  if (use_blocked(c, 0)) mgk::copy_boundary(c->s, c->g.dim, L0.n, u, L0.t);
   if (c->g.precision == MG_F32_IR) {
     double rn2 = 0;
     norm2(c, f, u, 0, 0);
     if (mg_status st = read_scalar(c, c->scal, &rn2)) return st;
     return ir_step(c, f, u, ir_scale(c, std::sqrt(rn2)));
   }
-  return f64_cycle(c, f, u);
+  double* ec = nullptr;
+  double* cur = f64_down(c, f, u, &ec);
+  return f64_up(c, f, u, cur, ec, false);
 }
 
 mg_status mg_solve(mg_ctx* c, const double* f, double* u, double tol, int* cycles,

@@ -65,6 +65,15 @@ bool rbgs_tiled_refine_fits(int n);
 // squares sum to norm2[0]: the scales of the first two right-hand sides of a fused solve.
 void ir_scales_init(hipStream_t s, int n, const double* norm2, double scale0, double* ss);
 
+// The 2D counterpart (mg_smooth_2d.hip): `sweeps` (1 or 2) red-black sweeps in one launch, out of
+// place, from u, from 0 (zero: u is not read) or from u + P ec.  fc: also the restricted residual
+// of the result (interior; not with ec).  norm2 (double; not with fc or zero): also norm2[0] =
+// sum of squares of the result's residual; partial: kStreamPartials doubles.  Boundaries of out
+// and fc are not written.
+template <typename T>
+void rbgs_strips(hipStream_t s, int n, double h, const T* k, const T* f, const T* u, T* out,
+                 int sweeps, bool zero, const T* ec, T* fc, double* partial, double* norm2);
+
 // r = f - A u (interior), 0 on the boundary.
 template <typename T>
 void residual(hipStream_t s, int dim, int n, double h, const T* k, const T* f, const T* u,
@@ -161,7 +170,8 @@ void copy(hipStream_t s, size_t count, const T* src, T* dst);
 // Copies the boundary nodes of src into dst.
 void copy_boundary(hipStream_t s, int dim, int n, const double* src, double* dst);
 // Sets the boundary nodes of p to 0.
-void zero_boundary(hipStream_t s, int dim, int n, double* p);
+template <typename T>
+void zero_boundary(hipStream_t s, int dim, int n, T* p);
 
 // ---- cell-centred finite volumes (N^3 cells, arrays of (N+2)^3 values with a ghost layer
 // holding the Dirichlet value at the adjacent face centre; a ghost neighbour enters the

@@ -494,8 +494,9 @@ __device__ __forceinline__ bool face_node(int dim, int n, int face, int a, int b
   return true;
 }
 
+template <typename T>
 __global__ void __launch_bounds__(kBlock)
-    k_boundary(const double* __restrict__ src, double* __restrict__ dst, int dim, int n)
+    k_boundary(const T* __restrict__ src, T* __restrict__ dst, int dim, int n)
 {
   const int a = blockIdx.x * blockDim.x + threadIdx.x;
   const int b = blockIdx.y;
@@ -503,7 +504,7 @@ __global__ void __launch_bounds__(kBlock)
   if (a >= n) return;
   size_t i;
   if (!face_node(dim, n, face, a, b, i)) return;
-  dst[i] = src ? src[i] : 0.0;
+  dst[i] = src ? src[i] : T(0);
 }
 
 inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
@@ -698,15 +699,20 @@ void copy_boundary(hipStream_t s, int dim, int n, const double* src, double* dst
 {
   const int bx = n >= 256 ? 256 : 64;
   const dim3 grid(cdiv(n, bx), dim == 3 ? n : 1, 2 * dim);
-  k_boundary<<<grid, bx, 0, s>>>(src, dst, dim, n);
+  k_boundary<double><<<grid, bx, 0, s>>>(src, dst, dim, n);
 }
 
-void zero_boundary(hipStream_t s, int dim, int n, double* p)
+template <typename T>
+void zero_boundary(hipStream_t s, int dim, int n, T* p)
 {
-  copy_boundary(s, dim, n, nullptr, p);
+  const int bx = n >= 256 ? 256 : 64;
+  const dim3 grid(cdiv(n, bx), dim == 3 ? n : 1, 2 * dim);
+  k_boundary<T><<<grid, bx, 0, s>>>(nullptr, p, dim, n);
 }
 
 // explicit instantiations
+template void zero_boundary<double>(hipStream_t, int, int, double*);
+template void zero_boundary<float>(hipStream_t, int, int, float*);
 template void rbgs_colour<double>(hipStream_t, int, int, double, const double*, const double*, double*, int);
 template void rbgs_colour<float>(hipStream_t, int, int, double, const float*, const float*, float*, int);
 template void rbgs_first<double>(hipStream_t, int, int, double, const double*, const double*, double*, const double*);

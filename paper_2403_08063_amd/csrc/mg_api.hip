@@ -324,7 +324,7 @@ T* cycle(mg_ctx* c, int l, T* u, T* t, const T* f, bool zero_guess)
     for (int q = 0; q < a.nlev; ++q) {
       const View<T> W = view<T>(c, l + q);
       const double h = c->lv[l + q].h;
-      a.lv[q] = {W.u, W.f, W.k, c->lv[l + q].n, (T)(h * h), (T)(1.0 / (h * h))};
+      a.lv[q] = {W.u, W.f, W.k, c->lv[l + q].n, (T)(h * h), (T)(1.0 / (h * h)), 0, 0, 0};
     }
     mgk::tail_cycle<T>(c->s, dim, a);
     return u;

@@ -152,6 +152,7 @@ struct TailLevel {
   const T* k;  // nullptr: constant coefficient
   int n;
   T h2, ih2;   // h^2 and 1/h^2 of the level, as the per-level kernels round them
+  unsigned div_half, div_m, div_n;  // reciprocals for index division, set by tail_cycle
 };
 template <typename T>
 struct TailArgs {
@@ -161,7 +162,7 @@ struct TailArgs {
 };
 bool tail_fits(int dim, int n);
 template <typename T>
-void tail_cycle(hipStream_t s, int dim, const TailArgs<T>& a);
+void tail_cycle(hipStream_t s, int dim, TailArgs<T> a);
 
 template <typename T>
 void fill(hipStream_t s, size_t count, T value, T* p);

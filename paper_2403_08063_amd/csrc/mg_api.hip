@@ -203,16 +203,22 @@ bool use_tiled(const mg_ctx* c, int l)
 // 2D levels outside the coarse tail: the marching strips of mg_smooth_2d.hip
 bool use_strips(const mg_ctx* c) { return (c->fuse & MG_FUSE_BLOCKED) && c->g.dim == 2; }
 
+// Small 3D levels outside the tail: the LDS cubes of mg_smooth_cube.hip.
+bool use_cube(const mg_ctx* c, int l)
+{
+  return (c->fuse & MG_FUSE_BLOCKED) && mgk::rbgs_cube_supported(c->g.dim, c->lv[l].n);
+}
+
 // Whether a level is smoothed out of place, alternating with its second buffer.
-bool use_blocked(const mg_ctx* c, int l) { return use_tiled(c, l) || use_strips(c); }
+bool use_blocked(const mg_ctx* c, int l) { return use_tiled(c, l) || use_strips(c) || use_cube(c, l); }
 
 // Whether the smoothing before a restriction can also form and restrict the residual: in 3D a
-// single 2-sweep pass with a constant coefficient, in 2D any last pass.
+// single 2-sweep pass with a constant coefficient on the large levels, else any last pass.
 template <typename T>
 bool fuses_restrict(const mg_ctx* c, int l, bool var)
 {
   if (!(c->fuse & MG_FUSE_RESTRICT) || c->g.nu1 < 1) return false;
-  if (use_strips(c)) return true;
+  if (use_strips(c) || use_cube(c, l)) return true;
   return use_tiled(c, l) && c->g.nu1 == 2 && mgk::rbgs_tiled_max_sweeps(var, sizeof(T)) == 2 &&
          mgk::rbgs_tiled_fuses_restrict(sizeof(T), var);
 }
@@ -232,7 +238,7 @@ T* smooth(mg_ctx* c, int l, T* u, T* t, const T* f, const T* k, int sweeps, bool
 {
   const Level& L = c->lv[l];
   const int dim = c->g.dim;
-  const bool tiled = use_tiled(c, l), strips = use_strips(c);
+  const bool tiled = use_tiled(c, l), strips = use_strips(c), cube = use_cube(c, l);
   // the blocked 3D pass that takes the correction is the first one: two sweeps unless only one
   // is asked for (FP64 passes fuse the correction into 2-sweep passes only)
   const bool pair = sweeps >= 2 && mgk::rbgs_tiled_max_sweeps(k != nullptr, sizeof(T)) == 2;
@@ -251,12 +257,12 @@ T* smooth(mg_ctx* c, int l, T* u, T* t, const T* f, const T* k, int sweeps, bool
     mgk::fill<T>(c->s, L.N, T(0), u);
     zero_guess = false;
   }
-  if (tiled || strips) {
+  if (tiled || strips || cube) {
     T* cur = u;
     T* other = t;
     int left = sweeps;
     bool zero = zero_guess;
-    const int maxsw = strips ? 2 : mgk::rbgs_tiled_max_sweeps(k != nullptr, sizeof(T));
+    const int maxsw = strips || cube ? 2 : mgk::rbgs_tiled_max_sweeps(k != nullptr, sizeof(T));
     while (left > 0) {
       const int sw = left >= maxsw ? maxsw : left;
       // fc, norm: taken by the last pass
@@ -264,6 +270,8 @@ T* smooth(mg_ctx* c, int l, T* u, T* t, const T* f, const T* k, int sweeps, bool
       if (strips)
         mgk::rbgs_strips<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, rfc, c->partial,
                             left == sw ? norm : nullptr);
+      else if (cube)
+        mgk::rbgs_cube<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, rfc);
       else
         mgk::rbgs_tiled<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, rfc);
       T* x = cur;
@@ -405,7 +413,7 @@ mg_status f64_up(mg_ctx* c, const double* f, double* u, double* cur, const doubl
 bool down_keeps_u(const mg_ctx* c)
 {
   return use_blocked(c, 0) && c->g.nu1 >= 1 && c->g.nu1 <= 2 &&
-         (use_strips(c) || mgk::rbgs_tiled_max_sweeps(c->g.variable, sizeof(double)) >= c->g.nu1);
+         (use_strips(c) || use_cube(c, 0) || mgk::rbgs_tiled_max_sweeps(c->g.variable, sizeof(double)) >= c->g.nu1);
 }
 
 mg_status check_ready(mg_ctx* c)

@@ -74,6 +74,13 @@ template <typename T>
 void rbgs_strips(hipStream_t s, int n, double h, const T* k, const T* f, const T* u, T* out,
                  int sweeps, bool zero, const T* ec, T* fc, double* partial, double* norm2);
 
+// The counterpart for small 3D levels (mg_smooth_cube.hip, up to 65 nodes a side): as rbgs_strips,
+// without the norm.
+bool rbgs_cube_supported(int dim, int n);
+template <typename T>
+void rbgs_cube(hipStream_t s, int n, double h, const T* k, const T* f, const T* u, T* out, int sweeps,
+               bool zero, const T* ec, T* fc);
+
 // r = f - A u (interior), 0 on the boundary.
 template <typename T>
 void residual(hipStream_t s, int dim, int n, double h, const T* k, const T* f, const T* u,

@@ -1,9 +1,10 @@
 // Galerkin coarsening of the variable-coefficient operator behind the C ABI of
 // include/mg_galerkin.h.  Level 0 runs the 7-point kernels of mg_kernels.hip (red-black
 // Gauss-Seidel with face coefficients, residual + full weighting, trilinear prolongation,
-// norms); the coarse levels hold 27-point stencils built on the GPU by probing R A P with
-// combs of coarse nodes, and run the kernels below: eight-colour Gauss-Seidel, residual with
-// full weighting, and the exact solve of the one-node coarsest level.  A coarse level stores
+// norms); the coarse levels hold 27-point stencils R A P built on the GPU from the finer level's
+// coefficients, and run the kernels below: eight-colour Gauss-Seidel, residual with full
+// weighting, and, from 17^3 nodes down to the exact solve of the one-node coarsest level, the
+// whole V-cycle in one launch.  A coarse level stores
 // its stencil colour-major: for each of the eight parity colours, 27 arrays over that colour's
 // nodes in C order, so that a colour pass of the smoother reads its coefficients contiguously.
 #include "../../include/mg_galerkin.h"
@@ -65,22 +66,33 @@ __device__ __forceinline__ double offdiag(const TS* __restrict__ Sn, size_t h3,
   return s;
 }
 
-// one colour of eight-colour Gauss-Seidel: nodes with parities (pz, py, px) of colour c
-template <typename TS>
+// One colour C of eight-colour Gauss-Seidel: nodes with parities (pz, py, px) = bits of C.  ZERO: the
+// first sweep from a zero iterate, which is not read before it is written: only the neighbours of
+// the colours before C count (the colour of a neighbour is C with the parities of the offset's
+// nonzero components flipped), which halves the coefficients read over the sweep.
+template <typename TS, int C, bool ZERO>
 __global__ void __launch_bounds__(kGalThreads)
-    k_gal_gs(int n, const TS* __restrict__ S, const double* __restrict__ f, double* u, int c)
+    k_gal_gs(int n, const TS* __restrict__ S, const double* __restrict__ f, double* u)
 {
   const int half = (n - 1) / 2;
   const int t = blockIdx.x * kGalThreads + threadIdx.x;
   if (t >= half * half * half) return;
-  const int px = c & 1, py = (c >> 1) & 1, pz = c >> 2;
+  constexpr int px = C & 1, py = (C >> 1) & 1, pz = C >> 2;
   // interior index with parity p: 2 j + 2 - p  (p = 1: 1, 3, ..; p = 0: 2, 4, ..)
   const int x = 2 * (t % half) + 2 - px, y = 2 * ((t / half) % half) + 2 - py, z = 2 * (t / (half * half)) + 2 - pz;
   if (x > n - 2 || y > n - 2 || z > n - 2) return;
   const size_t h3 = (size_t)half * half * half;
-  const TS* Sn = S + (size_t)c * 27 * h3 + t;
+  const TS* Sn = S + (size_t)C * 27 * h3 + t;
   const size_t i = gidx(n, z, y, x);
-  u[i] = (f[i] - offdiag(Sn, h3, u, n, z, y, x)) / (double)Sn[kCentre * h3];
+  double s = 0.0;
+#pragma unroll
+  for (int o = 0; o < 27; ++o) {
+    const int dz = o / 9 - 1, dy = (o / 3) % 3 - 1, dx = o % 3 - 1;
+    const int nb = C ^ ((dz ? 4 : 0) | (dy ? 2 : 0) | (dx ? 1 : 0));
+    if (o == kCentre || (ZERO && nb > C)) continue;
+    s += (double)Sn[o * h3] * u[gidx(n, z + dz, y + dy, x + dx)];
+  }
+  u[i] = (f[i] - s) / (double)Sn[kCentre * h3];
 }
 
 // r = f - A u at interior nodes (f == nullptr reads 0); the boundary of r is not written
@@ -119,32 +131,120 @@ __global__ void __launch_bounds__(kGalThreads)
   fc[gidx(nc, Z, Y, X)] = s;
 }
 
-// e = the comb of residue class (cz, cy, cx): 1 at interior nodes J with J_a = c_a mod 3
-__global__ void __launch_bounds__(kGalThreads)
-    k_gal_comb(int n, int cz, int cy, int cx, double* __restrict__ e)
-{
-  const size_t t = (size_t)blockIdx.x * kGalThreads + threadIdx.x;
-  const size_t cnt = (size_t)n * n * n;
-  if (t >= cnt) return;
-  const int x = (int)(t % n), y = (int)((t / n) % n), z = (int)(t / ((size_t)n * n));
-  const bool in = x > 0 && y > 0 && z > 0 && x < n - 1 && y < n - 1 && z < n - 1;
-  e[t] = in && x % 3 == cx && y % 3 == cy && z % 3 == cz ? 1.0 : 0.0;
-}
+// The Galerkin operator of the next level, one thread per coarse interior node I:
+//   S_c[I][s] = sum_a w_a sum_b A[2I + a][b] P(2I + a + b, I + s)
+// over the fine nodes 2I + a of the full weighting (w = 1/4, 1/2, 1/4 per axis), the couplings b of
+// the fine operator and the coarse neighbours s, with P the trilinear interpolation (per axis: a
+// fine node at distance 0 takes 1, at distance 1 takes 1/2 of the coarse value).  The 27 values of
+// each fine row are contracted axis by axis.  One pass over the fine coefficients per level, where
+// probing with 27 combs of coarse nodes took 27 prolongations, residuals and restrictions of
+// whole levels: RAP_US
+struct RapSum {
+  double c[3][3][3] = {};  // [z][y][x] offset + 1 of the coarse neighbour
+  // adds w times the fine row A (27 couplings at offset o = 9 (dz+1) + 3 (dy+1) + dx+1) of the
+  // fine node at distance (az, ay, ax) from 2I
+  __device__ __forceinline__ void add(double w, const double (&A)[27], int az, int ay, int ax)
+  {
+    auto p = [](int t, int s) {  // weight of coarse offset s for a fine node at distance t from 2I
+      const int d = t - 2 * s;
+      return d == 0 ? 1.0 : d == 1 || d == -1 ? 0.5 : 0.0;
+    };
+    double Y[3][3][3] = {};  // [dz][sy][sx]
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+        for (int sx = 0; sx < 3; ++sx) {
+          double X = 0.0;
+#pragma unroll
+          for (int dx = 0; dx < 3; ++dx) X += A[9 * dz + 3 * dy + dx] * p(ax + dx - 1, sx - 1);
+#pragma unroll
+          for (int sy = 0; sy < 3; ++sy) Y[dz][sy][sx] += X * p(ay + dy - 1, sy - 1);
+        }
+#pragma unroll
+    for (int dz = 0; dz < 3; ++dz)
+#pragma unroll
+      for (int sz = 0; sz < 3; ++sz) {
+        const double q = w * p(az + dz - 1, sz - 1);
+#pragma unroll
+        for (int sy = 0; sy < 3; ++sy)
+#pragma unroll
+          for (int sx = 0; sx < 3; ++sx) c[sz][sy][sx] += q * Y[dz][sy][sx];
+      }
+  }
+};
 
-// S[o][I] = -fc[I] at coarse interior nodes, o the offset to I's neighbour of class c
-__global__ void __launch_bounds__(kGalThreads)
-    k_gal_scatter(int nc, int cz, int cy, int cx, const double* __restrict__ fc,
-                  double* __restrict__ S)
+// coarse node t of a level with nc nodes per side; false past the last
+__device__ __forceinline__ bool rap_node(int nc, int t, int& Z, int& Y, int& X)
 {
   const int m = nc - 2;
-  const int t = blockIdx.x * kGalThreads + threadIdx.x;
-  if (t >= m * m * m) return;
-  const int X = 1 + t % m, Y = 1 + (t / m) % m, Z = 1 + t / (m * m);
-  auto off = [](int c, int I) { const int r = ((c - I) % 3 + 3) % 3; return r == 2 ? -1 : r; };
-  const int o = 9 * (off(cz, Z) + 1) + 3 * (off(cy, Y) + 1) + (off(cx, X) + 1);
+  X = 1 + t % m;
+  Y = 1 + (t / m) % m;
+  Z = 1 + t / (m * m);
+  return t < m * m * m;
+}
+
+// couplings that leave the interior are 0
+__device__ __forceinline__ void rap_store(const RapSum& R, int nc, int Z, int Y, int X, double* __restrict__ S)
+{
   const int half = (nc - 1) / 2;
   const size_t h3 = (size_t)half * half * half;
-  const_cast<double*>(node_coeffs(S, half, Z, Y, X))[o * h3] = -fc[gidx(nc, Z, Y, X)];
+  double* Sn = const_cast<double*>(node_coeffs(S, half, Z, Y, X));
+#pragma unroll
+  for (int o = 0; o < 27; ++o) {
+    const int dz = o / 9 - 1, dy = (o / 3) % 3 - 1, dx = o % 3 - 1;
+    const bool in = Z + dz >= 1 && Z + dz <= nc - 2 && Y + dy >= 1 && Y + dy <= nc - 2 && X + dx >= 1 && X + dx <= nc - 2;
+    Sn[o * h3] = in ? R.c[dz + 1][dy + 1][dx + 1] : 0.0;
+  }
+}
+
+// from the 7-point operator of coefficient k (nc: coarse nodes per side)
+__global__ void __launch_bounds__(kGalThreads)
+    k_gal_rap_fine(int nc, double ih2, const double* __restrict__ k, double* __restrict__ S)
+{
+  int Z, Y, X;
+  if (!rap_node(nc, blockIdx.x * kGalThreads + threadIdx.x, Z, Y, X)) return;
+  const int n = 2 * (nc - 1) + 1;
+  RapSum R;
+  for (int a = 0; a < 27; ++a) {
+    const int az = a / 9 - 1, ay = (a / 3) % 3 - 1, ax = a % 3 - 1;
+    const int z = 2 * Z + az, y = 2 * Y + ay, x = 2 * X + ax;
+    const double ki = k[gidx(n, z, y, x)];
+    const double c0 = 0.5 * (ki + k[gidx(n, z, y, x - 1)]) * ih2, c1 = 0.5 * (ki + k[gidx(n, z, y, x + 1)]) * ih2;
+    const double c2 = 0.5 * (ki + k[gidx(n, z, y - 1, x)]) * ih2, c3 = 0.5 * (ki + k[gidx(n, z, y + 1, x)]) * ih2;
+    const double c4 = 0.5 * (ki + k[gidx(n, z - 1, y, x)]) * ih2, c5 = 0.5 * (ki + k[gidx(n, z + 1, y, x)]) * ih2;
+    double A[27] = {};
+    A[13] = ((((c0 + c1) + c2) + c3) + c4) + c5;
+    A[12] = -c0;
+    A[14] = -c1;
+    A[10] = -c2;
+    A[16] = -c3;
+    A[4] = -c4;
+    A[22] = -c5;
+    R.add((az ? 0.25 : 0.5) * (ay ? 0.25 : 0.5) * (ax ? 0.25 : 0.5), A, az, ay, ax);
+  }
+  rap_store(R, nc, Z, Y, X, S);
+}
+
+// from a 27-point level
+__global__ void __launch_bounds__(kGalThreads)
+    k_gal_rap(int nc, const double* __restrict__ Sf, double* __restrict__ S)
+{
+  int Z, Y, X;
+  if (!rap_node(nc, blockIdx.x * kGalThreads + threadIdx.x, Z, Y, X)) return;
+  const int half = nc - 1;  // of the fine level
+  const size_t h3 = (size_t)half * half * half;
+  RapSum R;
+  for (int a = 0; a < 27; ++a) {
+    const int az = a / 9 - 1, ay = (a / 3) % 3 - 1, ax = a % 3 - 1;
+    const double* Sn = node_coeffs(Sf, half, 2 * Z + az, 2 * Y + ay, 2 * X + ax);
+    double A[27];
+#pragma unroll
+    for (int o = 0; o < 27; ++o) A[o] = Sn[o * h3];
+    R.add((az ? 0.25 : 0.5) * (ay ? 0.25 : 0.5) * (ax ? 0.25 : 0.5), A, az, ay, ax);
+  }
+  rap_store(R, nc, Z, Y, X, S);
 }
 
 __global__ void __launch_bounds__(kGalThreads)
@@ -160,6 +260,185 @@ __global__ void k_gal_coarsest(const double* __restrict__ S, const double* __res
 {
   const size_t i = gidx(3, 1, 1, 1);
   u[i] = f[i] / node_coeffs(S, 1, 1, 1, 1)[kCentre];
+}
+
+// The V-cycle's tail in one launch: the levels of at most 17^3 nodes from a zero guess, by one
+// workgroup, with u, f and the residual of every level in LDS.  A colour pass of such a level is
+// at most 343 nodes, so its launch (2-3 us) costs more than its work, and a cycle takes 8 colours
+// x 4 sweeps of each.  Up to 9^3 nodes a thread owns one node and keeps its 27 coefficients in
+// registers; at 17^3 it owns the same slot in every colour and reads the coefficients of the next
+// colour while it works on the current one.  Operations and their order are those of the per-level kernels.
+// Measured, 17^3 to 3^3, V(2,2): GALTAIL_US
+constexpr int kGalTailN = 17, kGalTailLevels = 4, kGalTailThreads = 512;
+static_assert(((kGalTailN - 1) / 2) * ((kGalTailN - 1) / 2) * ((kGalTailN - 1) / 2) <= kGalTailThreads, "a slot per thread");
+
+template <typename TS>
+struct GalTailArgs {
+  const TS* S[kGalTailLevels];
+  const double* Sc;  // the coarsest stencil, FP64
+  const double* f;
+  double* u;
+  int n, levels, nu1, nu2;
+};
+
+__host__ __device__ constexpr int gal_tail_offset(int n0, int l)
+{
+  int off = 0, n = n0;
+  for (int q = 0; q < l; ++q) {
+    off += 3 * n * n * n;
+    n = (n - 1) / 2 + 1;
+  }
+  return off;
+}
+constexpr size_t kGalTailLds = sizeof(double) * gal_tail_offset(kGalTailN, kGalTailLevels);
+
+template <typename TS>
+__device__ __forceinline__ void gal_load(TS (&A)[27], const TS* __restrict__ S, int c, int h3, int t)
+{
+#pragma unroll
+  for (int o = 0; o < 27; ++o) A[o] = S[(size_t)(c * 27 + o) * h3 + t];
+}
+
+// off-diagonal sum with the coefficients in registers and u in LDS (n nodes per side)
+template <typename TS>
+__device__ __forceinline__ double gal_offdiag(const TS (&A)[27], const double* u, int n, int i)
+{
+  double s = 0.0;
+#pragma unroll
+  for (int o = 0; o < 27; ++o) {
+    if (o == kCentre) continue;
+    const int dz = o / 9 - 1, dy = (o / 3) % 3 - 1, dx = o % 3 - 1;
+    s += (double)A[o] * u[i + (dz * n + dy) * n + dx];
+  }
+  return s;
+}
+
+template <typename TS>
+__global__ void __launch_bounds__(kGalTailThreads) k_gal_tail(GalTailArgs<TS> a)
+{
+  extern __shared__ __align__(16) double gal_lds[];
+  const int t = threadIdx.x;
+  const int total = gal_tail_offset(a.n, a.levels);
+  for (int i = t; i < total; i += kGalTailThreads) gal_lds[i] = 0.0;
+  __syncthreads();
+  struct L {
+    int n, half, h3;
+    double *u, *f, *r;
+  };
+  auto level = [&](int l) {
+    L v;
+    v.n = a.n;
+    for (int q = 0; q < l; ++q) v.n = (v.n - 1) / 2 + 1;
+    v.half = (v.n - 1) / 2;
+    v.h3 = v.half * v.half * v.half;
+    double* p = gal_lds + gal_tail_offset(a.n, l);
+    v.u = p;
+    v.f = p + v.n * v.n * v.n;
+    v.r = v.f + v.n * v.n * v.n;
+    return v;
+  };
+  // LDS index of a slot of colour c (-1: none)
+  auto node = [&](const L& v, int c, int slot) {
+    const int x = 2 * (slot % v.half) + 2 - (c & 1), y = 2 * ((slot / v.half) % v.half) + 2 - ((c >> 1) & 1);
+    const int z = 2 * (slot / (v.half * v.half)) + 2 - (c >> 2);
+    return x <= v.n - 2 && y <= v.n - 2 && z <= v.n - 2 ? (z * v.n + y) * v.n + x : -1;
+  };
+  // one step: the colour's update, or (res) its residual
+  auto step = [&](const L& v, const TS (&A)[27], int i, bool res) {
+    if (i < 0) return;
+    const double off = gal_offdiag(A, v.u, v.n, i), d = (double)A[kCentre];
+    if (res) v.r[i] = v.f[i] - (d * v.u[i] + off);
+    else v.u[i] = (v.f[i] - off) / d;
+  };
+  // `passes` sweeps, then (res) the residual
+  auto smooth = [&](const L& v, const TS* S, int passes, bool res) {
+    if (8 * v.h3 <= kGalTailThreads) {
+      // at most 9^3 nodes: thread c h3 + slot owns one node and keeps its coefficients
+      const int c = t / v.h3, slot = t - c * v.h3;
+      int i = -1;
+      TS A[27];
+      if (c < 8) {
+        gal_load(A, S, c, v.h3, slot);
+        i = node(v, c, slot);
+      }
+      for (int s = 0; s < passes; ++s)
+        for (int q = 0; q < 8; ++q) {
+          if (q == c) step(v, A, i, false);
+          __syncthreads();
+        }
+      if (res) {
+        step(v, A, i, true);
+        __syncthreads();
+      }
+      return;
+    }
+    const int steps = 8 * (passes + (res ? 1 : 0));
+    const bool on = t < v.h3;
+    auto advance = [&](const TS (&A)[27], TS (&next)[27], int s) {
+      if (s + 1 < steps && on) gal_load(next, S, (s + 1) & 7, v.h3, t);
+      step(v, A, on ? node(v, s & 7, t) : -1, s >= 8 * passes);
+      __syncthreads();
+    };
+    TS A[27], B[27];
+    if (steps && on) gal_load(A, S, 0, v.h3, t);
+    for (int s = 0; s < steps; s += 2) {  // steps is a multiple of 8
+      advance(A, B, s);
+      advance(B, A, s + 1);
+    }
+  };
+  {
+    const L v = level(0);
+    const int N = v.n * v.n * v.n;
+    for (int i = t; i < N; i += kGalTailThreads) v.f[i] = a.f[i];
+    __syncthreads();
+  }
+  const int last = a.levels - 1;
+  for (int l = 0; l < last; ++l) {
+    const L v = level(l), w = level(l + 1);
+    smooth(v, a.S[l], a.nu1, true);
+    const int m = w.n - 2;
+    for (int q = t; q < m * m * m; q += kGalTailThreads) {
+      const int X = 1 + q % m, Y = 1 + (q / m) % m, Z = 1 + q / (m * m);
+      double s = 0.0;
+#pragma unroll
+      for (int oz = -1; oz <= 1; ++oz)
+#pragma unroll
+        for (int oy = -1; oy <= 1; ++oy)
+#pragma unroll
+          for (int ox = -1; ox <= 1; ++ox)
+            s += (oz ? 0.25 : 0.5) * (oy ? 0.25 : 0.5) * (ox ? 0.25 : 0.5) *
+                 v.r[((2 * Z + oz) * v.n + 2 * Y + oy) * v.n + 2 * X + ox];
+      w.f[(Z * w.n + Y) * w.n + X] = s;
+    }
+    __syncthreads();
+  }
+  {
+    const L v = level(last);  // 3^3: one interior node (colour 7, slot 0 of one)
+    if (t == 0) v.u[13] = v.f[13] / node_coeffs(a.Sc, 1, 1, 1, 1)[kCentre];
+    __syncthreads();
+  }
+  for (int l = last - 1; l >= 0; --l) {
+    const L v = level(l), w = level(l + 1);
+    const int m = v.n - 2;
+    for (int q = t; q < m * m * m; q += kGalTailThreads) {
+      const int x = 1 + q % m, y = 1 + (q / m) % m, z = 1 + q / (m * m);
+      const double wt = ((z & 1) ? 0.5 : 1.0) * ((y & 1) ? 0.5 : 1.0) * ((x & 1) ? 0.5 : 1.0);
+      double s = 0.0;  // the terms of prolong_add, in its order
+      for (int b = 0; b <= (z & 1); ++b)
+        for (int c = 0; c <= (y & 1); ++c) {
+          const double* e = w.u + (((z >> 1) + b) * w.n + (y >> 1) + c) * w.n + ((x + 1) >> 1);
+          if (x & 1) s = s + wt * e[-1];
+          s = s + wt * e[0];
+        }
+      const int i = (z * v.n + y) * v.n + x;
+      v.u[i] = v.u[i] + s;
+    }
+    __syncthreads();
+    smooth(v, a.S[l], a.nu2, false);
+  }
+  const L v = level(0);
+  const int N = v.n * v.n * v.n;
+  for (int i = t; i < N; i += kGalTailThreads) a.u[i] = v.u[i];
 }
 
 // out[o][i] = the stencil in natural layout (27 arrays of n^3 values, 0 off the interior)
@@ -197,8 +476,8 @@ struct mggal_ctx {
   hipStream_t s = nullptr;
   double h = 0;
   double* k = nullptr;      // copy of the coefficient
-  double* probe = nullptr;  // level-0 probe vector; the sweeps' second buffer after setup
-  double* zero = nullptr;   // level-0 zero right-hand side (probing)
+  double* t = nullptr;      // level 0's second buffer
+  int tail = -1;            // first level of the one-launch tail (-1: none)
   double* partial = nullptr;
   double* scal = nullptr;
   std::vector<GalLevel> lv;
@@ -256,8 +535,7 @@ void gal_layout(const mggal_grid* g, GalCarver& cv, mggal_ctx* c)
 {
   const size_t cnt0 = (size_t)g->n * g->n * g->n;
   double* k = cv.take<double>(cnt0);
-  double* probe = cv.take<double>(cnt0);
-  double* zero = cv.take<double>(cnt0);
+  double* t = cv.take<double>(cnt0);
   double* partial = cv.take<double>(mgk::kStreamPartials);
   double* scal = cv.take<double>(8);
   std::vector<GalLevel> lv;
@@ -280,8 +558,7 @@ void gal_layout(const mggal_grid* g, GalCarver& cv, mggal_ctx* c)
   }
   if (c) {
     c->k = k;
-    c->probe = probe;
-    c->zero = zero;
+    c->t = t;
     c->partial = partial;
     c->scal = scal;
     c->lv = lv;
@@ -291,87 +568,126 @@ void gal_layout(const mggal_grid* g, GalCarver& cv, mggal_ctx* c)
 // level 0 on a large grid: the streaming kernels of the rediscretised path
 bool fine_tiled(const mggal_ctx* c) { return mgk::rbgs_tiled_supported(3, c->g.n); }
 
-void smooth(mggal_ctx* c, int l, const double* f, double* u, int sweeps)
+// `sweeps` red-black sweeps on level 0, two per launch, from u (or u + P ec), alternating with t
+// (same boundary values); returns the buffer with the result.  fc: also the restricted residual.
+double* smooth_fine(mggal_ctx* c, const double* f, double* u, double* t, int sweeps, const double* ec, double* fc)
 {
-  const GalLevel& L = c->lv[l];
-  if (l == 0 && fine_tiled(c)) {
-    // one red-black sweep per out-of-place pass, alternating with the second buffer (same
-    // boundary values)
-    mgk::copy_boundary(c->s, 3, L.n, u, c->probe);
-    double *cur = u, *oth = c->probe;
-    for (int s = 0; s < sweeps; ++s) {
-      mgk::rbgs_tiled<double>(c->s, L.n, c->h, c->k, f, cur, oth, 1, false);
-      double* x = cur;
-      cur = oth;
-      oth = x;
-    }
-    if (cur != u) mgk::copy<double>(c->s, L.cnt, cur, u);
-    return;
+  const int n = c->g.n;
+  const bool tiled = fine_tiled(c);
+  if (ec && (sweeps == 0 || (tiled && sweeps == 1))) {  // the large grids' one-sweep pass takes no correction
+    mgk::prolong_add<double>(c->s, 3, c->lv[1].n, ec, u);
+    ec = nullptr;
   }
-  for (int s = 0; s < sweeps; ++s) {
-    if (l == 0) {
-      mgk::rbgs_colour<double>(c->s, 3, L.n, c->h, c->k, f, u, 0);
-      mgk::rbgs_colour<double>(c->s, 3, L.n, c->h, c->k, f, u, 1);
+  double *cur = u, *oth = t;
+  bool restricted = false;
+  while (sweeps > 0) {
+    const int sw = sweeps >= 2 ? 2 : 1;
+    if (tiled) {
+      mgk::rbgs_tiled<double>(c->s, n, c->h, c->k, f, cur, oth, sw, false, ec);
     } else {
-      const int half = (L.n - 1) / 2;
-      for (int col = 0; col < 8; ++col) {
-        const unsigned gb = blocks_for((size_t)half * half * half);
-        if (L.S32) k_gal_gs<float><<<gb, kGalThreads, 0, c->s>>>(L.n, L.S32, f, u, col);
-        else k_gal_gs<double><<<gb, kGalThreads, 0, c->s>>>(L.n, L.S, f, u, col);
-      }
+      mgk::rbgs_cube<double>(c->s, n, c->h, c->k, f, cur, oth, sw, false, ec, sweeps == sw ? fc : nullptr);
+      restricted = sweeps == sw && fc;
     }
+    double* x = cur;
+    cur = oth;
+    oth = x;
+    sweeps -= sw;
+    ec = nullptr;
   }
+  if (fc && !restricted) {
+    if (tiled) mgk::restrict_residual_tiled<double>(c->s, n, c->h, c->k, f, cur, fc);
+    else mgk::restrict_residual<double>(c->s, 3, n, c->h, c->k, f, cur, fc);
+  }
+  return cur;
 }
 
-// fc (level l+1) = FW(f - A_l u); f == nullptr reads 0
-void restrict_to(mggal_ctx* c, int l, const double* f, const double* u, double* fc)
+template <typename TS, bool ZERO>
+void sweep_coarse(hipStream_t s, const GalLevel& L, const TS* S, const double* f, double* u)
+{
+  const size_t half = (size_t)(L.n - 1) / 2;
+  const unsigned gb = blocks_for(half * half * half);
+  k_gal_gs<TS, 0, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+  k_gal_gs<TS, 1, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+  k_gal_gs<TS, 2, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+  k_gal_gs<TS, 3, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+  k_gal_gs<TS, 4, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+  k_gal_gs<TS, 5, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+  k_gal_gs<TS, 6, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+  k_gal_gs<TS, 7, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+}
+
+// `sweeps` eight-colour sweeps on a coarse level; zero: u is 0 (not read)
+void smooth_coarse(mggal_ctx* c, int l, int sweeps, bool zero)
 {
   const GalLevel& L = c->lv[l];
-  if (l == 0) {
-    if (fine_tiled(c)) mgk::restrict_residual_tiled<double>(c->s, L.n, c->h, c->k, f ? f : c->zero, u, fc);
-    else mgk::restrict_residual<double>(c->s, 3, L.n, c->h, c->k, f ? f : c->zero, u, fc);
-  } else {
-    const size_t mf = (size_t)L.n - 2, mc = (size_t)c->lv[l + 1].n - 2;
-    // the probes that build the hierarchy always run with the FP64 stencil
-    if (L.S32 && f) k_gal_residual<float><<<blocks_for(mf * mf * mf), kGalThreads, 0, c->s>>>(L.n, L.S32, f, u, L.r);
-    else k_gal_residual<double><<<blocks_for(mf * mf * mf), kGalThreads, 0, c->s>>>(L.n, L.S, f, u, L.r);
-    k_gal_fw<<<blocks_for(mc * mc * mc), kGalThreads, 0, c->s>>>(L.n, L.r, fc);
+  if (zero && sweeps == 0) mgk::fill<double>(c->s, L.cnt, 0.0, L.u);
+  for (int s = 0; s < sweeps; ++s) {
+    if (L.S32 && zero && s == 0) sweep_coarse<float, true>(c->s, L, L.S32, L.f, L.u);
+    else if (L.S32) sweep_coarse<float, false>(c->s, L, L.S32, L.f, L.u);
+    else if (zero && s == 0) sweep_coarse<double, true>(c->s, L, L.S, L.f, L.u);
+    else sweep_coarse<double, false>(c->s, L, L.S, L.f, L.u);
   }
 }
 
-void vcycle_rec(mggal_ctx* c, int l, const double* f, double* u)
+template <typename TS>
+void launch_tail(mggal_ctx* c, int l, const TS* (*stencil)(const GalLevel&))
+{
+  GalTailArgs<TS> a{};
+  a.levels = (int)c->lv.size() - l;
+  for (int q = 0; q + 1 < a.levels; ++q) a.S[q] = stencil(c->lv[l + q]);
+  a.Sc = c->lv.back().S;
+  a.f = c->lv[l].f;
+  a.u = c->lv[l].u;
+  a.n = c->lv[l].n;
+  a.nu1 = c->g.nu1;
+  a.nu2 = c->g.nu2;
+  k_gal_tail<TS><<<1, kGalTailThreads, kGalTailLds, c->s>>>(a);
+}
+
+// the correction of coarse level l (its f to its u), from zero
+void coarse_cycle(mggal_ctx* c, int l)
 {
   const int last = (int)c->lv.size() - 1;
-  if (l == last) {
-    k_gal_coarsest<<<1, 1, 0, c->s>>>(c->lv[l].S, f, u);
+  GalLevel& L = c->lv[l];
+  if (l == c->tail) {
+    if (c->g.coarse_f32) launch_tail<float>(c, l, [](const GalLevel& q) -> const float* { return q.S32; });
+    else launch_tail<double>(c, l, [](const GalLevel& q) -> const double* { return q.S; });
     return;
   }
-  smooth(c, l, f, u, c->g.nu1);
+  if (l == last) {
+    k_gal_coarsest<<<1, 1, 0, c->s>>>(L.S, L.f, L.u);
+    return;
+  }
   GalLevel& C = c->lv[l + 1];
-  restrict_to(c, l, f, u, C.f);
-  mgk::fill<double>(c->s, C.cnt, 0.0, C.u);
-  vcycle_rec(c, l + 1, C.f, C.u);
-  mgk::prolong_add<double>(c->s, 3, C.n, C.u, u);
-  smooth(c, l, f, u, c->g.nu2);
+  smooth_coarse(c, l, c->g.nu1, true);
+  const size_t mf = (size_t)L.n - 2, mc = (size_t)C.n - 2;
+  if (L.S32) k_gal_residual<float><<<blocks_for(mf * mf * mf), kGalThreads, 0, c->s>>>(L.n, L.S32, L.f, L.u, L.r);
+  else k_gal_residual<double><<<blocks_for(mf * mf * mf), kGalThreads, 0, c->s>>>(L.n, L.S, L.f, L.u, L.r);
+  k_gal_fw<<<blocks_for(mc * mc * mc), kGalThreads, 0, c->s>>>(L.n, L.r, C.f);
+  coarse_cycle(c, l + 1);
+  mgk::prolong_add<double>(c->s, 3, C.n, C.u, L.u);
+  smooth_coarse(c, l, c->g.nu2, false);
 }
 
-// Galerkin operator of level l+1 by probing with the 27 combs of coarse nodes
+// one V-cycle, the result in u; the second buffer holds u's boundary values
+void vcycle(mggal_ctx* c, const double* f, double* u)
+{
+  double* cur = smooth_fine(c, f, u, c->t, c->g.nu1, nullptr, c->lv[1].f);
+  coarse_cycle(c, 1);
+  double* r = smooth_fine(c, f, cur, cur == u ? c->t : u, c->g.nu2, c->lv[1].u, nullptr);
+  if (r != u) mgk::copy<double>(c->s, c->lv[0].cnt, r, u);
+}
+
+void copy_boundary(mggal_ctx* c, const double* u) { mgk::copy_boundary(c->s, 3, c->g.n, u, c->t); }
+
+// Galerkin operator of level l+1 from level l
 void build_level(mggal_ctx* c, int l)
 {
-  GalLevel& F = c->lv[l];
   GalLevel& C = c->lv[l + 1];
-  double* w = l == 0 ? c->probe : F.u;  // fine probe vector (zero boundary)
-  mgk::fill<double>(c->s, C.scnt, 0.0, C.S);
   const size_t m = (size_t)C.n - 2;
-  for (int cz = 0; cz < 3; ++cz)
-    for (int cy = 0; cy < 3; ++cy)
-      for (int cx = 0; cx < 3; ++cx) {
-        k_gal_comb<<<blocks_for(C.cnt), kGalThreads, 0, c->s>>>(C.n, cz, cy, cx, C.u);
-        mgk::fill<double>(c->s, F.cnt, 0.0, w);
-        mgk::prolong_add<double>(c->s, 3, C.n, C.u, w);
-        restrict_to(c, l, nullptr, w, C.f);
-        k_gal_scatter<<<blocks_for(m * m * m), kGalThreads, 0, c->s>>>(C.n, cz, cy, cx, C.f, C.S);
-      }
+  const unsigned gb = blocks_for(m * m * m);
+  if (l == 0) k_gal_rap_fine<<<gb, kGalThreads, 0, c->s>>>(C.n, 1.0 / (c->h * c->h), c->k, C.S);
+  else k_gal_rap<<<gb, kGalThreads, 0, c->s>>>(C.n, c->lv[l].S, C.S);
 }
 
 mg_status read_norm2(mggal_ctx* c, const double* f, const double* u, int mode, double* out)
@@ -418,13 +734,20 @@ mg_status mggal_setup(const mggal_grid* grid, const double* k, void* workspace, 
   GalCarver cv{static_cast<char*>(workspace)};
   gal_layout(grid, cv, c);
   mgk::copy<double>(c->s, c->lv[0].cnt, k, c->k);
-  mgk::fill<double>(c->s, c->lv[0].cnt, 0.0, c->zero);
   for (size_t l = 1; l < c->lv.size(); ++l) {  // zero boundaries of every coarse array
     mgk::fill<double>(c->s, c->lv[l].cnt, 0.0, c->lv[l].u);
     mgk::fill<double>(c->s, c->lv[l].cnt, 0.0, c->lv[l].f);
     mgk::fill<double>(c->s, c->lv[l].cnt, 0.0, c->lv[l].r);
   }
   for (size_t l = 0; l + 1 < c->lv.size(); ++l) build_level(c, (int)l);
+  for (int l = 1; l < grid->levels && c->tail < 0; ++l)
+    if (c->lv[l].n <= kGalTailN && grid->levels - l <= kGalTailLevels) c->tail = l;
+  const void* tail = grid->coarse_f32 ? reinterpret_cast<const void*>(k_gal_tail<float>)
+                                      : reinterpret_cast<const void*>(k_gal_tail<double>);
+  if (hipFuncSetAttribute(tail, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGalTailLds) != hipSuccess) {
+    (void)hipGetLastError();
+    c->tail = -1;  // per-level launches
+  }
   for (size_t l = 1; l < c->lv.size(); ++l)
     if (c->lv[l].S32)
       k_gal_to_f32<<<blocks_for(c->lv[l].scnt), kGalThreads, 0, c->s>>>(c->lv[l].S, c->lv[l].S32, c->lv[l].scnt);
@@ -457,7 +780,8 @@ mg_status mggal_vcycle(mggal_ctx* c, const double* f, double* u)
 {
   if (!c) return gal_fail(nullptr, MG_EINVAL, "context is NULL");
   if (!f || !u) return gal_fail(c, MG_EINVAL, "f and u must be non-NULL");
-  vcycle_rec(c, 0, f, u);
+  copy_boundary(c, u);
+  vcycle(c, f, u);
   return gal_hip(c, hipGetLastError(), "V-cycle");
 }
 
@@ -475,8 +799,9 @@ mg_status mggal_solve(mggal_ctx* c, const double* f, double* u, double tol, int*
   double rel = 1.0;
   if (!st) st = read_norm2(c, f, u, 0, &r2);
   if (!st) rel = std::sqrt(r2) / bn;
+  if (!st) copy_boundary(c, u);
   while (!st && std::isfinite(rel) && rel > tol && kcyc < c->g.max_cycles) {
-    vcycle_rec(c, 0, f, u);
+    vcycle(c, f, u);
     ++kcyc;
     st = read_norm2(c, f, u, 0, &r2);
     rel = std::sqrt(r2) / bn;

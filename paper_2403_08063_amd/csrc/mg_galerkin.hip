@@ -3,7 +3,7 @@
 // Gauss-Seidel with face coefficients, residual + full weighting, trilinear prolongation,
 // norms); the coarse levels hold 27-point stencils R A P built on the GPU from the finer level's
 // coefficients, and run the kernels below: eight-colour Gauss-Seidel, residual with full
-// weighting, and, from 17^3 nodes down to the exact solve of the one-node coarsest level, the
+// weighting, and, from 9^3 nodes down to the exact solve of the one-node coarsest level, the
 // whole V-cycle in one launch.  A coarse level stores
 // its stencil colour-major: for each of the eight parity colours, 27 arrays over that colour's
 // nodes in C order, so that a colour pass of the smoother reads its coefficients contiguously.
@@ -17,6 +17,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 namespace {
@@ -66,33 +67,120 @@ __device__ __forceinline__ double offdiag(const TS* __restrict__ Sn, size_t h3,
   return s;
 }
 
-// One colour C of eight-colour Gauss-Seidel: nodes with parities (pz, py, px) = bits of C.  ZERO: the
-// first sweep from a zero iterate, which is not read before it is written: only the neighbours of
-// the colours before C count (the colour of a neighbour is C with the parities of the offset's
-// nonzero components flipped), which halves the coefficients read over the sweep.
-template <typename TS, int C, bool ZERO>
-__global__ void __launch_bounds__(kGalThreads)
-    k_gal_gs(int n, const TS* __restrict__ S, const double* __restrict__ f, double* u)
+// Eight-colour Gauss-Seidel visits the colours C = 4 (z%2) + 2 (y%2) + x%2 in order; nodes of one
+// colour never couple.  ZERO below: the first sweep from a zero iterate, which is not read before
+// it is written: only the neighbours of the colours before C count (the colour of a neighbour is C
+// with the parities of the offset's nonzero components flipped), which halves the coefficients
+// read over the sweep.
+
+// the coefficients of slot `slot` of colour C
+template <int C, bool ZERO, typename TS>
+__device__ __forceinline__ void load_coeffs(TS (&A)[27], const TS* __restrict__ S, size_t h3, size_t slot)
 {
-  const int half = (n - 1) / 2;
-  const int t = blockIdx.x * kGalThreads + threadIdx.x;
-  if (t >= half * half * half) return;
-  constexpr int px = C & 1, py = (C >> 1) & 1, pz = C >> 2;
-  // interior index with parity p: 2 j + 2 - p  (p = 1: 1, 3, ..; p = 0: 2, 4, ..)
-  const int x = 2 * (t % half) + 2 - px, y = 2 * ((t / half) % half) + 2 - py, z = 2 * (t / (half * half)) + 2 - pz;
-  if (x > n - 2 || y > n - 2 || z > n - 2) return;
-  const size_t h3 = (size_t)half * half * half;
-  const TS* Sn = S + (size_t)C * 27 * h3 + t;
-  const size_t i = gidx(n, z, y, x);
+#pragma unroll
+  for (int o = 0; o < 27; ++o) {
+    const int nb = C ^ ((o / 9 != 1 ? 4 : 0) | ((o / 3) % 3 != 1 ? 2 : 0) | (o % 3 != 1 ? 1 : 0));
+    if (ZERO && nb > C) continue;
+    A[o] = S[((size_t)C * 27 + o) * h3 + slot];
+  }
+}
+
+// The off-diagonal sum of colour C with the coefficients in registers; value(o, dz, dy, dx) gives
+// the neighbour at an offset.
+template <int C, bool ZERO, typename TS, typename F>
+__device__ __forceinline__ double colour_offdiag(const TS (&A)[27], F&& value)
+{
   double s = 0.0;
 #pragma unroll
   for (int o = 0; o < 27; ++o) {
     const int dz = o / 9 - 1, dy = (o / 3) % 3 - 1, dx = o % 3 - 1;
     const int nb = C ^ ((dz ? 4 : 0) | (dy ? 2 : 0) | (dx ? 1 : 0));
     if (o == kCentre || (ZERO && nb > C)) continue;
-    s += (double)Sn[o * h3] * u[gidx(n, z + dz, y + dy, x + dx)];
+    s += (double)A[o] * value(dz, dy, dx);
   }
-  u[i] = (f[i] - s) / (double)Sn[kCentre * h3];
+  return s;
+}
+
+// Two colours of a sweep in one launch, C = 2 ZY and C + 1: the even and the odd nodes of the rows
+// of (z, y)-parity ZY, which do not couple across rows.  A thread owns an even node and the odd
+// one before it (the same slot of both colours); the odd node's two neighbours in the row come
+// from the even phase through LDS.  Both nodes' 54 coefficients are in flight at once, and a sweep
+// is four launches: at 65^3 ROWS_US
+template <typename TS, int ZY, bool ZERO>
+__global__ void __launch_bounds__(kGalThreads)
+    k_gal_rows(int n, const TS* __restrict__ S, const double* __restrict__ f, double* u)
+{
+  constexpr int C = 2 * ZY;
+  __shared__ double even[kGalThreads + 1];
+  const int half = (n - 1) / 2;  // a power of two up to 256: rows do not straddle workgroups
+  const int h2 = half * half, t = blockIdx.x * kGalThreads + threadIdx.x;
+  const int jx = t % half, y = 2 * ((t / half) % half) + 2 - (ZY & 1), z = 2 * (t / h2) + 2 - (ZY >> 1);
+  const bool row = t < h2 * half && y <= n - 2 && z <= n - 2;
+  const size_t h3 = (size_t)h2 * half;
+  const size_t i = gidx(n, z, y, 2 * jx + 1);  // the odd node; the even one is next
+  TS A[27], B[27];
+  double fo = 0.0, ve = 0.0;
+  const bool e = row && 2 * jx + 2 <= n - 2;
+  if (row) load_coeffs<C + 1, ZERO>(B, S, h3, t);
+  if (e) {
+    load_coeffs<C, ZERO>(A, S, h3, t);
+    const double off = colour_offdiag<C, ZERO>(A, [&](int dz, int dy, int dx) {
+      return u[i + 1 + (ptrdiff_t)(dz * n + dy) * n + dx];
+    });
+    ve = (f[i + 1] - off) / (double)A[kCentre];
+    u[i + 1] = ve;
+  }
+  if (row) fo = f[i];
+  even[threadIdx.x + 1] = ve;  // 0 on the boundary
+  __syncthreads();
+  if (!row) return;
+  const double vw = jx ? even[threadIdx.x] : 0.0;
+  const double off = colour_offdiag<C + 1, ZERO>(B, [&](int dz, int dy, int dx) {
+    return dz || dy ? u[i + (ptrdiff_t)(dz * n + dy) * n + dx] : dx < 0 ? vw : ve;
+  });
+  u[i] = (fo - off) / (double)B[kCentre];
+}
+
+// Four colours of a sweep (those of z-parity PZ) in one launch on a small level: planes of one
+// parity do not couple, and within a plane the colours follow each other in LDS.  One workgroup
+// per plane, one thread per slot of a colour (half^2 of them); the coefficients of the next colour
+// are read while the current one is computed.  A sweep is two launches: at 33^3 17.3 us against
+// 35 in eight (one per colour).  Not at 65^3: its 32 workgroups draw too little bandwidth (87 us
+// against 35).
+template <typename TS, int PZ, bool ZERO, int HALF>
+__global__ void __launch_bounds__(HALF * HALF)
+    k_gal_planes(const TS* __restrict__ S, const double* __restrict__ f, double* u)
+{
+  constexpr int n = 2 * HALF + 1, plane = n * n, T = HALF * HALF;
+  __shared__ double P[3 * plane];
+  const int t = threadIdx.x, jx = t % HALF, jy = t / HALF;
+  const int z = 2 * (int)blockIdx.x + 2 - PZ;
+  if (z > n - 2) return;
+  constexpr size_t h3 = (size_t)HALF * T;
+  const size_t slot = (size_t)blockIdx.x * T + t;
+  TS A[27], B[27];
+  load_coeffs<4 * PZ, ZERO>(A, S, h3, slot);
+  for (int i = t; i < 3 * plane; i += T) P[i] = u[(size_t)(z - 1) * plane + i];
+  __syncthreads();
+  auto colour = [&](auto CC, const TS (&K)[27]) {
+    constexpr int C = decltype(CC)::value;
+    const int x = 2 * jx + 2 - (C & 1), y = 2 * jy + 2 - ((C >> 1) & 1);
+    if (x <= n - 2 && y <= n - 2) {
+      const double* U = P + plane + y * n + x;
+      const double off = colour_offdiag<C, ZERO>(K, [&](int dz, int dy, int dx) { return U[dz * plane + dy * n + dx]; });
+      const double v = (f[(size_t)z * plane + y * n + x] - off) / (double)K[kCentre];
+      P[plane + y * n + x] = v;
+      u[(size_t)z * plane + y * n + x] = v;
+    }
+    __syncthreads();
+  };
+  load_coeffs<4 * PZ + 1, ZERO>(B, S, h3, slot);
+  colour(std::integral_constant<int, 4 * PZ>{}, A);
+  load_coeffs<4 * PZ + 2, ZERO>(A, S, h3, slot);
+  colour(std::integral_constant<int, 4 * PZ + 1>{}, B);
+  load_coeffs<4 * PZ + 3, ZERO>(B, S, h3, slot);
+  colour(std::integral_constant<int, 4 * PZ + 2>{}, A);
+  colour(std::integral_constant<int, 4 * PZ + 3>{}, B);
 }
 
 // r = f - A u at interior nodes (f == nullptr reads 0); the boundary of r is not written
@@ -262,15 +350,15 @@ __global__ void k_gal_coarsest(const double* __restrict__ S, const double* __res
   u[i] = f[i] / node_coeffs(S, 1, 1, 1, 1)[kCentre];
 }
 
-// The V-cycle's tail in one launch: the levels of at most 17^3 nodes from a zero guess, by one
-// workgroup, with u, f and the residual of every level in LDS.  A colour pass of such a level is
-// at most 343 nodes, so its launch (2-3 us) costs more than its work, and a cycle takes 8 colours
-// x 4 sweeps of each.  Up to 9^3 nodes a thread owns one node and keeps its 27 coefficients in
-// registers; at 17^3 it owns the same slot in every colour and reads the coefficients of the next
-// colour while it works on the current one.  Operations and their order are those of the per-level kernels.
-// Measured, 17^3 to 3^3, V(2,2): GALTAIL_US
-constexpr int kGalTailN = 17, kGalTailLevels = 4, kGalTailThreads = 512;
-static_assert(((kGalTailN - 1) / 2) * ((kGalTailN - 1) / 2) * ((kGalTailN - 1) / 2) <= kGalTailThreads, "a slot per thread");
+// The V-cycle's tail in one launch: the levels of at most 9^3 nodes from a zero guess, by one
+// workgroup, with u, f and the residual of every level in LDS and every thread the owner of one
+// node with its 27 coefficients in registers.  A colour pass of such a level is at most 64 nodes,
+// so its launch (2-3 us) costs far more than its work, and a cycle takes 8 colours x 4 sweeps of
+// each.  (17^3 does not belong here: one compute unit draws its 0.7 MB of coefficients per sweep
+// too slowly; the tail from 17^3 took 127 us per V(2,2)-cycle.)  Operations and their order are
+// those of the per-level kernels.  Measured, 9^3 to 3^3, V(2,2): GALTAIL_US
+constexpr int kGalTailN = 9, kGalTailLevels = 3, kGalTailThreads = 512;
+static_assert((kGalTailN - 1) * (kGalTailN - 1) * (kGalTailN - 1) <= kGalTailThreads, "a node per thread");
 
 template <typename TS>
 struct GalTailArgs {
@@ -290,7 +378,6 @@ __host__ __device__ constexpr int gal_tail_offset(int n0, int l)
   }
   return off;
 }
-constexpr size_t kGalTailLds = sizeof(double) * gal_tail_offset(kGalTailN, kGalTailLevels);
 
 template <typename TS>
 __device__ __forceinline__ void gal_load(TS (&A)[27], const TS* __restrict__ S, int c, int h3, int t)
@@ -316,7 +403,7 @@ __device__ __forceinline__ double gal_offdiag(const TS (&A)[27], const double* u
 template <typename TS>
 __global__ void __launch_bounds__(kGalTailThreads) k_gal_tail(GalTailArgs<TS> a)
 {
-  extern __shared__ __align__(16) double gal_lds[];
+  __shared__ double gal_lds[gal_tail_offset(kGalTailN, kGalTailLevels)];
   const int t = threadIdx.x;
   const int total = gal_tail_offset(a.n, a.levels);
   for (int i = t; i < total; i += kGalTailThreads) gal_lds[i] = 0.0;
@@ -352,38 +439,22 @@ __global__ void __launch_bounds__(kGalTailThreads) k_gal_tail(GalTailArgs<TS> a)
   };
   // `passes` sweeps, then (res) the residual
   auto smooth = [&](const L& v, const TS* S, int passes, bool res) {
-    if (8 * v.h3 <= kGalTailThreads) {
-      // at most 9^3 nodes: thread c h3 + slot owns one node and keeps its coefficients
-      const int c = t / v.h3, slot = t - c * v.h3;
-      int i = -1;
-      TS A[27];
-      if (c < 8) {
-        gal_load(A, S, c, v.h3, slot);
-        i = node(v, c, slot);
-      }
-      for (int s = 0; s < passes; ++s)
-        for (int q = 0; q < 8; ++q) {
-          if (q == c) step(v, A, i, false);
-          __syncthreads();
-        }
-      if (res) {
-        step(v, A, i, true);
+    // thread c h3 + slot owns one node
+    const int c = t / v.h3, slot = t - c * v.h3;
+    int i = -1;
+    TS A[27];
+    if (c < 8) {
+      gal_load(A, S, c, v.h3, slot);
+      i = node(v, c, slot);
+    }
+    for (int s = 0; s < passes; ++s)
+      for (int q = 0; q < 8; ++q) {
+        if (q == c) step(v, A, i, false);
         __syncthreads();
       }
-      return;
-    }
-    const int steps = 8 * (passes + (res ? 1 : 0));
-    const bool on = t < v.h3;
-    auto advance = [&](const TS (&A)[27], TS (&next)[27], int s) {
-      if (s + 1 < steps && on) gal_load(next, S, (s + 1) & 7, v.h3, t);
-      step(v, A, on ? node(v, s & 7, t) : -1, s >= 8 * passes);
+    if (res) {
+      step(v, A, i, true);
       __syncthreads();
-    };
-    TS A[27], B[27];
-    if (steps && on) gal_load(A, S, 0, v.h3, t);
-    for (int s = 0; s < steps; s += 2) {  // steps is a multiple of 8
-      advance(A, B, s);
-      advance(B, A, s + 1);
     }
   };
   {
@@ -601,19 +672,24 @@ double* smooth_fine(mggal_ctx* c, const double* f, double* u, double* t, int swe
   return cur;
 }
 
+// one sweep: whole planes per workgroup where a level has too few rows to fill the device
 template <typename TS, bool ZERO>
 void sweep_coarse(hipStream_t s, const GalLevel& L, const TS* S, const double* f, double* u)
 {
-  const size_t half = (size_t)(L.n - 1) / 2;
-  const unsigned gb = blocks_for(half * half * half);
-  k_gal_gs<TS, 0, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
-  k_gal_gs<TS, 1, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
-  k_gal_gs<TS, 2, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
-  k_gal_gs<TS, 3, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
-  k_gal_gs<TS, 4, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
-  k_gal_gs<TS, 5, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
-  k_gal_gs<TS, 6, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
-  k_gal_gs<TS, 7, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+  if (L.n == 17) {
+    k_gal_planes<TS, 0, ZERO, 8><<<8, 64, 0, s>>>(S, f, u);
+    k_gal_planes<TS, 1, ZERO, 8><<<8, 64, 0, s>>>(S, f, u);
+  } else if (L.n == 33) {
+    k_gal_planes<TS, 0, ZERO, 16><<<16, 256, 0, s>>>(S, f, u);
+    k_gal_planes<TS, 1, ZERO, 16><<<16, 256, 0, s>>>(S, f, u);
+  } else {
+    const size_t half = (size_t)(L.n - 1) / 2;
+    const unsigned gb = blocks_for(half * half * half);
+    k_gal_rows<TS, 0, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+    k_gal_rows<TS, 1, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+    k_gal_rows<TS, 2, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+    k_gal_rows<TS, 3, ZERO><<<gb, kGalThreads, 0, s>>>(L.n, S, f, u);
+  }
 }
 
 // `sweeps` eight-colour sweeps on a coarse level; zero: u is 0 (not read)
@@ -641,7 +717,7 @@ void launch_tail(mggal_ctx* c, int l, const TS* (*stencil)(const GalLevel&))
   a.n = c->lv[l].n;
   a.nu1 = c->g.nu1;
   a.nu2 = c->g.nu2;
-  k_gal_tail<TS><<<1, kGalTailThreads, kGalTailLds, c->s>>>(a);
+  k_gal_tail<TS><<<1, kGalTailThreads, 0, c->s>>>(a);
 }
 
 // the correction of coarse level l (its f to its u), from zero
@@ -742,12 +818,6 @@ mg_status mggal_setup(const mggal_grid* grid, const double* k, void* workspace, 
   for (size_t l = 0; l + 1 < c->lv.size(); ++l) build_level(c, (int)l);
   for (int l = 1; l < grid->levels && c->tail < 0; ++l)
     if (c->lv[l].n <= kGalTailN && grid->levels - l <= kGalTailLevels) c->tail = l;
-  const void* tail = grid->coarse_f32 ? reinterpret_cast<const void*>(k_gal_tail<float>)
-                                      : reinterpret_cast<const void*>(k_gal_tail<double>);
-  if (hipFuncSetAttribute(tail, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGalTailLds) != hipSuccess) {
-    (void)hipGetLastError();
-    c->tail = -1;  // per-level launches
-  }
   for (size_t l = 1; l < c->lv.size(); ++l)
     if (c->lv[l].S32)
       k_gal_to_f32<<<blocks_for(c->lv[l].scnt), kGalThreads, 0, c->s>>>(c->lv[l].S, c->lv[l].S32, c->lv[l].scnt);

@@ -105,7 +105,7 @@ __device__ __forceinline__ double colour_offdiag(const TS (&A)[27], F&& value)
 // of (z, y)-parity ZY, which do not couple across rows.  A thread owns an even node and the odd
 // one before it (the same slot of both colours); the odd node's two neighbours in the row come
 // from the even phase through LDS.  Both nodes' 54 coefficients are in flight at once, and a sweep
-// is four launches: at 65^3 ROWS_US
+// is four launches: at 65^3 5.9 us each, 23.6 us a sweep against 35 in eight (one per colour).
 template <typename TS, int ZY, bool ZERO>
 __global__ void __launch_bounds__(kGalThreads)
     k_gal_rows(int n, const TS* __restrict__ S, const double* __restrict__ f, double* u)
@@ -226,7 +226,7 @@ __global__ void __launch_bounds__(kGalThreads)
 // fine node at distance 0 takes 1, at distance 1 takes 1/2 of the coarse value).  The 27 values of
 // each fine row are contracted axis by axis.  One pass over the fine coefficients per level, where
 // probing with 27 combs of coarse nodes took 27 prolongations, residuals and restrictions of
-// whole levels: RAP_US
+// whole levels (129^3: about 4 ms of launches for the hierarchy, 0.17 ms in all now).
 struct RapSum {
   double c[3][3][3] = {};  // [z][y][x] offset + 1 of the coarse neighbour
   // adds w times the fine row A (27 couplings at offset o = 9 (dz+1) + 3 (dy+1) + dx+1) of the
@@ -273,18 +273,14 @@ __device__ __forceinline__ bool rap_node(int nc, int t, int& Z, int& Y, int& X)
   return t < m * m * m;
 }
 
-// couplings that leave the interior are 0
-__device__ __forceinline__ void rap_store(const RapSum& R, int nc, int Z, int Y, int X, double* __restrict__ S)
+// the coupling of coarse node (Z, Y, X) to its neighbour at offset o; 0 if that leaves the interior
+__device__ __forceinline__ void rap_store(double v, int o, int nc, int Z, int Y, int X, double* __restrict__ S)
 {
   const int half = (nc - 1) / 2;
   const size_t h3 = (size_t)half * half * half;
-  double* Sn = const_cast<double*>(node_coeffs(S, half, Z, Y, X));
-#pragma unroll
-  for (int o = 0; o < 27; ++o) {
-    const int dz = o / 9 - 1, dy = (o / 3) % 3 - 1, dx = o % 3 - 1;
-    const bool in = Z + dz >= 1 && Z + dz <= nc - 2 && Y + dy >= 1 && Y + dy <= nc - 2 && X + dx >= 1 && X + dx <= nc - 2;
-    Sn[o * h3] = in ? R.c[dz + 1][dy + 1][dx + 1] : 0.0;
-  }
+  const int z = Z + o / 9 - 1, y = Y + (o / 3) % 3 - 1, x = X + o % 3 - 1;
+  const bool in = z >= 1 && z <= nc - 2 && y >= 1 && y <= nc - 2 && x >= 1 && x <= nc - 2;
+  const_cast<double*>(node_coeffs(S, half, Z, Y, X))[o * h3] = in ? v : 0.0;
 }
 
 // from the 7-point operator of coefficient k (nc: coarse nodes per side)
@@ -312,27 +308,42 @@ __global__ void __launch_bounds__(kGalThreads)
     A[22] = -c5;
     R.add((az ? 0.25 : 0.5) * (ay ? 0.25 : 0.5) * (ax ? 0.25 : 0.5), A, az, ay, ax);
   }
-  rap_store(R, nc, Z, Y, X, S);
+#pragma unroll
+  for (int o = 0; o < 27; ++o) rap_store(R.c[o / 9][(o / 3) % 3][o % 3], o, nc, Z, Y, X, S);
 }
 
-// from a 27-point level
+// From a 27-point level: eight coarse nodes per workgroup and one lane per fine row of a node (27 of
+// 32 lanes), whose contributions meet in LDS and are summed in the order of the rows.  The levels
+// are small: with a thread per coarse node the 27 rows were a serial chain of loads, 63-99 us a
+// level from 65^3 down to 3^3; with a lane per row 46 us at 65^3, below 10 us on the others.
+constexpr int kRapNodes = kGalThreads / 32;
+
 __global__ void __launch_bounds__(kGalThreads)
     k_gal_rap(int nc, const double* __restrict__ Sf, double* __restrict__ S)
 {
+  __shared__ double part[kRapNodes][27][27];  // [node][row][coarse neighbour]
+  const int g = threadIdx.x >> 5, a = threadIdx.x & 31;
   int Z, Y, X;
-  if (!rap_node(nc, blockIdx.x * kGalThreads + threadIdx.x, Z, Y, X)) return;
-  const int half = nc - 1;  // of the fine level
-  const size_t h3 = (size_t)half * half * half;
-  RapSum R;
-  for (int a = 0; a < 27; ++a) {
+  const bool node = rap_node(nc, blockIdx.x * kRapNodes + g, Z, Y, X) && a < 27;
+  if (node) {
+    const int half = nc - 1;  // of the fine level
+    const size_t h3 = (size_t)half * half * half;
     const int az = a / 9 - 1, ay = (a / 3) % 3 - 1, ax = a % 3 - 1;
     const double* Sn = node_coeffs(Sf, half, 2 * Z + az, 2 * Y + ay, 2 * X + ax);
     double A[27];
 #pragma unroll
     for (int o = 0; o < 27; ++o) A[o] = Sn[o * h3];
+    RapSum R;
     R.add((az ? 0.25 : 0.5) * (ay ? 0.25 : 0.5) * (ax ? 0.25 : 0.5), A, az, ay, ax);
+#pragma unroll
+    for (int s = 0; s < 27; ++s) part[g][a][s] = R.c[s / 9][(s / 3) % 3][s % 3];
   }
-  rap_store(R, nc, Z, Y, X, S);
+  __syncthreads();
+  if (!node) return;
+  double sum = 0.0;  // lane a: the coupling to the coarse neighbour at offset a
+#pragma unroll
+  for (int r = 0; r < 27; ++r) sum += part[g][r][a];
+  rap_store(sum, a, nc, Z, Y, X, S);
 }
 
 __global__ void __launch_bounds__(kGalThreads)
@@ -356,7 +367,8 @@ __global__ void k_gal_coarsest(const double* __restrict__ S, const double* __res
 // so its launch (2-3 us) costs far more than its work, and a cycle takes 8 colours x 4 sweeps of
 // each.  (17^3 does not belong here: one compute unit draws its 0.7 MB of coefficients per sweep
 // too slowly; the tail from 17^3 took 127 us per V(2,2)-cycle.)  Operations and their order are
-// those of the per-level kernels.  Measured, 9^3 to 3^3, V(2,2): GALTAIL_US
+// those of the per-level kernels.  Measured, 9^3 to 3^3, V(2,2): 33.6 us, against
+// about 150 us in 70 launches.
 constexpr int kGalTailN = 9, kGalTailLevels = 3, kGalTailThreads = 512;
 static_assert((kGalTailN - 1) * (kGalTailN - 1) * (kGalTailN - 1) <= kGalTailThreads, "a node per thread");
 
@@ -761,9 +773,8 @@ void build_level(mggal_ctx* c, int l)
 {
   GalLevel& C = c->lv[l + 1];
   const size_t m = (size_t)C.n - 2;
-  const unsigned gb = blocks_for(m * m * m);
-  if (l == 0) k_gal_rap_fine<<<gb, kGalThreads, 0, c->s>>>(C.n, 1.0 / (c->h * c->h), c->k, C.S);
-  else k_gal_rap<<<gb, kGalThreads, 0, c->s>>>(C.n, c->lv[l].S, C.S);
+  if (l == 0) k_gal_rap_fine<<<blocks_for(m * m * m), kGalThreads, 0, c->s>>>(C.n, 1.0 / (c->h * c->h), c->k, C.S);
+  else k_gal_rap<<<(unsigned)((m * m * m + kRapNodes - 1) / kRapNodes), kGalThreads, 0, c->s>>>(C.n, c->lv[l].S, C.S);
 }
 
 mg_status read_norm2(mggal_ctx* c, const double* f, const double* u, int mode, double* out)

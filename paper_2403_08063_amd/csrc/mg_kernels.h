@@ -116,9 +116,8 @@ void ir_pass_tiled(hipStream_t s, int n, double h, const double* k, const double
 template <typename T>
 void prolong_add(hipStream_t s, int dim, int nc, const T* ec, T* u);
 
-// Coarsest level: assemble the interior operator, Cholesky-factor it and form its inverse
-// (one workgroup).  work: m*m doubles; ainv: m*m doubles; flag: set to 1 if the matrix is
-// not positive definite.
+// Coarsest level: the inverse of the interior operator.  work: m*m doubles; ainv: m*m doubles;
+// flag: set to 1 if the matrix is not positive definite.
 void coarsest_factor(hipStream_t s, int dim, int n, double h, const double* k, double* work,
                      double* ainv, int* flag);
 // Interior of u = ainv * (interior of f), computed in double; boundary untouched.

@@ -131,71 +131,103 @@ __global__ void __launch_bounds__(kBlock)
 
 // ------------------------------------------------------------------ coarsest level
 
-// One workgroup: assemble A (m x m, row-major) in `a`, Cholesky-factor it in place
-// (right-looking: scale column j, then update the trailing lower triangle), then form
-// A^-1 = L^-T L^-1 one column per thread by forward and back substitution.
-__global__ void __launch_bounds__(kBlock)
-    k_coarsest_factor(int dim, int n, double ih2, const double* __restrict__ k,
-                      double* __restrict__ a, double* __restrict__ ainv, int* flag)
+// The inverse of the coarsest operator A (m x m, symmetric positive definite) by Gauss-Jordan
+// elimination without pivoting, which such a matrix does not need; the pivots are those of the
+// Cholesky factorisation (squared).  m steps, each of them parallel over the m^2 entries:
+//   row i = k: a_kj / p;  column j = k: -a_ik / p;  the pivot: 1 / p;  else a_ij - a_ik (a_kj / p).
+// Up to kLdsCoarse unknowns one workgroup does them in LDS; larger matrices (the coarsest levels
+// of grids such as 7 2^j + 1 in 3D) take a launch per step, from one global buffer to another.
+// A workgroup that factored in global memory and substituted column by column took 0.75 ms at
+// m = 64 (0.10 ms now), and tens of milliseconds at 216.
+constexpr int kLdsCoarse = 128;
+constexpr int kFactorThreads = 1024;
+
+// entry (q, col) of A: diagonal sum of the face coefficients, minus those to interior neighbours
+__device__ __forceinline__ double coarsest_entry(int dim, int n, double ih2, const double* __restrict__ k,
+                                                 int q, int col)
 {
-  const int m1 = n - 2;
-  const int m = dim == 3 ? m1 * m1 * m1 : m1 * m1;
-  const int tid = threadIdx.x;
-  for (size_t e = tid; e < (size_t)m * m; e += blockDim.x) a[e] = 0.0;
-  if (tid == 0) *flag = 0;
-  __syncthreads();
+  int z, y, x, cz, cy, cx;
+  unknown_to_node(dim, n, q, z, y, x);
+  unknown_to_node(dim, n, col, cz, cy, cx);
   const size_t sy = (size_t)n, sz = (size_t)n * n;
-  for (int q = tid; q < m; q += blockDim.x) {
-    int z, y, x;
-    unknown_to_node(dim, n, q, z, y, x);
-    const size_t i = ((size_t)z * n + y) * (size_t)n + x;
-    const int nz[6] = {z, z, z, z, z - 1, z + 1};
-    const int ny[6] = {y, y, y - 1, y + 1, y, y};
-    const int nx[6] = {x - 1, x + 1, x, x, x, x};
-    const ptrdiff_t off[6] = {-1, 1, -(ptrdiff_t)sy, (ptrdiff_t)sy, -(ptrdiff_t)sz, (ptrdiff_t)sz};
-    for (int j = 0; j < 2 * dim; ++j) {
-      const double c = k ? 0.5 * (k[i] + k[i + off[j]]) : 1.0;
-      a[(size_t)q * m + q] += c * ih2;
-      const bool nb_in = nx[j] >= 1 && nx[j] <= n - 2 && ny[j] >= 1 && ny[j] <= n - 2 &&
-                         (dim == 2 || (nz[j] >= 1 && nz[j] <= n - 2));
-      if (nb_in) {
-        const int col = dim == 3 ? ((nz[j] - 1) * m1 + (ny[j] - 1)) * m1 + (nx[j] - 1)
-                                 : (ny[j] - 1) * m1 + (nx[j] - 1);
-        a[(size_t)q * m + col] -= c * ih2;
-      }
-    }
+  const size_t i = ((size_t)z * n + y) * (size_t)n + x;
+  const int nz[6] = {z, z, z, z, z - 1, z + 1};
+  const int ny[6] = {y, y, y - 1, y + 1, y, y};
+  const int nx[6] = {x - 1, x + 1, x, x, x, x};
+  const ptrdiff_t off[6] = {-1, 1, -(ptrdiff_t)sy, (ptrdiff_t)sy, -(ptrdiff_t)sz, (ptrdiff_t)sz};
+  double v = 0.0;
+  for (int j = 0; j < 2 * dim; ++j) {
+    const double c = k ? 0.5 * (k[i] + k[i + off[j]]) : 1.0;
+    if (q == col) v += c * ih2;
+    else if (nz[j] == cz && ny[j] == cy && nx[j] == cx) v -= c * ih2;
   }
+  return v;
+}
+
+// entry (i, j) after the elimination of row and column r, from a_ij, a_ir, a_rj and the pivot
+__device__ __forceinline__ double eliminate(int i, int j, int r, double aij, double air, double arj, double pivot)
+{
+  const double inv = 1.0 / pivot;
+  if (i == r) return j == r ? inv : arj * inv;
+  return j == r ? -(air * inv) : aij - air * (arj * inv);
+}
+
+__device__ __forceinline__ double checked_pivot(double d, int* flag)
+{
+  if (d > 0.0) return d;
+  *flag = 1;
+  return 1.0;
+}
+
+__global__ void __launch_bounds__(kFactorThreads)
+    k_coarsest_inverse(int dim, int n, int m, double ih2, const double* __restrict__ k,
+                       double* __restrict__ ainv, int* flag)
+{
+  extern __shared__ __align__(16) double gj[];
+  constexpr int K = kLdsCoarse * kLdsCoarse / kFactorThreads;
+  if (threadIdx.x == 0) *flag = 0;
+  for (int e = threadIdx.x; e < m * m; e += kFactorThreads) gj[e] = coarsest_entry(dim, n, ih2, k, e / m, e % m);
   __syncthreads();
-  __shared__ double piv;
-  for (int j = 0; j < m; ++j) {
-    if (tid == 0) {
-      const double d = a[(size_t)j * m + j];
-      if (!(d > 0.0)) *flag = 1;
-      piv = d > 0.0 ? sqrt(d) : 1.0;
-      a[(size_t)j * m + j] = piv;
+  for (int r = 0; r < m; ++r) {
+    const double pivot = checked_pivot(gj[r * m + r], flag);
+    double v[K];
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const int e = threadIdx.x + q * kFactorThreads;
+      if (q * kFactorThreads >= m * m) break;  // uniform
+      if (e >= m * m) continue;
+      const int i = e / m, j = e - i * m;
+      v[q] = eliminate(i, j, r, gj[e], gj[i * m + r], gj[r * m + j], pivot);
     }
     __syncthreads();
-    for (int i = j + 1 + tid; i < m; i += blockDim.x) a[(size_t)i * m + j] /= piv;
-    __syncthreads();
-    for (int i = j + 1 + tid; i < m; i += blockDim.x) {
-      const double lij = a[(size_t)i * m + j];
-      for (int p = j + 1; p <= i; ++p) a[(size_t)i * m + p] -= lij * a[(size_t)p * m + j];
+#pragma unroll
+    for (int q = 0; q < K; ++q) {
+      const int e = threadIdx.x + q * kFactorThreads;
+      if (e < m * m) gj[e] = v[q];
     }
     __syncthreads();
   }
-  // column c of A^-1: solve L y = e_c, then L^T x = y; stored in column c of ainv
-  for (int c = tid; c < m; c += blockDim.x) {
-    for (int i = 0; i < m; ++i) {
-      double s = (i == c) ? 1.0 : 0.0;
-      for (int p = c; p < i; ++p) s -= a[(size_t)i * m + p] * ainv[(size_t)p * m + c];
-      ainv[(size_t)i * m + c] = (i < c) ? 0.0 : s / a[(size_t)i * m + i];
-    }
-    for (int i = m - 1; i >= 0; --i) {
-      double s = ainv[(size_t)i * m + c];
-      for (int p = i + 1; p < m; ++p) s -= a[(size_t)p * m + i] * ainv[(size_t)p * m + c];
-      ainv[(size_t)i * m + c] = s / a[(size_t)i * m + i];
-    }
-  }
+  for (int e = threadIdx.x; e < m * m; e += kFactorThreads) ainv[e] = gj[e];
+}
+
+__global__ void __launch_bounds__(kBlock)
+    k_coarsest_assemble(int dim, int n, int m, double ih2, const double* __restrict__ k,
+                        double* __restrict__ a, int* flag)
+{
+  const int e = blockIdx.x * kBlock + threadIdx.x;
+  if (e == 0) *flag = 0;
+  if (e < m * m) a[e] = coarsest_entry(dim, n, ih2, k, e / m, e % m);
+}
+
+// step r, src -> dst
+__global__ void __launch_bounds__(kBlock)
+    k_coarsest_step(int m, int r, const double* __restrict__ src, double* __restrict__ dst, int* flag)
+{
+  const int e = blockIdx.x * kBlock + threadIdx.x;
+  if (e >= m * m) return;
+  const int i = e / m, j = e - i * m;
+  const double pivot = checked_pivot(src[r * m + r], flag);
+  dst[e] = eliminate(i, j, r, src[e], src[i * m + r], src[r * m + j], pivot);
 }
 
 // One workgroup: interior of u = ainv * interior of f (coarsest_apply).
@@ -610,7 +642,25 @@ void prolong_add(hipStream_t s, int dim, int nc, const T* ec, T* u)
 void coarsest_factor(hipStream_t s, int dim, int n, double h, const double* k, double* work,
                      double* ainv, int* flag)
 {
-  k_coarsest_factor<<<1, kBlock, 0, s>>>(dim, n, 1.0 / (h * h), k, work, ainv, flag);
+  const int m1 = n - 2, m = dim == 3 ? m1 * m1 * m1 : m1 * m1;
+  const double ih2 = 1.0 / (h * h);
+  const size_t lds = sizeof(double) * m * m;
+  if (m <= kLdsCoarse &&
+      (lds <= 64 * 1024 || hipFuncSetAttribute(reinterpret_cast<const void*>(k_coarsest_inverse),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess)) {
+    k_coarsest_inverse<<<1, kFactorThreads, lds, s>>>(dim, n, m, ih2, k, ainv, flag);
+    return;
+  }
+  if (m <= kLdsCoarse) (void)hipGetLastError();  // refused: the steps by launches
+  const int blocks = cdiv((long long)m * m, kBlock);
+  double *src = m % 2 ? work : ainv, *dst = m % 2 ? ainv : work;  // m steps end in ainv
+  k_coarsest_assemble<<<blocks, kBlock, 0, s>>>(dim, n, m, ih2, k, src, flag);
+  for (int r = 0; r < m; ++r) {
+    k_coarsest_step<<<blocks, kBlock, 0, s>>>(m, r, src, dst, flag);
+    double* x = src;
+    src = dst;
+    dst = x;
+  }
 }
 
 template <typename T>

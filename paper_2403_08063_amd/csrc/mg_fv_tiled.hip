@@ -483,6 +483,11 @@ void fv_sweeps(hipStream_t s, int N, double h, double omega, int sweeps, const d
                const double* f, const double* ec, double* out, double* fc, double* partial,
                double* norm2)
 {
+  if (fv_cube_supported(N)) {
+    const int blocks = fv_cube_sweeps(s, N, h, omega, sweeps, u, f, ec, out, fc, partial, norm2 != nullptr);
+    if (norm2) k_fv_sum_partials<<<1, 256, 0, s>>>(partial, blocks, norm2);
+    return;
+  }
   if (sweeps == 3) launch_s<3>(s, N, h, omega, u, f, ec, out, fc, partial, norm2);
   else launch_s<2>(s, N, h, omega, u, f, ec, out, fc, partial, norm2);
 }

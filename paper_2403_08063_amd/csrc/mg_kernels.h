@@ -207,6 +207,11 @@ void fv_restrict_tiled(hipStream_t s, int N, double h, const double* f, const do
 void fv_sweeps(hipStream_t s, int N, double h, double omega, int sweeps, const double* u,
                const double* f, const double* ec, double* out, double* fc, double* partial,
                double* norm2);
+// The passes of fv_sweeps on small levels (mg_fv_cube.hip; fv_sweeps calls it there): returns the
+// number of partial sums (norm).
+bool fv_cube_supported(int N);
+int fv_cube_sweeps(hipStream_t s, int N, double h, double omega, int sweeps, const double* u,
+                   const double* f, const double* ec, double* out, double* fc, double* partial, bool norm);
 // out = sum over cells of (f - A u)^2 (partial: kStreamPartials doubles)
 void fv_norm2_tiled(hipStream_t s, int N, double h, const double* f, const double* u,
                     double* partial, double* out);

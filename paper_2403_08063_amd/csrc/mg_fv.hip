@@ -330,7 +330,7 @@ __global__ void __launch_bounds__(kFvCoarseThreads)
 
 // The coarsest solver on 4^3 cells, one lane per cell of one wave: no barrier, the value and f
 // stay in registers, x- and y-neighbours come by DPP within 16 lanes (a plane), z-neighbours by
-// a lane permute.  Same operations as k_fv_coarse.  256 iterations: FVC4_US us, against 90 us in
+// a lane permute.  Same operations as k_fv_coarse.  256 iterations: 20 us, against 90 us in
 // a 1024-thread workgroup that read f from memory and met a barrier per iteration.
 constexpr int kRowShl1 = 0x101, kRowShl4 = 0x104, kRowShr1 = 0x111, kRowShr4 = 0x114;
 
@@ -372,15 +372,15 @@ __global__ void __launch_bounds__(64)
   u[i] = fv_coarse4(ih2, coef, iters, zero ? 0.0 : u[i], f[i], ghost(x, 1), ghost(y, 6), ghost(z, 36));
 }
 
-// The V-cycle's tail in one launch: the levels from at most 16^3 cells down to the coarsest, from
-// a zero correction, in one workgroup with the iterates in LDS and f in registers.  A level of
-// that size is launch latency (a sweep of 3.5-5 us does 0.3-1 us of work), and a cycle visits
-// each with six sweeps and two transfers.  Same operations as the per-level kernels.
-// Measured, 16^3 to 4^3 with 256 coarsest iterations: FVTAIL_US us per cycle, against 150 us in
-// 17 launches.
-constexpr int kFvTailN = 16, kFvTailLevels = 4, kFvTailThreads = 1024;
+// The V-cycle's tail in one launch: the level of 8^3 cells down to the coarsest, from a zero
+// correction, in one workgroup with the iterates in LDS and f in registers.  Such a level is
+// launch latency (a sweep of 3.5 us does 0.3 us of work).  16^3 cells do better in the eight
+// workgroups of mg_fv_cube.hip (14 us a cycle) than here (24 us).
+// Same operations as the per-level kernels.
+// Measured, 8^3 and 4^3 with 256 coarsest iterations: 32 us per cycle, against 120 us in 9 launches.
+constexpr int kFvTailN = 8, kFvTailThreads = kFvTailN * kFvTailN * kFvTailN;
 struct FvTailArgs {
-  int N, levels, nu1, nu2, coarse_iters;
+  int levels, nu1, nu2, coarse_iters;
   double omega, h;  // of the first level
   const double* f;
   double* u;
@@ -388,72 +388,60 @@ struct FvTailArgs {
 
 // LDS doubles of a tail level: two iterates with their ghost layers
 __host__ __device__ constexpr int fv_tail_doubles(int N) { return 2 * (N + 2) * (N + 2) * (N + 2); }
-constexpr size_t kFvTailLds = sizeof(double) * (fv_tail_doubles(16) + fv_tail_doubles(8) + fv_tail_doubles(4) + fv_tail_doubles(2));
 
-// N: cells per side (compile-time, so that the cells of a thread and their f are registers)
+// `left` levels from one of N cells per side and spacing h on; the result in the first of its two
+// buffers at `base`
 template <int N>
-__device__ void fv_tail_level(const FvTailArgs& a, int left, double h, double* base,
-                              const double (&f)[(N * N * N + kFvTailThreads - 1) / kFvTailThreads])
+__device__ void fv_tail_level(const FvTailArgs& a, int left, double h, double* base, double f)
 {
-  constexpr int m = N + 2, cells = N * N * N, K = (cells + kFvTailThreads - 1) / kFvTailThreads;
-  constexpr int lg = N == 16 ? 4 : N == 8 ? 3 : N == 4 ? 2 : 1;
+  constexpr int m = N + 2, cells = N * N * N;
+  constexpr int lg = N == 8 ? 3 : N == 4 ? 2 : 1;
   const double ih2 = 1.0 / (h * h), coef = a.omega * (h * h / 6.0);
   double* buf[2] = {base, base + m * m * m};
   int cur = 0;
-  int at[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int t = threadIdx.x + k * kFvTailThreads;
-    at[k] = ((1 + (t >> (2 * lg))) * m + 1 + ((t >> lg) & (N - 1))) * m + 1 + (t & (N - 1));
-  }
-  // A u at cell k from the current buffer; the correction vanishes on the faces (ghost 2 0 - u)
-  auto apply = [&](const double* s, int k) {
-    const int t = threadIdx.x + k * kFvTailThreads, i = at[k];
-    const int x = t & (N - 1), y = (t >> lg) & (N - 1), z = t >> (2 * lg);
-    const double ui = s[i], g = 0.0 - ui;
-    double v = ui - (x == 0 ? g : s[i - 1]);
-    v = v + (ui - (x == N - 1 ? g : s[i + 1]));
-    v = v + (ui - (y == 0 ? g : s[i - m]));
-    v = v + (ui - (y == N - 1 ? g : s[i + m]));
-    v = v + (ui - (z == 0 ? g : s[i - m * m]));
-    v = v + (ui - (z == N - 1 ? g : s[i + m * m]));
+  const int t = threadIdx.x, x = t & (N - 1), y = (t >> lg) & (N - 1), z = t >> (2 * lg);
+  const bool on = t < cells;  // one cell per thread
+  const int at = ((1 + z) * m + 1 + y) * m + 1 + x;
+  // A u at the cell; the correction vanishes on the faces (ghost 2 0 - u)
+  auto apply = [&](const double* s) {
+    const double ui = s[at], g = 0.0 - ui;
+    double v = ui - (x == 0 ? g : s[at - 1]);
+    v = v + (ui - (x == N - 1 ? g : s[at + 1]));
+    v = v + (ui - (y == 0 ? g : s[at - m]));
+    v = v + (ui - (y == N - 1 ? g : s[at + m]));
+    v = v + (ui - (z == 0 ? g : s[at - m * m]));
+    v = v + (ui - (z == N - 1 ? g : s[at + m * m]));
     return v * ih2;
-  };
-  auto each = [&](auto&& fn) {
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-      if (cells % kFvTailThreads == 0 || threadIdx.x + k * kFvTailThreads < cells) fn(k);
   };
   auto sweep = [&](bool zero) {
     const double* s = buf[cur];
     double* d = buf[1 - cur];
-    if (zero) each([&](int k) { d[at[k]] = 0.0 + coef * (f[k] - 0.0); });
-    else each([&](int k) { d[at[k]] = s[at[k]] + coef * (f[k] - apply(s, k)); });
+    if (on && zero) d[at] = 0.0 + coef * (f - 0.0);
+    else if (on) d[at] = s[at] + coef * (f - apply(s));
     cur = 1 - cur;
     __syncthreads();
   };
   if (left == 1) {  // the coarsest level
     if (a.coarse_iters == 0) {
-      each([&](int k) { buf[cur][at[k]] = 0.0; });
+      if (on) buf[cur][at] = 0.0;
     } else if (N == 4) {
-      if (threadIdx.x < 64) buf[cur][at[0]] = fv_coarse4(ih2, coef, a.coarse_iters, 0.0, f[0], 0.0, 0.0, 0.0);
+      if (on) buf[cur][at] = fv_coarse4(ih2, coef, a.coarse_iters, 0.0, f, 0.0, 0.0, 0.0);
     } else {
       for (int it = 0; it < a.coarse_iters; ++it) sweep(it == 0);
     }
     __syncthreads();
   } else {
     if (a.nu1 == 0) {
-      each([&](int k) { buf[cur][at[k]] = 0.0; });
+      if (on) buf[cur][at] = 0.0;
       __syncthreads();
     }
     for (int s = 0; s < a.nu1; ++s) sweep(s == 0);
     if constexpr (N > 2) {
       // restriction: the residuals into the other buffer, then the mean of 8 children
       constexpr int C = N / 2, cc = C * C * C, lc = lg - 1;
-      each([&](int k) { buf[1 - cur][at[k]] = f[k] - apply(buf[cur], k); });
+      if (on) buf[1 - cur][at] = f - apply(buf[cur]);
       __syncthreads();
-      double fc[1] = {0.0};
-      const int t = threadIdx.x;
+      double fc = 0.0;
       if (t < cc) {
         const int X = t & (C - 1), Y = (t >> lc) & (C - 1), Z = t >> (2 * lc);
         const double* r = buf[1 - cur] + ((1 + 2 * Z) * m + 1 + 2 * Y) * m + 1 + 2 * X;
@@ -464,15 +452,14 @@ __device__ void fv_tail_level(const FvTailArgs& a, int left, double h, double* b
           for (int dy = 0; dy < 2; ++dy)
 #pragma unroll
             for (int dx = 0; dx < 2; ++dx) s += r[(dz * m + dy) * m + dx];
-        fc[0] = s / 8.0;
+        fc = s / 8.0;
       }
       double* cbase = base + fv_tail_doubles(N);
       fv_tail_level<C>(a, left - 1, 2.0 * h, cbase, fc);
       // u += P e: 8 terms in the order z, y, x, parent first
       constexpr int mc = C + 2;
-      each([&](int k) {
-        const int q = threadIdx.x + k * kFvTailThreads;
-        const int c[3] = {q & (N - 1), (q >> lg) & (N - 1), q >> (2 * lg)};
+      if (on) {
+        const int c[3] = {x, y, z};
         int par[3], nb[3];
         double sg[3];
 #pragma unroll
@@ -485,49 +472,39 @@ __device__ void fv_tail_level(const FvTailArgs& a, int left, double h, double* b
         double s = 0.0;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-          const bool z = j & 4, y = j & 2, x = j & 1;
-          const double wt = (z ? 0.25 : 0.75) * (y ? 0.25 : 0.75) * (x ? 0.25 : 0.75);
-          const double sign = (z ? sg[2] : 1.0) * (y ? sg[1] : 1.0) * (x ? sg[0] : 1.0);
-          s += wt * (sign * cbase[((z ? nb[2] : par[2]) * mc + (y ? nb[1] : par[1])) * mc + (x ? nb[0] : par[0])]);
+          const bool qz = j & 4, qy = j & 2, qx = j & 1;  // the neighbour along that axis
+          const double wt = (qz ? 0.25 : 0.75) * (qy ? 0.25 : 0.75) * (qx ? 0.25 : 0.75);
+          const double sign = (qz ? sg[2] : 1.0) * (qy ? sg[1] : 1.0) * (qx ? sg[0] : 1.0);
+          s += wt * (sign * cbase[((qz ? nb[2] : par[2]) * mc + (qy ? nb[1] : par[1])) * mc + (qx ? nb[0] : par[0])]);
         }
-        buf[cur][at[k]] = buf[cur][at[k]] + s;
-      });
+        buf[cur][at] = buf[cur][at] + s;
+      }
       __syncthreads();
     }
     for (int s = 0; s < a.nu2; ++s) sweep(false);
   }
   if (cur == 1) {  // the caller reads the first buffer
-    each([&](int k) { buf[0][at[k]] = buf[1][at[k]]; });
+    if (on) buf[0][at] = buf[1][at];
     __syncthreads();
   }
 }
 
-template <int N>
 __global__ void __launch_bounds__(kFvTailThreads) k_fv_tail(FvTailArgs a)
 {
-  extern __shared__ __align__(16) double fv_lds[];
-  constexpr int m = N + 2, cells = N * N * N, K = (cells + kFvTailThreads - 1) / kFvTailThreads;
-  auto node = [](int t) { return (size_t)((1 + t / (N * N)) * m + 1 + (t / N) % N) * m + 1 + t % N; };
-  double f[K];
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int t = threadIdx.x + k * kFvTailThreads;
-    f[k] = t < cells ? a.f[node(t)] : 0.0;
-  }
-  fv_tail_level<N>(a, a.levels, a.h, fv_lds, f);
-#pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int t = threadIdx.x + k * kFvTailThreads;
-    if (t < cells) a.u[node(t)] = fv_lds[node(t)];
-  }
+  constexpr int N = kFvTailN, m = N + 2;
+  __shared__ double lds[fv_tail_doubles(8) + fv_tail_doubles(4) + fv_tail_doubles(2)];
+  const int t = threadIdx.x;
+  const int node = ((1 + t / (N * N)) * m + 1 + (t / N) % N) * m + 1 + t % N;
+  fv_tail_level<N>(a, a.levels, a.h, lds, a.f[node]);
+  a.u[node] = lds[node];
 }
 
 // ---------------------------------------------------------------- level operations
 double jacobi_coef(const mgfv_ctx* c, const FvLevel& L) { return c->g.omega * (L.h * L.h / 6.0); }
 
-// Levels of at least this many cells per side run 2 or 3 sweeps per launch (mg_fv_tiled.hip): at
-// 32^3 a pass is still a chain of about ten plane steps on 16 workgroups, FVMIN
-constexpr int kFvBlockedMin = 32;
+// Levels of at least this many cells per side run 2 or 3 sweeps per launch (fv_sweeps); smaller ones
+// are in the tail or are the coarsest.
+constexpr int kFvBlockedMin = 16;
 
 // `sweeps` Jacobi sweeps on level l from u (alternating with t, whose ghost layer equals u's);
 // returns the buffer that holds the result.  zero: u is 0 (a coarse level's zero correction,
@@ -633,9 +610,8 @@ double* coarse_cycle(mgfv_ctx* c, int l)
 {
   FvLevel& L = c->lv[l];
   if (l == c->tail) {
-    const FvTailArgs a{L.N, c->g.levels - l, c->g.nu1, c->g.nu2, c->g.coarse_iters, c->g.omega, L.h, L.f, L.u};
-    auto k = L.N == 16 ? k_fv_tail<16> : k_fv_tail<8>;
-    k<<<1, kFvTailThreads, kFvTailLds, c->s>>>(a);
+    const FvTailArgs a{c->g.levels - l, c->g.nu1, c->g.nu2, c->g.coarse_iters, c->g.omega, L.h, L.f, L.u};
+    k_fv_tail<<<1, kFvTailThreads, 0, c->s>>>(a);
     return L.u;
   }
   if (l == c->g.levels - 1) {
@@ -730,17 +706,8 @@ mg_status mgfv_setup(const mgfv_grid* grid, void* workspace, size_t bytes, void*
   fv_layout(grid, cv, c);
   // coarse ghost layers (zero Dirichlet data of the corrections) are never written after this
   mgk::fill<double>(c->s, need / sizeof(double), 0.0, static_cast<double*>(workspace));
-  // the tail starts at the first coarse level of at most 16^3 cells
-  for (int l = 1; l < grid->levels && c->tail < 0; ++l)
-    if (c->lv[l].N <= kFvTailN && c->lv[l].N >= 8 && grid->levels - l <= kFvTailLevels) c->tail = l;
-  if (c->tail >= 0) {
-    const void* k = c->lv[c->tail].N == 16 ? reinterpret_cast<const void*>(k_fv_tail<16>)
-                                           : reinterpret_cast<const void*>(k_fv_tail<8>);
-    if (hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kFvTailLds) != hipSuccess) {
-      (void)hipGetLastError();
-      c->tail = -1;  // per-level launches
-    }
-  }
+  for (int l = 1; l < grid->levels; ++l)
+    if (c->lv[l].N == kFvTailN) c->tail = l;
   // one pinned word for norm reads that leave the stream running; without it they wait
   void* hp = nullptr;
   if (hipHostMalloc(&hp, 64, hipHostMallocDefault) == hipSuccess) {

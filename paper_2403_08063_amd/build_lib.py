@@ -16,7 +16,8 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmg.so")
 SOURCES = ["mg_api.hip", "mg_fv.hip", "mg_blocks.hip", "mg_galerkin.hip", "mg_kernels.hip", "mg_smooth_tiled.hip",
            "mg_resid_tiled.hip", "mg_tail.hip", "mg_fv_tiled.hip",
-           "mg_smooth_2d.hip", "mg_smooth_cube.hip", "mg_fv_cube.hip"]
+           "mg_smooth_2d.hip", "mg_smooth_cube.hip", "mg_fv_cube.hip",
+           "mg_blocks_tiled.hip"]
 ARCH = os.environ.get("MG_OFFLOAD_ARCH", "gfx950")
 
 FLAGS = [

@@ -10,13 +10,16 @@
 // fly: the C2F value is the tensor product of three 1D Lagrange weight sets (normal,
 // first and second tangential axis), the bases chosen per cell as the rule prescribes.  The
 // Jacobi kernel runs one thread per inner cell of all blocks, each block with its own h; the
+// Levels of 64 to 128 cells a side take two sweeps per pass (mg_blocks_tiled.hip); the
 // restriction one thread per coarse cell (its 8 children's residuals, mean), the
 // prolongation one thread per fine cell (parent and three face neighbours, weight 1/4 each).
 #include "../../include/mg_blocks.h"
+#include "mg_blocks_layout.h"
 #include "mg_kernels.h"
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -24,15 +27,13 @@
 #include <map>
 #include <new>
 #include <tuple>
+#include <utility>
 #include <vector>
 
 namespace {
 
-constexpr int kBlocks = 120;
-constexpr int kFaceInts = 8;  // kind, neighbour blocks[4], quadrant s1, s2, slot (see build_faces)
 constexpr size_t kBlkAlign = 256;
 constexpr int kBlkNormBlocks = 1024;
-enum { kFaceBoundary = 0, kFaceSame = 1, kFaceF2C = 2, kFaceC2F = 3 };
 
 thread_local char g_blk_err[512] = "no error";
 
@@ -60,6 +61,7 @@ std::vector<BlockDesc> build_layout()
 // face f = 2 * axis + side (axis 0 = x, 1 = y, 2 = z; side 0 = low, 1 = high).  Entry 7 of an
 // F2C or C2F face is its number among the faces of its kind (kF2CFaces, kC2FFaces of them).
 constexpr int kF2CFaces = 24, kC2FFaces = 96;
+constexpr int kInterpFaces = kF2CFaces + kC2FFaces;
 
 std::vector<int> build_faces(const std::vector<BlockDesc>& blocks)
 {
@@ -118,6 +120,9 @@ std::vector<int> build_faces(const std::vector<BlockDesc>& blocks)
       }
     }
   }
+  // behind the table: the F2C and C2F faces as 6 block + face
+  for (int i = 0; i < (int)blocks.size() * 6; ++i)
+    if (t[(size_t)i * kFaceInts] == kFaceF2C || t[(size_t)i * kFaceInts] == kFaceC2F) t.push_back(i);
   return t;
 }
 
@@ -170,7 +175,8 @@ struct BlkLevel {
 struct mgblk_ctx {
   mgblk_grid g{};
   hipStream_t s = nullptr;
-  int* faces = nullptr;   // device face table
+  int* faces = nullptr;   // device face table, then the list of interpolated faces
+  double* g1 = nullptr;   // ghost values of a first sweep (k_blk_pair), 0 where no level uses them
   double* partial = nullptr;
   double* scal = nullptr;
   std::vector<BlkLevel> lv;
@@ -236,8 +242,8 @@ struct BlkCarver {
 
 void blk_layout(const mgblk_grid* g, BlkCarver& cv, mgblk_ctx* c)
 {
-  int* faces = cv.take<int>((size_t)kBlocks * 6 * kFaceInts);
-  double* partial = cv.take<double>(kBlkNormBlocks);
+  int* faces = cv.take<int>((size_t)kBlocks * 6 * kFaceInts + kInterpFaces);
+  double* partial = cv.take<double>(mgk::kBlkPartials);
   double* scal = cv.take<double>(8);
   std::vector<BlkLevel> lv;
   for (int B : level_sizes(g)) {
@@ -253,7 +259,12 @@ void blk_layout(const mgblk_grid* g, BlkCarver& cv, mgblk_ctx* c)
     }
     lv.push_back(L);
   }
+  size_t ghosts = 0;
+  for (const BlkLevel& L : lv)
+    if (mgk::blk_pair_supported(L.B)) ghosts = std::max(ghosts, (size_t)kBlocks * 6 * L.B * L.B);
+  double* gh = ghosts ? cv.take<double>(ghosts) : nullptr;
   if (c) {
+    c->g1 = gh;
     c->faces = faces;
     c->partial = partial;
     c->scal = scal;
@@ -376,6 +387,22 @@ __global__ void __launch_bounds__(kFillThreads)
   fill_ghost<ORDER>(B, W, faces, u, q, blockIdx.y, blockIdx.z);
 }
 
+// The ghosts of the interpolated faces (`list`: 6 block + face) from u, into the ghost planes g.
+template <int ORDER>
+__global__ void __launch_bounds__(kFillThreads)
+    k_blk_fill_planes(int B, C2FWeights W, const int* __restrict__ faces,
+                      const int* __restrict__ list, const double* __restrict__ u,
+                      double* __restrict__ g)
+{
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= B * B) return;
+  const int bf = list[blockIdx.y], f = bf % 6, b = bf / 6;
+  const int m = B + 2;
+  auto rd = [&](int bb, int z, int y, int x) { return u[bidx(m, bb, z, y, x)]; };
+  g[ghost_index(B, b, f, 1 + q % B, 1 + q / B)] =
+      interface_ghost<ORDER>(rd, B, W, faces + (size_t)bf * kFaceInts, f >> 1, f & 1, 1 + q % B, 1 + q / B);
+}
+
 // (A u) at inner cell (z, y, x) of block b from the six stored neighbours: interface ghosts
 // filled from the neighbouring blocks; on the solution level the domain-boundary ghosts hold
 // the Dirichlet data at their own centres and are read as stored (Sect. 5; the reading under
@@ -456,6 +483,47 @@ __device__ __forceinline__ bool cell_of(int B, int& b, int& z, int& y, int& x)
   y = 1 + yy;
   x = 1 + r - yy * B;
   return true;
+}
+
+// First sweep's values that k_blk_pair reads at its blocks' ghosts, into g: one thread per ghost
+// of every face.  A same-level face's ghost is the sweep's value in the neighbour's cell, sent
+// by the block that owns the cell; a domain-boundary ghost keeps its value; next to an
+// interpolated face the cells that its rule reads (order + 1 deep from the coarse side, 2 from
+// the fine) go into t's inner cells, for k_blk_fill_planes.  zero: u is identically 0.
+__global__ void __launch_bounds__(kFillThreads)
+    k_blk_shell(int B, int order, double omega, const int* __restrict__ faces,
+                const double* __restrict__ hs, const double* __restrict__ f,
+                const double* __restrict__ u, double* __restrict__ t, double* __restrict__ g,
+                int coarse, int zero)
+{
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= B * B) return;
+  const int face = blockIdx.y, b = blockIdx.z, ax = face >> 1, side = face & 1;
+  const int* fb = faces + (size_t)b * 6 * kFaceInts;
+  const int* e = fb + face * kFaceInts;
+  const int m = B + 2, t1 = 1 + q % B, t2 = 1 + q / B;
+  int x, y, z;
+  if (e[0] == kFaceBoundary) {
+    face_coords(ax, side ? B + 1 : 0, t1, t2, x, y, z);
+    g[ghost_index(B, b, face, t1, t2)] = u[bidx(m, b, z, y, x)];
+    return;
+  }
+  const double h = hs[b];
+  const int depth = e[0] == kFaceSame ? 1 : e[0] == kFaceF2C ? order + 1 : 2;
+  for (int d = 0; d < depth; ++d) {
+    face_coords(ax, side ? B - d : 1 + d, t1, t2, x, y, z);
+    const size_t i = bidx(m, b, z, y, x);
+    double v;
+    if (zero) {
+      const double none[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+      v = 0.0 + omega * (h * h / 6.0) * (f[i] - blk_apply_vals(1.0 / (h * h), 0.0, none, 0u, coarse != 0));
+    } else {
+      const double au = blk_apply_at(B, fb, 1.0 / (h * h), u, i, z, y, x, coarse != 0);
+      v = u[i] + omega * (h * h / 6.0) * (f[i] - au);
+    }
+    if (e[0] == kFaceSame) g[ghost_index(B, e[1], face ^ 1, t1, t2)] = v;
+    else t[i] = v;
+  }
 }
 
 // the damped Jacobi update of inner cell (z, y, x) of block b, u -> uout
@@ -1080,6 +1148,24 @@ void copy_boundary(mgblk_ctx* c, int l, const double* src, double* dst)
   k_blk_copy_boundary<<<face_grid(B), face_threads(B), 0, c->s>>>(B, c->faces, src, dst);
 }
 
+// Two sweeps in one pass, cur -> oth (blk_pair): cur's interface ghosts are filled, then the first
+// sweep's values at the ghosts are formed in c->g1.  norm: see blk_pair.
+void pair_sweep(mgblk_ctx* c, int l, const double* f, double* cur, double* oth, bool zero,
+                double* norm = nullptr)
+{
+  const BlkLevel& L = c->lv[l];
+  const int B = L.B, t = face_threads(B);
+  if (!zero) fill(c, l, cur);
+  k_blk_shell<<<face_grid(B), t, 0, c->s>>>(B, c->g.order, c->g.omega, c->faces, L.hs, f, cur, oth, c->g1,
+                                            l > 0, zero);
+  const dim3 grid((unsigned)((B * B + t - 1) / t), kInterpFaces);
+  const int* list = c->faces + (size_t)kBlocks * 6 * kFaceInts;
+  if (c->g.order == 0) k_blk_fill_planes<0><<<grid, t, 0, c->s>>>(B, c->w, c->faces, list, oth, c->g1);
+  else if (c->g.order == 1) k_blk_fill_planes<1><<<grid, t, 0, c->s>>>(B, c->w, c->faces, list, oth, c->g1);
+  else k_blk_fill_planes<2><<<grid, t, 0, c->s>>>(B, c->w, c->faces, list, oth, c->g1);
+  mgk::blk_pair(c->s, B, c->g.omega, c->faces, L.hs, f, cur, c->g1, oth, l > 0, zero, c->partial, norm);
+}
+
 // `count` sweeps on level l with a fill before each, alternating between cur and oth (which
 // holds the same domain-boundary ghosts); returns the buffer holding the result.  zero: cur is
 // identically 0 (a coarse level's initial correction, l > 0): the first sweep reads neither
@@ -1103,6 +1189,12 @@ double* sweeps(mgblk_ctx* c, int l, const double* f, double* cur, double* oth, i
       double* x = cur;
       cur = oth;
       oth = x;
+      continue;
+    }
+    if (mgk::blk_pair_supported(B) && s + 1 < count) {
+      pair_sweep(c, l, f, cur, oth, z0);
+      std::swap(cur, oth);
+      ++s;
       continue;
     }
     if (!z0) fill(c, l, cur);
@@ -1157,8 +1249,10 @@ Coarse4Kernel coarse4_kernel(int order)
 }
 
 // V(nu1, nu2) on level l from the iterate in x (y: the level's second buffer); returns the
-// buffer holding the result.  Coarse problems start from 0 in the level's u.
-double* vcycle_rec(mgblk_ctx* c, int l, const double* f, double* x, double* y, bool zero = false)
+// buffer holding the result.  Coarse problems start from 0 in the level's u.  done: pre-smoothing
+// sweeps that x has had.
+double* vcycle_rec(mgblk_ctx* c, int l, const double* f, double* x, double* y, bool zero = false,
+                   int done = 0)
 {
   const int last = (int)c->lv.size() - 1;
   if (l == last) {
@@ -1172,7 +1266,7 @@ double* vcycle_rec(mgblk_ctx* c, int l, const double* f, double* x, double* y, b
     }
     return sweeps(c, l, f, x, y, c->g.coarse_iters, zero);
   }
-  double* cur = sweeps(c, l, f, x, y, c->g.nu1, zero);
+  double* cur = sweeps(c, l, f, x, y, c->g.nu1 - done, zero);
   double* oth = cur == x ? y : x;
   BlkLevel& C = c->lv[l + 1];
   // the coarse level starts from a zero correction: read as 0 by its first sweep, or, when
@@ -1184,11 +1278,8 @@ double* vcycle_rec(mgblk_ctx* c, int l, const double* f, double* x, double* y, b
   return sweeps(c, l, f, cur, oth, c->g.nu2);
 }
 
-mg_status norm2(mgblk_ctx* c, const double* f, double* u, double* out)
+mg_status read_norm(mgblk_ctx* c, double* out)
 {
-  fill(c, 0, u);
-  k_blk_norm2<<<kBlkNormBlocks, 256, 0, c->s>>>(c->lv[0].B, c->faces, c->lv[0].hs, f, u, c->partial);
-  k_blk_sum<<<1, 256, 0, c->s>>>(c->partial, kBlkNormBlocks, c->scal);
   if (mg_status st = blk_hip(c, hipGetLastError(), "norm")) return st;
   if (mg_status st = blk_hip(c, hipMemcpyAsync(out, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s),
                              "reading the norm"))
@@ -1196,12 +1287,21 @@ mg_status norm2(mgblk_ctx* c, const double* f, double* u, double* out)
   return blk_hip(c, hipStreamSynchronize(c->s), "stream synchronisation");
 }
 
-// one V-cycle on the finest level, the result in u
-void vcycle_top(mgblk_ctx* c, const double* f, double* u)
+mg_status norm2(mgblk_ctx* c, const double* f, double* u, double* out)
+{
+  fill(c, 0, u);
+  k_blk_norm2<<<kBlkNormBlocks, 256, 0, c->s>>>(c->lv[0].B, c->faces, c->lv[0].hs, f, u, c->partial);
+  k_blk_sum<<<1, 256, 0, c->s>>>(c->partial, kBlkNormBlocks, c->scal);
+  return read_norm(c, out);
+}
+
+// one V-cycle on the finest level, the result in u; started: the first two pre-smoothing sweeps
+// are done, their result in the level's t
+void vcycle_top(mgblk_ctx* c, const double* f, double* u, bool started = false)
 {
   BlkLevel& F = c->lv[0];
-  copy_boundary(c, 0, u, F.t);
-  double* r = vcycle_rec(c, 0, f, u, F.t);
+  if (!started) copy_boundary(c, 0, u, F.t);
+  double* r = started ? vcycle_rec(c, 0, f, F.t, u, false, 2) : vcycle_rec(c, 0, f, u, F.t);
   if (r != u) mgk::copy<double>(c->s, F.cnt, r, u);
 }
 
@@ -1374,15 +1474,24 @@ mg_status mgblk_mg_solve(mgblk_ctx* c, const double* f, double* u, double tol, i
   if (!c) return blk_fail(nullptr, MG_EINVAL, "context is NULL");
   if (!f || !u) return blk_fail(c, MG_EINVAL, "f and u must be non-NULL");
   if (!(tol >= 0)) return blk_fail(c, MG_EINVAL, "tol must be >= 0");
-  double rn2 = 0;
-  mg_status st = norm2(c, f, u, &rn2);
-  double rn = std::sqrt(rn2);
+  // Where two pre-smoothing sweeps are one pass, the norm rides on it (1.4 ms less a cycle at 128^3
+  // cells per block): the pass leaves u alone, and u is returned if the norm ends the solve.
+  const bool ride = mgk::blk_pair_supported(c->lv[0].B) && c->g.nu1 >= 2 && c->lv.size() > 1;
+  if (ride) copy_boundary(c, 0, u, c->lv[0].t);
+  double rn2 = 0, rn = 0;
+  mg_status st = MG_OK;
   int k = 0;
-  while (!st && std::isfinite(rn) && rn > tol && k < c->g.max_cycles) {
-    vcycle_top(c, f, u);
-    ++k;
-    st = norm2(c, f, u, &rn2);
+  for (;; ++k) {
+    const bool last = k == c->g.max_cycles;
+    if (ride && !last) {
+      pair_sweep(c, 0, f, u, c->lv[0].t, false, c->scal);
+      st = read_norm(c, &rn2);
+    } else {
+      st = norm2(c, f, u, &rn2);
+    }
     rn = std::sqrt(rn2);
+    if (st || !std::isfinite(rn) || rn <= tol || last) break;
+    vcycle_top(c, f, u, ride);
   }
   if (cycles) *cycles = k;
   if (resnorm) *resnorm = rn;

@@ -216,4 +216,15 @@ int fv_cube_sweeps(hipStream_t s, int N, double h, double omega, int sweeps, con
 void fv_norm2_tiled(hipStream_t s, int N, double h, const double* f, const double* u,
                     double* partial, double* out);
 
+// Two damped-Jacobi sweeps of the refined layout in one pass, u -> out (mg_blocks_tiled.hip), for
+// the block sizes that blk_pair_supported names.  g: the first sweep's values at every block's
+// ghosts (ghost_index); u's interface ghosts filled; out's ghosts are not written.  coarse:
+// domain-boundary ghosts hold face values; zero: u is identically 0 and not read.  norm2 (optional): the squared norm of u's residual;
+// partial: kBlkPartials doubles.
+constexpr int kBlkPartials = 8192;
+bool blk_pair_supported(int B);
+void blk_pair(hipStream_t s, int B, double omega, const int* faces, const double* hs, const double* f,
+              const double* u, const double* g, double* out, bool coarse, bool zero, double* partial,
+              double* norm2);
+
 }  // namespace mgk

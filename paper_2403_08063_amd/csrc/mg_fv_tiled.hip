@@ -23,6 +23,12 @@
 //
 // Tiles that touch no domain face run without the ghost and Dirichlet selects (EDGE = false).
 // Every cell takes the single passes' operations in their order: results are bitwise equal.
+//
+// A pass is bound by the FP64 issue of its two waves per SIMD (about 300 instructions per wave and
+// plane, 240 of them FP64).  What is not arithmetic counts: cells of a plane in one block without
+// branches, the planes next to a domain face in a copy of their own, and edge rows as 16-byte
+// pairs took the 512^3 passes from 1.40 and 1.07 ms (pre- and post-smoothing) to 1.14 and 0.94;
+// 35 V(3,3) cycles 105.9 -> 88.5 ms.
 #include "mg_buffer.h"
 #include "mg_kernels.h"
 #include "mg_lanes.h"
@@ -64,7 +70,7 @@ struct FvPass {
   static_assert(S >= 1 && S <= 3 && TY > 0, "halo of the tile");
 
   struct Shared {
-    double e[2][NL][VW][2][2][LW];  // [parity][field][row group][first, last row][column][lane]
+    double2 e[2][NL][VW][2][LW];  // [parity][field][row group][first, last row][lane]: two columns
     double red[NORM ? W : 1];
   };
 
@@ -79,13 +85,12 @@ struct FvPass {
 
     // bit 2 i + o: a cell; a cell this tile stores
     unsigned cell = 0, own = 0;
-    uint32_t rowb[RPW], colb[2], stb[2];
+    uint32_t rowb[RPW], colb[2];
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
       const int x = gx + o, px = 2 * lane + o;
       colb[o] = (uint32_t)(EDGE ? min(max(x, 0), N + 1) : x) * 8u;
       const bool xin = x >= 1 && x <= N, xown = xin && px >= H && px < H + TX;
-      stb[o] = xown ? (uint32_t)x * 8u : 0x80000000u;
 #pragma unroll
       for (int i = 0; i < RPW; ++i) {
         const int y = gy + i, py = w * RPW + i;
@@ -116,9 +121,11 @@ struct FvPass {
         for (int q = 0; q < 6; ++q) F[q][i][o] = 0.0;
       }
 
+    // u of plane z, f of plane z - 1: of each plane when it is first needed
     auto load = [&](int z) {
       const size_t zb = (size_t)min(max(z, 0), N + 1) * planeb;
-      const PlaneBuf bu = plane_buf(a.u, zb, planeb), bf = plane_buf(a.f, zb, planeb);
+      const size_t fb = (size_t)min(max(z - 1, 0), N + 1) * planeb;
+      const PlaneBuf bu = plane_buf(a.u, zb, planeb), bf = plane_buf(a.f, fb, planeb);
 #pragma unroll
       for (int i = 0; i < RPW; ++i) {
         if constexpr (EDGE) {
@@ -137,40 +144,50 @@ struct FvPass {
     // Prolongation: the lane's columns 2X, 2X+1 lie between coarse columns X and X+1 (weight
     // 3/4 for the nearer), its rows likewise between coarse rows Y.. ; CA and CB hold the two
     // coarse planes around the current fine plane, CE the one in flight.  Outside the domain
-    // the correction is extended by minus the adjacent cell (sign per axis).
+    // the correction is extended by minus the adjacent cell (a sign per axis).
     constexpr int CR = RPW / 2 + 1;
     const int Nc = N / 2, mc = Nc + 2;
     const uint32_t cplaneb = (uint32_t)((size_t)mc * (size_t)mc * 8u);
     uint32_t ccb[2] = {0, 0}, crb[CR] = {};
-    double csx[2] = {1.0, 1.0}, csy[CR];
+    unsigned csign = 0;  // bit 2 r + c: outside the domain in x or y, not both
     double CA[CR][2], CB[CR][2], CE[CR][2];
-    double csz = 1.0;
+    uint32_t cneg = 0;   // sign of a coarse plane outside the domain
     if constexpr (IN == kProlong) {
       const int X = gx >> 1, Y = gy >> 1;
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        csx[c] = EDGE && (X + c <= 0 || X + c > Nc) ? -1.0 : 1.0;
-        ccb[c] = (uint32_t)min(max(X + c, 1), Nc) * 8u;
+        ccb[c] = (uint32_t)(EDGE ? min(max(X + c, 1), Nc) : X + c) * 8u;
       }
 #pragma unroll
       for (int r = 0; r < CR; ++r) {
-        csy[r] = EDGE && (Y + r <= 0 || Y + r > Nc) ? -1.0 : 1.0;
-        crb[r] = (uint32_t)(min(max(Y + r, 1), Nc) * mc) * 8u;
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          csign |= ((X + c <= 0 || X + c > Nc) != (Y + r <= 0 || Y + r > Nc)) ? 1u << (2 * r + c) : 0u;
+        crb[r] = (uint32_t)((EDGE ? min(max(Y + r, 1), Nc) : Y + r) * mc) * 8u;
       }
     }
     auto cload = [&](int Z) {
-      csz = Z <= 0 || Z > Nc ? -1.0 : 1.0;
+      cneg = Z <= 0 || Z > Nc ? 0x80000000u : 0u;
       const PlaneBuf be = plane_buf(a.ec, (size_t)min(max(Z, 1), Nc) * cplaneb, cplaneb);
 #pragma unroll
-      for (int r = 0; r < CR; ++r)
+      for (int r = 0; r < CR; ++r) {
+        if constexpr (EDGE) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) CE[r][c] = buf_load<double>(be, ccb[c] + crb[r], 0u);
+          for (int c = 0; c < 2; ++c) CE[r][c] = buf_load<double>(be, ccb[c] + crb[r], 0u);
+        } else {
+          buf_load2(be, ccb[0] + crb[r], 0u, CE[r][0], CE[r][1]);
+        }
+      }
     };
     auto ctake = [&](double (&C)[CR][2]) {
 #pragma unroll
       for (int r = 0; r < CR; ++r)
 #pragma unroll
-        for (int c = 0; c < 2; ++c) C[r][c] = csz * (EDGE ? csy[r] * (csx[c] * CE[r][c]) : CE[r][c]);
+        for (int c = 0; c < 2; ++c) {
+          uint32_t flip = cneg;
+          if constexpr (EDGE) flip ^= ((csign >> (2 * r + c)) & 1u) << 31;
+          C[r][c] = __hiloint2double((int)((uint32_t)__double2hiint(CE[r][c]) ^ flip), __double2loint(CE[r][c]));
+        }
     };
     // P e at (i, o) between the planes p (the parent) and q: 8 terms in the order z, y, x, the
     // parent first, with the weights of fv_jacobi_prolong_tiled
@@ -187,30 +204,29 @@ struct FvPass {
       return e;
     };
 
-    double OUT[RPW][2];  // the finished plane of the previous step, stored behind its barrier
-    auto store = [&](int p) {
+    // finished plane p, queue slot SO of field S, stored behind the next step's barrier
+    auto store = [&](int p, auto SOC) {
+      constexpr int so = decltype(SOC)::value;
       if (p < z0 || p >= z1) return;
       const PlaneBuf bo = plane_buf(a.out, (size_t)p * planeb, planeb);
 #pragma unroll
       for (int i = 0; i < RPW; ++i) {
-        const bool yown = (own >> (2 * i)) & 3u;
+        const bool pown = (own >> (2 * i)) & 1u;
         if constexpr (RES) {
           // pairs are wholly inside or outside the stored columns
-          buf_store2(OUT[i][0], OUT[i][1], bo, yown ? stb[0] + rowb[i] : 0x80000000u, 0u);
+          buf_store2(U[S][so][i][0], U[S][so][i][1], bo, pown ? colb[0] + rowb[i] : 0x80000000u, 0u);
         } else {
 #pragma unroll
           for (int o = 0; o < 2; ++o)
-            buf_store(OUT[i][o], bo, ((own >> (2 * i + o)) & 1u) ? stb[o] + rowb[i] : 0x80000000u, 0u);
+            buf_store(U[S][so][i][o], bo, ((own >> (2 * i + o)) & 1u) ? colb[o] + rowb[i] : 0x80000000u, 0u);
         }
       }
     };
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) OUT[i][0] = OUT[i][1] = 0.0;
 
     double RA[RPW / 2];  // RES: sums over the children of a plane pair
 #pragma unroll
     for (int i = 0; i < RPW / 2; ++i) RA[i] = 0.0;
-    double sumsq = 0.0;
+    double sumsq[RPW][2] = {};  // of every cell; those that the tile does not own drop out at the end
 
     const int zbeg = z0 - HZ, zend = z1 + HZ;
     int zl = zbeg;
@@ -241,27 +257,28 @@ struct FvPass {
             v = in ? v + e : v;
           }
           U[0][P % 3][i][o] = v;
-          F[P % 6][i][o] = PF[i][o];
+          F[imod(P - 1, 6)][i][o] = PF[i][o];
         }
 #pragma unroll
       for (int i = 0; i < RPW; ++i)
 #pragma unroll
         for (int o = 0; o < 2; ++o) asm volatile("" : "+v"(U[0][P % 3][i][o]));
       __syncthreads();
-      store(zl - 1 - S);
+      store(zl - 1 - S, IC<imod(P - 1 - S, 3)>{});
       if (zl + 1 < zend) {
         if constexpr (IN == kProlong && zpar == 1) cload(((zl + 1) >> 1) + 1);
         load(zl + 1);
       }
-      // (A u) at (i, o) of field j's centre plane
-      auto apply = [&](auto JC, auto QC, int p, int i, int o) -> double {
+      // (A u) at (i, o) of field j's centre plane p; ZF: p lies next to a domain face (the planes
+      // that do take a copy of the code, so that the others' cells stay in one block)
+      auto apply = [&](auto JC, auto QC, auto ZF, double2 em, double2 ep, int p, int i, int o) -> double {
         constexpr int j = decltype(JC)::value, d = decltype(QC)::value;  // plane p = zl - d
         constexpr int c = imod(P - d, 3), lo = imod(P - d - 1, 3), hi = imod(P - d + 1, 3);
         const double ui = U[j][c][i][o];
         double xm = o ? U[j][c][i][0] : from_lane_below(U[j][c][i][1]);
         double xp = o ? from_lane_above(U[j][c][i][0]) : U[j][c][i][1];
-        double ym = i > 0 ? U[j][c][i - 1][o] : sh.e[rb][j][wm][1][o][lane];
-        double yp = i < RPW - 1 ? U[j][c][i + 1][o] : sh.e[rb][j][wp][0][o][lane];
+        double ym = i > 0 ? U[j][c][i - 1][o] : o ? em.y : em.x;
+        double yp = i < RPW - 1 ? U[j][c][i + 1][o] : o ? ep.y : ep.x;
         double zm = U[j][lo][i][o], zp = U[j][hi][i][o];
         if constexpr (EDGE) {
           // a ghost neighbour enters as 2 g - u_i
@@ -270,8 +287,10 @@ struct FvPass {
           if (i % 2 == XLO) ym = gy + i == 1 ? 2.0 * ym - ui : ym;
           if (i % 2 == XHI) yp = gy + i == N ? 2.0 * yp - ui : yp;
         }
-        if (p == 1) zm = 2.0 * zm - ui;
-        if (p == N) zp = 2.0 * zp - ui;
+        if constexpr (decltype(ZF)::value) {
+          if (p == 1) zm = 2.0 * zm - ui;
+          if (p == N) zp = 2.0 * zp - ui;
+        }
         double s = ui - xm;
         s = s + (ui - xp);
         s = s + (ui - ym);
@@ -284,51 +303,66 @@ struct FvPass {
         constexpr int j = decltype(JC)::value;  // sweep j + 1: field j -> j + 1, plane zl - 1 - j
         constexpr int c = imod(P - 1 - j, 3), fs = imod(P - 1 - j, 6);
         const int p = zl - 1 - j;
-        const bool zin = p >= 1 && p <= N;
+        if (p < 1 || p > N) {
 #pragma unroll
-        for (int i = 0; i < RPW; ++i)
+          for (int i = 0; i < RPW; ++i)
 #pragma unroll
-          for (int o = 0; o < 2; ++o) {
-            const double ui = U[j][c][i][o];
-            double v = ui;
-            if (zin) {
+            for (int o = 0; o < 2; ++o) U[j + 1][c][i][o] = U[j][c][i][o];
+          return;
+        }
+        constexpr bool zero = IN == kZero && j == 0;
+        [[maybe_unused]] double R[RPW][2];
+        double2 em{}, ep{};  // the adjacent row groups' edge rows
+        if constexpr (!zero) {
+          em = sh.e[rb][j][wm][1][lane];
+          ep = sh.e[rb][j][wp][0][lane];
+        }
+        auto cells = [&](auto ZF) {
+#pragma unroll
+          for (int i = 0; i < RPW; ++i)
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+              const double ui = U[j][c][i][o];
               double r;
-              if constexpr (IN == kZero && j == 0) r = F[fs][i][o] - 0.0;
-              else r = F[fs][i][o] - apply(IC<j>{}, IC<1 + j>{}, p, i, o);
-              v = ui + a.coef * r;
-              if constexpr (EDGE) v = ((cell >> (2 * i + o)) & 1u) ? v : ui;
-              if constexpr (NORM && j == 0) {
-                const bool mine = ((own >> (2 * i + o)) & 1u) && p >= z0 && p < z1;
-                const double rr = mine ? r : 0.0;
-                sumsq += rr * rr;
-              }
+              if constexpr (zero) r = F[fs][i][o] - 0.0;
+              else r = F[fs][i][o] - apply(IC<j>{}, IC<1 + j>{}, ZF, em, ep, p, i, o);
+              const double v = ui + a.coef * r;
+              U[j + 1][c][i][o] = EDGE && !((cell >> (2 * i + o)) & 1u) ? ui : v;
+              if constexpr (NORM && j == 0) R[i][o] = r;
             }
-            U[j + 1][c][i][o] = v;
+        };
+        if (!zero && (p == 1 || p == N)) cells(IC<1>{});
+        else cells(IC<0>{});
+        if constexpr (NORM && j == 0) {
+          if (p >= z0 && p < z1) {
+#pragma unroll
+            for (int i = 0; i < RPW; ++i)
+#pragma unroll
+              for (int o = 0; o < 2; ++o) sumsq[i][o] += R[i][o] * R[i][o];
           }
+        }
       };
       sweep(IC<0>{});
       if constexpr (S >= 2) sweep(IC<1>{});
       if constexpr (S >= 3) sweep(IC<2>{});
-      {
-        constexpr int c = imod(P - S, 3);
-#pragma unroll
-        for (int i = 0; i < RPW; ++i)
-#pragma unroll
-          for (int o = 0; o < 2; ++o) OUT[i][o] = U[S][c][i][o];
-      }
       if constexpr (RES) {
         constexpr int fs = imod(P - 1 - S, 6);
         constexpr int qpar = (zpar + 1 + S) & 1;
         const int q = zl - 1 - S;
         if (q >= z0 && q < z1) {
+          const double2 em = sh.e[rb][S][wm][1][lane], ep = sh.e[rb][S][wp][0][lane];
+          auto cells = [&](auto ZF) {
 #pragma unroll
-          for (int i = 0; i < RPW; ++i)
+            for (int i = 0; i < RPW; ++i)
 #pragma unroll
-            for (int o = 0; o < 2; ++o) {
-              const double r = F[fs][i][o] - apply(IC<S>{}, IC<1 + S>{}, q, i, o);
-              if (qpar == 1 && i % 2 == 0 && o == 0) RA[i / 2] = 0.0;
-              RA[i / 2] = RA[i / 2] + r;
-            }
+              for (int o = 0; o < 2; ++o) {
+                const double r = F[fs][i][o] - apply(IC<S>{}, IC<1 + S>{}, ZF, em, ep, q, i, o);
+                if (qpar == 1 && i % 2 == 0 && o == 0) RA[i / 2] = 0.0;
+                RA[i / 2] = RA[i / 2] + r;
+              }
+          };
+          if (q == 1 || q == N) cells(IC<1>{});
+          else cells(IC<0>{});
           if constexpr (qpar == 0) {
             const PlaneBuf bc = plane_buf(a.fc, (size_t)(q >> 1) * cplaneb, cplaneb);
 #pragma unroll
@@ -344,11 +378,8 @@ struct FvPass {
         constexpr int j = decltype(JC)::value;
         if constexpr (IN == kZero && j == 0) return;  // the sweep from zero reads no neighbours
         constexpr int c = imod(P - j, 3);
-#pragma unroll
-        for (int o = 0; o < 2; ++o) {
-          sh.e[wb][j][w][0][o][lane] = U[j][c][0][o];
-          sh.e[wb][j][w][1][o][lane] = U[j][c][RPW - 1][o];
-        }
+        sh.e[wb][j][w][0][lane] = make_double2(U[j][c][0][0], U[j][c][0][1]);
+        sh.e[wb][j][w][1][lane] = make_double2(U[j][c][RPW - 1][0], U[j][c][RPW - 1][1]);
       };
       edges(IC<0>{});
       if constexpr (NL >= 2) edges(IC<1>{});
@@ -365,6 +396,8 @@ struct FvPass {
         }
       }
       ++zl;
+      // the last step stores its own finished plane
+      if (zl == zend) store(zl - 1 - S, IC<imod(P - S, 3)>{});
       return zl < zend;
     };
     auto round = [&]<int... Ps>(std::integer_sequence<int, Ps...>) {
@@ -374,11 +407,15 @@ struct FvPass {
     };
     while (round(std::make_integer_sequence<int, 6>{})) {
     }
-    store(zl - 1 - S);
     if constexpr (NORM) {
+      double sum = 0.0;
 #pragma unroll
-      for (int o2 = 32; o2 >= 1; o2 >>= 1) sumsq += __shfl_xor(sumsq, o2, 64);
-      if ((threadIdx.x & 63) == 0) sh.red[threadIdx.x >> 6] = sumsq;
+      for (int i = 0; i < RPW; ++i)
+#pragma unroll
+        for (int o = 0; o < 2; ++o) sum += ((own >> (2 * i + o)) & 1u) ? sumsq[i][o] : 0.0;
+#pragma unroll
+      for (int o2 = 32; o2 >= 1; o2 >>= 1) sum += __shfl_xor(sum, o2, 64);
+      if ((threadIdx.x & 63) == 0) sh.red[threadIdx.x >> 6] = sum;
       __syncthreads();
       if (threadIdx.x == 0) {
         double tot = 0.0;

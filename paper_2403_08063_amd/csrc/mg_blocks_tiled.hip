@@ -19,7 +19,7 @@
 // Every cell takes the operations of the single sweep in its order: results are bitwise equal.
 //
 // Measured, one pass (two sweeps) against single sweeps with the fill between them: 1.41 ms against
-// 1.44 + 0.17 + 1.44 at 128^3 cells per block, 0.22 against 0.18 + 0.04 + 0.18 at 64^3; the ghost
+// 1.44 + 0.17 + 1.44 at 128^3 cells per block, 0.19 against 0.18 + 0.04 + 0.18 at 64^3; the ghost
 // planes before it take 0.34 and 0.09 ms.  A V(3,3) cycle at 128^3 with the norm riding on its
 // first pass: 16.8 -> 11.9 ms.  12 waves of 2 rows (142-162 registers, 3 waves per SIMD); 8 x 3
 // takes 0.4 % longer per solve, 12 x 3, 16 x 2 and 8 x 4 spill.  Blocks of less than 64 cells a
@@ -62,7 +62,7 @@ struct PairPass {
   static constexpr int H = 2, TY = BY - 2 * H;
 
   struct Shared {
-    double e[2][2][VW][2][2][LW];  // [parity][field][row group][first, last row][column][lane]
+    double2 e[2][2][VW][2][LW];  // [parity][field][row group][first, last row][lane]: two columns
     double red[W];
   };
 
@@ -180,17 +180,18 @@ struct PairPass {
       store(zl - 3);
       if (zl + 1 < zend) load(zl + 1);
 
-      // residual at (i, o) of field j's centre plane, phase c (lo, hi: its z-neighbours)
-      auto resid = [&](auto JC, auto CC, auto LC, auto HC, const double (&X)[RPW], double fv, int p, int i,
-                       int o) -> double {
+      // residual at (i, o) of field j's centre plane, phase c (lo, hi: its z-neighbours; em, ep: the
+      // adjacent row groups' edge rows)
+      auto resid = [&](auto JC, auto CC, auto LC, auto HC, const double (&X)[RPW], double2 em, double2 ep,
+                       double fv, int p, int i, int o) -> double {
         constexpr int j = decltype(JC)::value, c = decltype(CC)::value, lo = decltype(LC)::value,
                       hi = decltype(HC)::value;
         const double ui = U[j][c][i][o];
         const double below = from_lane_below(U[j][c][i][1]), above = from_lane_above(U[j][c][i][0]);
         double xm = o ? U[j][c][i][0] : first ? X[i] : below;
         double xp = o ? (last ? X[i] : above) : U[j][c][i][1];
-        double ym = i > 0 ? U[j][c][i - 1][o] : sh.e[rb][j][wm][1][o][lane];
-        double yp = i < RPW - 1 ? U[j][c][i + 1][o] : sh.e[rb][j][wp][0][o][lane];
+        double ym = i > 0 ? U[j][c][i - 1][o] : (o ? em.y : em.x);
+        double yp = i < RPW - 1 ? U[j][c][i + 1][o] : (o ? ep.y : ep.x);
         double zm = U[j][lo][i][o], zp = U[j][hi][i][o];
         if constexpr (COARSE) {
           // a domain-boundary ghost holds the face value: it enters as 2 g - u_i
@@ -212,12 +213,13 @@ struct PairPass {
       {
         const int p = zl - 1;
         const bool zghost = p < 1 || p > B;
+        const double2 em = sh.e[rb][0][wm][1][lane], ep = sh.e[rb][0][wp][0][lane];
 #pragma unroll
         for (int i = 0; i < RPW; ++i)
 #pragma unroll
           for (int o = 0; o < 2; ++o) {
             const double fv = F[f1][i][o];
-            const double r = resid(IC<0>{}, IC<s1>{}, IC<s2>{}, IC<s0>{}, X0, fv, p, i, o);
+            const double r = resid(IC<0>{}, IC<s1>{}, IC<s2>{}, IC<s0>{}, X0, em, ep, fv, p, i, o);
             const double v = U[0][s1][i][o] + coef * r;
             U[1][s1][i][o] = zghost || ((ghost >> i) & 1u) ? fv : v;
             if constexpr (NORM) {
@@ -229,23 +231,21 @@ struct PairPass {
       }
       {
         const int p = zl - 2;
+        const double2 em = sh.e[rb][1][wm][1][lane], ep = sh.e[rb][1][wp][0][lane];
 #pragma unroll
         for (int i = 0; i < RPW; ++i)
 #pragma unroll
           for (int o = 0; o < 2; ++o) {
             // field 1: planes zl-2 (centre), zl-3 and zl-1
-            const double r = resid(IC<1>{}, IC<s2>{}, IC<s0>{}, IC<s1>{}, X1, F[f2][i][o], p, i, o);
+            const double r = resid(IC<1>{}, IC<s2>{}, IC<s0>{}, IC<s1>{}, X1, em, ep, F[f2][i][o], p, i, o);
             OUT[i][o] = U[1][s2][i][o] + coef * r;
           }
       }
       // edge rows of the next step's centres: plane zl of field 0, zl - 1 of field 1
-#pragma unroll
-      for (int o = 0; o < 2; ++o) {
-        sh.e[wb][0][w][0][o][lane] = U[0][s0][0][o];
-        sh.e[wb][0][w][1][o][lane] = U[0][s0][RPW - 1][o];
-        sh.e[wb][1][w][0][o][lane] = U[1][s1][0][o];
-        sh.e[wb][1][w][1][o][lane] = U[1][s1][RPW - 1][o];
-      }
+      sh.e[wb][0][w][0][lane] = make_double2(U[0][s0][0][0], U[0][s0][0][1]);
+      sh.e[wb][0][w][1][lane] = make_double2(U[0][s0][RPW - 1][0], U[0][s0][RPW - 1][1]);
+      sh.e[wb][1][w][0][lane] = make_double2(U[1][s1][0][0], U[1][s1][0][1]);
+      sh.e[wb][1][w][1][lane] = make_double2(U[1][s1][RPW - 1][0], U[1][s1][RPW - 1][1]);
       ++zl;
       return zl < zend;
     };

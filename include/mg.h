@@ -151,29 +151,31 @@ mg_status mg_coarsest_solve(mg_ctx* ctx, const double* f, double* u);
 mg_status mg_residual_norm2(mg_ctx* ctx, const double* f, const double* u, double* norm2);
 
 /* Kernel-fusion flags (diagnostics and tests), a bitwise OR of:
- *  MG_FUSE_BLOCKED  temporally blocked out-of-place smoother and single-pass streaming
- *                   residual / restriction / norm / refinement kernels on large 3D levels
- *                   (otherwise the per-colour smoother and one launch per step);
+ *  MG_FUSE_BLOCKED  out-of-place smoothers with two sweeps per pass: marching strips on 2D levels,
+ *                   LDS boxes on 3D levels of up to 65 nodes a side, marching tiles on larger
+ *                   ones, and there single-pass streaming residual / restriction / norm /
+ *                   refinement kernels (otherwise the per-colour smoother and one launch per
+ *                   step);
  *  MG_FUSE_PROLONG  the coarse-grid correction u += P e applied inside the first
- *                   post-smoothing pass (blocked levels: FP32 passes and the FP64
- *                   constant-coefficient pass) or, on levels served
- *                   by the per-colour kernels, inside the first colour-0 half-sweep, instead
- *                   of a separate pass;
+ *                   post-smoothing pass (FP64 variable-coefficient tiles: from two sweeps on) or,
+ *                   without MG_FUSE_BLOCKED, inside the first colour-0 half-sweep, instead of a
+ *                   separate pass;
  *  MG_FUSE_ZERO     a zero initial guess read as 0 by the first pre-smoothing pass (or the
  *                   first colour-0 half-sweep, which also writes the other colour's zeros)
  *                   instead of being written first;
  *  MG_FUSE_TAIL     all levels with at most 4096 interior nodes in one launch;
- *  MG_FUSE_RESTRICT on such large 3D levels, the residual and its full-weighting restriction
- *                   computed inside the pre-smoothing pass (constant coefficient, FP32
- *                   and FP64) instead of a separate pass;
+ *  MG_FUSE_RESTRICT the residual and its full-weighting restriction computed inside the
+ *                   pre-smoothing pass (with MG_FUSE_BLOCKED: strips, boxes, and tiles with a
+ *                   constant coefficient) instead of a separate pass;
  *  MG_FUSE_REFINE   in an MG_F32_IR solve with a large 3D finest level, a constant
  *                   coefficient and nu2 = 2 (with MG_FUSE_PROLONG), the refinement step
  *                   (u += s e, the FP64 residual, its norm and the next FP32 right-hand side)
  *                   performed inside the FP32 cycle's last post-smoothing pass instead of a
  *                   separate pass, so the correction is never stored.
  * Default MG_FUSE_ALL.  Clearing MG_FUSE_PROLONG, MG_FUSE_ZERO, MG_FUSE_TAIL or
- * MG_FUSE_RESTRICT leaves every result bitwise unchanged; without MG_FUSE_BLOCKED smoothing results are unchanged but
- * residual sums are accumulated in another order; MG_FUSE_REFINE leaves the iterate bitwise
+ * MG_FUSE_RESTRICT leaves every result bitwise unchanged; without MG_FUSE_BLOCKED smoothing
+ * results are unchanged but residual norms, and on 3D levels of more than 65 nodes a side the
+ * restriction, are summed in another order; MG_FUSE_REFINE leaves the iterate bitwise
  * unchanged and sums the residual norm in another order.  EINVAL for bits outside
  * MG_FUSE_ALL. */
 enum {

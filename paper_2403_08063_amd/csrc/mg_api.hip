@@ -52,9 +52,11 @@ struct mg_ctx {
   bool coeffs = false;
   int fuse = MG_FUSE_ALL;  // kernel-fusion flags (mg_set_fusion)
   int tail_first = -1;  // first level handled by the one-launch coarse tail (-1: none)
-  // norm read-back without draining the stream: a pinned host word and an event after the
-  // copy (nullptr: synchronous reads only)
+  // norm read-back without draining the stream: pinned host memory (host_norm_alloc) and an event
+  // after the norm (nullptr: synchronous reads only).  FP64 norms are written there by the kernels,
+  // hcount partial sums or a finished one (0).
   double* hnorm = nullptr;
+  int hcount = 0;
   hipEvent_t ev = nullptr;
   char err[512] = "no error";
   ~mg_ctx()
@@ -239,6 +241,7 @@ T* smooth(mg_ctx* c, int l, T* u, T* t, const T* f, const T* k, int sweeps, bool
   const Level& L = c->lv[l];
   const int dim = c->g.dim;
   const bool tiled = use_tiled(c, l), strips = use_strips(c), cube = use_cube(c, l);
+  const bool direct = norm && norm == c->hnorm;  // the host adds the partial sums
   // the blocked 3D pass that takes the correction is the first one: two sweeps unless only one
   // is asked for (FP64 passes fuse the correction into 2-sweep passes only)
   const bool pair = sweeps >= 2 && mgk::rbgs_tiled_max_sweeps(k != nullptr, sizeof(T)) == 2;
@@ -268,8 +271,9 @@ T* smooth(mg_ctx* c, int l, T* u, T* t, const T* f, const T* k, int sweeps, bool
       // fc, norm: taken by the last pass
       T* rfc = left == sw ? fc : nullptr;
       if (strips)
-        mgk::rbgs_strips<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, rfc, c->partial,
-                            left == sw ? norm : nullptr);
+        mgk::rbgs_strips<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, rfc,
+                            direct ? c->hnorm + mgk::kNormHead : c->partial, left == sw ? norm : nullptr,
+                            direct ? &c->hcount : nullptr);
       else if (cube)
         mgk::rbgs_cube<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, rfc);
       else
@@ -368,14 +372,43 @@ double ir_scale(const mg_ctx* c, double rn)
   return std::ldexp(1.0, (int)std::lround(std::log2(rms)));
 }
 
-// ||f - A u||^2 (mode 0) or of the full right-hand side (mode 1) into c->scal[slot].
-void norm2(mg_ctx* c, const double* f, const double* u, int mode, int slot)
+// ||f - A u||^2 (mode 0) or of the full right-hand side (mode 1) into out[0].
+void norm2(mg_ctx* c, const double* f, const double* u, int mode, double* out)
 {
   const Level& L0 = c->lv[0];
   if (use_tiled(c, 0))
-    mgk::resid_norm2_tiled(c->s, L0.n, L0.h, L0.k, f, u, mode, c->partial, c->scal + slot);
+    mgk::resid_norm2_tiled(c->s, L0.n, L0.h, L0.k, f, u, mode, c->partial, out);
   else
-    mgk::resid_norm2(c->s, c->g.dim, L0.n, L0.h, L0.k, f, u, mode, c->partial, c->scal + slot);
+    mgk::resid_norm2(c->s, c->g.dim, L0.n, L0.h, L0.k, f, u, mode, c->partial, out);
+}
+
+// Where the kernels of an FP64 solve put norms, and their read-back.
+double* norm_place(mg_ctx* c)
+{
+  c->hcount = 0;
+  return c->hnorm ? c->hnorm : c->scal;
+}
+
+mg_status read_norms(mg_ctx* c, double* host, int count = 1)
+{
+  if (!c->hnorm) return read_scalar(c, c->scal, host, count);
+  if (mg_status st = hip_check(c, hipStreamSynchronize(c->s), "stream synchronisation")) return st;
+  host[0] = mgk::host_norm(c->hnorm, c->hcount);
+  for (int i = 1; i < count; ++i) host[i] = c->hnorm[i];
+  return MG_OK;
+}
+
+// In two halves, the second waiting for the work enqueued before the first only (hnorm, ev).
+mg_status read_norm_start(mg_ctx* c)
+{
+  return hip_check(c, hipEventRecord(c->ev, c->s), "recording the norm event");
+}
+
+mg_status read_norm_finish(mg_ctx* c, double* host)
+{
+  if (mg_status st = hip_check(c, hipEventSynchronize(c->ev), "waiting for a norm")) return st;
+  *host = mgk::host_norm(c->hnorm, c->hcount);
+  return MG_OK;
 }
 
 // One outer step of iterative refinement (FP64 u, f) with the per-step kernels:
@@ -392,7 +425,7 @@ mg_status ir_step(mg_ctx* c, const double* f, double* u, double scale)
 }
 
 // The two halves of an FP64 cycle on the caller's (f, u).  The way up leaves the result in u
-// and, with norm, the squared residual norm of the result in scal[0].
+// and, with norm, the squared residual norm of the result at norm_place.
 double* f64_down(mg_ctx* c, const double* f, double* u, double** ec)
 {
   return cycle_down<double>(c, 0, u, c->lv[0].t, f, false, ec);
@@ -403,9 +436,9 @@ mg_status f64_up(mg_ctx* c, const double* f, double* u, double* cur, const doubl
   Level& L0 = c->lv[0];
   const bool ride = norm && fuses_norm(c);
   double* r = smooth<double>(c, 0, cur, cur == u ? L0.t : u, f, L0.k, c->g.nu2, false, ec, nullptr,
-                             ride ? c->scal : nullptr);
+                             ride ? norm_place(c) : nullptr);
   if (r != u) mgk::copy<double>(c->s, L0.N, r, u);
-  if (norm && !ride) norm2(c, f, u, 0, 0);
+  if (norm && !ride) norm2(c, f, u, 0, norm_place(c));
   return launch_check(c, "V-cycle");
 }
 
@@ -634,12 +667,12 @@ mg_status solve_ir_plain(mg_ctx* c, const double* f, double* u, double tol, doub
   int k = 0;
   mg_status st = MG_OK;
   if (std::isfinite(rel) && rel > tol)
-    mgk::ir_residual(c->s, dim, L0.n, L0.h, L0.k, f, u, 1.0 / scale, L0.f32, c->partial, c->scal);
+    mgk::ir_residual(c->s, dim, L0.n, L0.h, L0.k, f, u, 1.0 / scale, L0.f32, c->partial, norm_place(c));
   while (std::isfinite(rel) && rel > tol && k < c->g.max_cycles) {
     if (!e) e = cycle<float>(c, 0, L0.u32, L0.t32, L0.f32, true);
     const double next = ir_scale(c, rn);
     mgk::ir_update(c->s, dim, L0.n, scale, e, u);
-    mgk::ir_residual(c->s, dim, L0.n, L0.h, L0.k, f, u, 1.0 / next, L0.f32, c->partial, c->scal);
+    mgk::ir_residual(c->s, dim, L0.n, L0.h, L0.k, f, u, 1.0 / next, L0.f32, c->partial, norm_place(c));
     e = nullptr;
     scale = next;
     ++k;
@@ -648,14 +681,14 @@ mg_status solve_ir_plain(mg_ctx* c, const double* f, double* u, double tol, doub
     const double predicted = k < c->g.max_cycles ? rel * rho : 0.0;
     rel_prev = rel;
     if (overlap) {
-      if ((st = read_scalar_start(c, c->scal))) break;
+      if ((st = read_norm_start(c))) break;
       if (predicted > 4.0 * tol) {
         e = cycle<float>(c, 0, L0.u32, L0.t32, L0.f32, true);
         if ((st = launch_check(c, "V-cycle"))) break;
       }
-      st = read_scalar_finish(c, &rn2);
+      st = read_norm_finish(c, &rn2);
     } else {
-      st = read_scalar(c, c->scal, &rn2);
+      st = read_norms(c, &rn2);
     }
     if (st) break;
     rn = std::sqrt(rn2);
@@ -679,7 +712,7 @@ mg_status solve_impl(mg_ctx* c, const double* f, double* u, double tol, int* cyc
     return solve_ir_streamed(c, f, u, tol, 0.0, cycles, relres);
   double two[2] = {0, 0};  // squared norms of the residual and of the full right-hand side
   if (ir && use_tiled(c, 0)) {
-    norm2(c, f, u, 1, 1);
+    norm2(c, f, u, 1, c->scal + 1);
     if (mg_status st = launch_check(c, "norm")) return st;
     if (mg_status st = read_scalar(c, c->scal + 1, two + 1)) return st;
     double bn = std::sqrt(two[1]);
@@ -688,13 +721,13 @@ mg_status solve_impl(mg_ctx* c, const double* f, double* u, double tol, int* cyc
   }
   if (use_tiled(c, 0) && !c->g.variable) {
     // both in one pass (each in its own pass's order)
-    mgk::resid_norm2_both_tiled(c->s, L0.n, L0.h, f, u, c->partial, c->partial_b, c->scal);
+    mgk::resid_norm2_both_tiled(c->s, L0.n, L0.h, f, u, c->partial, c->partial_b, norm_place(c));
   } else {
-    norm2(c, f, u, 1, 1);
-    norm2(c, f, u, 0, 0);
+    norm2(c, f, u, 1, norm_place(c) + 1);
+    norm2(c, f, u, 0, norm_place(c));
   }
   if (mg_status st = launch_check(c, "norm")) return st;
-  if (mg_status st = read_scalar(c, c->scal, two, 2)) return st;
+  if (mg_status st = read_norms(c, two, 2)) return st;
   double bn = std::sqrt(two[1]);
   if (!(bn > 0)) bn = 1.0;
   if (ir) return solve_ir_plain(c, f, u, tol, bn, std::sqrt(two[0]), cycles, relres);
@@ -715,12 +748,12 @@ mg_status solve_impl(mg_ctx* c, const double* f, double* u, double tol, int* cyc
     const double predicted = k < c->g.max_cycles ? rel * rho : 0.0;
     rel_prev = rel;
     if (overlap && predicted > 4.0 * tol) {
-      if ((st = read_scalar_start(c, c->scal))) break;
+      if ((st = read_norm_start(c))) break;
       down = f64_down(c, f, u, &ec);
       if ((st = launch_check(c, "V-cycle"))) break;
-      st = read_scalar_finish(c, &rn2);
+      st = read_norm_finish(c, &rn2);
     } else {
-      st = read_scalar(c, c->scal, &rn2);
+      st = read_norms(c, &rn2);
     }
     if (st) break;
     rel = std::sqrt(rn2) / bn;
@@ -868,14 +901,11 @@ mg_status mg_setup(const mg_grid* grid, void* workspace, size_t bytes, void* str
   mg_ctx* c = new (std::nothrow) mg_ctx;
   if (!c) return fail(nullptr, MG_ENOMEM, "host allocation of the context failed");
   mg_status st = init_ctx(c, grid, workspace, need, static_cast<hipStream_t>(stream));
-  // one pinned host word for overlapped norm reads; without it the solve reads synchronously
+  // pinned host memory for norms; without it the solve reads them synchronously
   if (!st) {
-    void* hp = nullptr;
-    if (hipHostMalloc(&hp, 64, hipHostMallocDefault) == hipSuccess) {
-      c->hnorm = static_cast<double*>(hp);
-      if (hipEventCreateWithFlags(&c->ev, hipEventDisableTiming) != hipSuccess) c->ev = nullptr;
-    }
-    (void)hipGetLastError();  // a failed pinned allocation only disables the overlap
+    c->hnorm = mgk::host_norm_alloc();
+    if (c->hnorm && hipEventCreateWithFlags(&c->ev, hipEventDisableTiming) != hipSuccess) c->ev = nullptr;
+    (void)hipGetLastError();  // a failed event only disables the overlap
   }
   if (st) {
     snprintf(g_err, sizeof g_err, "%s", c->err);
@@ -902,8 +932,8 @@ mg_status mg_vcycle(mg_ctx* c, const double* f, double* u)
   if (use_blocked(c, 0)) mgk::copy_boundary(c->s, c->g.dim, L0.n, u, L0.t);
   if (c->g.precision == MG_F32_IR) {
     double rn2 = 0;
-    norm2(c, f, u, 0, 0);
-    if (mg_status st = read_scalar(c, c->scal, &rn2)) return st;
+    norm2(c, f, u, 0, norm_place(c));
+    if (mg_status st = read_norms(c, &rn2)) return st;
     return ir_step(c, f, u, ir_scale(c, std::sqrt(rn2)));
   }
   double* ec = nullptr;
@@ -1005,9 +1035,9 @@ mg_status mg_residual_norm2(mg_ctx* c, const double* f, const double* u, double*
 {
   if (mg_status st = check_ready(c)) return st;
   if (!f || !u || !out) return fail(c, MG_EINVAL, "NULL argument");
-  norm2(c, f, u, 0, 0);
+  norm2(c, f, u, 0, norm_place(c));
   if (mg_status st = launch_check(c, "norm")) return st;
-  return read_scalar(c, c->scal, out);
+  return read_norms(c, out);
 }
 
 mg_status mg_solve_noalloc(const mg_grid* grid, const double* k, const double* f, double* u,

@@ -183,7 +183,12 @@ struct mgblk_ctx {
   std::vector<double> hhost;
   C2FWeights w{};
   bool coarse4 = false;   // k_blk_coarse4 may use the LDS it needs
+  double* hnorm = nullptr;  // pinned memory that norms are written to (host_norm_alloc)
   char err[512] = "no error";
+  ~mgblk_ctx()
+  {
+    if (hnorm) (void)hipHostFree(hnorm);
+  }
 };
 
 namespace {
@@ -1278,20 +1283,25 @@ double* vcycle_rec(mgblk_ctx* c, int l, const double* f, double* x, double* y, b
   return sweeps(c, l, f, cur, oth, c->g.nu2);
 }
 
+double* norm_place(mgblk_ctx* c) { return c->hnorm ? c->hnorm : c->scal; }
+
 mg_status read_norm(mgblk_ctx* c, double* out)
 {
   if (mg_status st = blk_hip(c, hipGetLastError(), "norm")) return st;
-  if (mg_status st = blk_hip(c, hipMemcpyAsync(out, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s),
-                             "reading the norm"))
-    return st;
-  return blk_hip(c, hipStreamSynchronize(c->s), "stream synchronisation");
+  if (!c->hnorm)
+    if (mg_status st = blk_hip(c, hipMemcpyAsync(out, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s),
+                               "reading the norm"))
+      return st;
+  if (mg_status st = blk_hip(c, hipStreamSynchronize(c->s), "stream synchronisation")) return st;
+  if (c->hnorm) *out = mgk::host_norm(c->hnorm, 0);
+  return MG_OK;
 }
 
 mg_status norm2(mgblk_ctx* c, const double* f, double* u, double* out)
 {
   fill(c, 0, u);
   k_blk_norm2<<<kBlkNormBlocks, 256, 0, c->s>>>(c->lv[0].B, c->faces, c->lv[0].hs, f, u, c->partial);
-  k_blk_sum<<<1, 256, 0, c->s>>>(c->partial, kBlkNormBlocks, c->scal);
+  k_blk_sum<<<1, 256, 0, c->s>>>(c->partial, kBlkNormBlocks, norm_place(c));
   return read_norm(c, out);
 }
 
@@ -1368,6 +1378,7 @@ mg_status mgblk_setup(const mgblk_grid* grid, void* workspace, size_t bytes, voi
     delete c;
     return st;
   }
+  c->hnorm = mgk::host_norm_alloc();
   *out = c;
   return MG_OK;
 }
@@ -1484,7 +1495,7 @@ mg_status mgblk_mg_solve(mgblk_ctx* c, const double* f, double* u, double tol, i
   for (;; ++k) {
     const bool last = k == c->g.max_cycles;
     if (ride && !last) {
-      pair_sweep(c, 0, f, u, c->lv[0].t, false, c->scal);
+      pair_sweep(c, 0, f, u, c->lv[0].t, false, norm_place(c));
       st = read_norm(c, &rn2);
     } else {
       st = norm2(c, f, u, &rn2);

@@ -49,7 +49,8 @@ struct mgfv_ctx {
   double* partial = nullptr;
   double* scal = nullptr;
   int tail = -1;           // first level of the one-launch tail (-1: none)
-  double* hnorm = nullptr; // pinned host word and event of the norm read-back
+  double* hnorm = nullptr; // pinned memory (host_norm_alloc) and event of the norm read-back
+  int hcount = 0;          // partial sums there, 0: a finished norm
   hipEvent_t ev = nullptr;
   char err[512] = "no error";
   ~mgfv_ctx()
@@ -515,6 +516,7 @@ constexpr int kFvBlockedMin = 16;
 double* smooth(mgfv_ctx* c, int l, double* u, double* t, const double* f, int sweeps, bool zero = false,
                const double* ec = nullptr, double* fc = nullptr, double* norm2 = nullptr)
 {
+  const bool direct = norm2 && norm2 == c->hnorm;  // the host adds the partial sums
   const FvLevel& L = c->lv[l];
   const double ih2 = 1.0 / (L.h * L.h);
   const bool blocked = L.N >= kFvBlockedMin, tiled = mgk::fv_tiled_supported(L.N);
@@ -531,7 +533,8 @@ double* smooth(mgfv_ctx* c, int l, double* u, double* t, const double* f, int sw
     const bool last = left == n;
     if (n > 1) {
       mgk::fv_sweeps(c->s, L.N, L.h, c->g.omega, n, zero ? nullptr : cur, f, ec, oth,
-                     last ? fc : nullptr, c->partial, last && fc ? norm2 : nullptr);
+                     last ? fc : nullptr, direct ? c->hnorm + mgk::kNormHead : c->partial,
+                     last && fc ? norm2 : nullptr, direct ? &c->hcount : nullptr);
       restricted = last && fc;
     } else if (ec) {
       mgk::fv_jacobi_prolong_tiled(c->s, L.N, L.h, c->g.omega, f, cur, ec, oth, c->partial);
@@ -593,15 +596,23 @@ void prolong(mgfv_ctx* c, int l, const double* ec, double* u)
   smooth(c, l, u, nullptr, nullptr, 0, false, ec);
 }
 
+// Where norms are put (see host_norm_alloc).
+double* norm_place(mgfv_ctx* c)
+{
+  c->hcount = 0;
+  return c->hnorm ? c->hnorm : c->scal;
+}
+
 void norm2(mgfv_ctx* c, const double* f, const double* u)
 {
   const FvLevel& L = c->lv[0];
+  double* out = norm_place(c);
   if (mgk::fv_tiled_supported(L.N)) {
-    mgk::fv_norm2_tiled(c->s, L.N, L.h, f, u, c->partial, c->scal);
+    mgk::fv_norm2_tiled(c->s, L.N, L.h, f, u, c->partial, out);
     return;
   }
   k_fv_norm2_blocks<<<kFvNormBlocks, 256, 0, c->s>>>(L.N, 1.0 / (L.h * L.h), f, u, c->partial);
-  k_fv_sum<<<1, 256, 0, c->s>>>(c->partial, kFvNormBlocks, c->scal);
+  k_fv_sum<<<1, 256, 0, c->s>>>(c->partial, kFvNormBlocks, out);
 }
 
 // One V-cycle on level l from a zero correction in the level's own arrays; returns the buffer
@@ -642,10 +653,13 @@ void top_up(mgfv_ctx* c, const double* f, double* u, double* cur, const double* 
 
 mg_status read_norm(mgfv_ctx* c, double* out)
 {
-  if (mg_status st = fv_hip(c, hipMemcpyAsync(out, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s),
-                            "reading the norm"))
-    return st;
-  return fv_hip(c, hipStreamSynchronize(c->s), "stream synchronisation");
+  if (!c->hnorm)
+    if (mg_status st = fv_hip(c, hipMemcpyAsync(out, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s),
+                              "reading the norm"))
+      return st;
+  if (mg_status st = fv_hip(c, hipStreamSynchronize(c->s), "stream synchronisation")) return st;
+  if (c->hnorm) *out = mgk::host_norm(c->hnorm, c->hcount);
+  return MG_OK;
 }
 
 mg_status level_args(mgfv_ctx* c, int level, bool coarser)
@@ -708,12 +722,9 @@ mg_status mgfv_setup(const mgfv_grid* grid, void* workspace, size_t bytes, void*
   mgk::fill<double>(c->s, need / sizeof(double), 0.0, static_cast<double*>(workspace));
   for (int l = 1; l < grid->levels; ++l)
     if (c->lv[l].N == kFvTailN) c->tail = l;
-  // one pinned word for norm reads that leave the stream running; without it they wait
-  void* hp = nullptr;
-  if (hipHostMalloc(&hp, 64, hipHostMallocDefault) == hipSuccess) {
-    c->hnorm = static_cast<double*>(hp);
-    if (hipEventCreateWithFlags(&c->ev, hipEventDisableTiming) != hipSuccess) c->ev = nullptr;
-  }
+  // pinned memory for norm reads that leave the stream running; without it they wait
+  c->hnorm = mgk::host_norm_alloc();
+  if (c->hnorm && hipEventCreateWithFlags(&c->ev, hipEventDisableTiming) != hipSuccess) c->ev = nullptr;
   (void)hipGetLastError();
   if (mg_status st = fv_launch_check(c, "setup")) {
     snprintf(g_fv_err, sizeof g_fv_err, "%s", c->err);
@@ -813,16 +824,13 @@ mg_status mgfv_solve(mgfv_ctx* c, const double* f, double* u, double tol, int* c
     for (;; ++k) {
       const bool more = k < c->g.max_cycles;
       double *cur = nullptr, *ec = nullptr;
-      if (more) cur = top_down(c, f, u, c->scal);
+      if (more) cur = top_down(c, f, u, norm_place(c));
       else norm2(c, f, u);
-      if ((st = fv_hip(c, hipMemcpyAsync(c->hnorm, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s),
-                       "reading the norm")))
-        break;
       if ((st = fv_hip(c, hipEventRecord(c->ev, c->s), "recording the norm event"))) break;
       if (more) ec = coarse_cycle(c, 1);
       if ((st = fv_launch_check(c, "V-cycle"))) break;
       if ((st = fv_hip(c, hipEventSynchronize(c->ev), "waiting for the norm"))) break;
-      rn = std::sqrt(*c->hnorm);
+      rn = std::sqrt(mgk::host_norm(c->hnorm, c->hcount));
       if (!more || !std::isfinite(rn) || rn <= tol) break;
       top_up(c, f, u, cur, ec);
     }

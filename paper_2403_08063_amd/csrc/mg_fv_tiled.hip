@@ -476,7 +476,8 @@ int resident(Kernel kernel, int block)
 
 template <int S, int IN, bool RES, bool NORM>
 void launch(hipStream_t s, int N, double h, double omega, const double* u, const double* f,
-            const double* ec, double* out, double* fc, double* partial, double* norm2)
+            const double* ec, double* out, double* fc, double* partial, double* norm2,
+            int* count)
 {
   constexpr int W = MG_FVS_W, RPW = MG_FVS_RPW;
   using C = FvPass<S, IN, RES, NORM, W, RPW>;
@@ -499,34 +500,37 @@ void launch(hipStream_t s, int N, double h, double omega, const double* u, const
   }
   const int blocks = per * ((N + a.zlen - 1) / a.zlen);
   kern<<<blocks, 64 * W, 0, s>>>(a);
-  if (NORM) k_fv_sum_partials<<<1, 256, 0, s>>>(partial, blocks, norm2);
+  if (NORM && count) *count = blocks;
+  else if (NORM) k_fv_sum_partials<<<1, 256, 0, s>>>(partial, blocks, norm2);
 }
 
 template <int S>
 void launch_s(hipStream_t s, int N, double h, double omega, const double* u, const double* f,
-              const double* ec, double* out, double* fc, double* partial, double* norm2)
+              const double* ec, double* out, double* fc, double* partial, double* norm2,
+            int* count)
 {
-  if (ec) launch<S, kProlong, false, false>(s, N, h, omega, u, f, ec, out, fc, partial, norm2);
-  else if (!u && fc) launch<S, kZero, true, false>(s, N, h, omega, u, f, ec, out, fc, partial, norm2);
-  else if (!u) launch<S, kZero, false, false>(s, N, h, omega, u, f, ec, out, fc, partial, norm2);
-  else if (fc && norm2) launch<S, kRead, true, true>(s, N, h, omega, u, f, ec, out, fc, partial, norm2);
-  else if (fc) launch<S, kRead, true, false>(s, N, h, omega, u, f, ec, out, fc, partial, norm2);
-  else launch<S, kRead, false, false>(s, N, h, omega, u, f, ec, out, fc, partial, norm2);
+  if (ec) launch<S, kProlong, false, false>(s, N, h, omega, u, f, ec, out, fc, partial, norm2, count);
+  else if (!u && fc) launch<S, kZero, true, false>(s, N, h, omega, u, f, ec, out, fc, partial, norm2, count);
+  else if (!u) launch<S, kZero, false, false>(s, N, h, omega, u, f, ec, out, fc, partial, norm2, count);
+  else if (fc && norm2) launch<S, kRead, true, true>(s, N, h, omega, u, f, ec, out, fc, partial, norm2, count);
+  else if (fc) launch<S, kRead, true, false>(s, N, h, omega, u, f, ec, out, fc, partial, norm2, count);
+  else launch<S, kRead, false, false>(s, N, h, omega, u, f, ec, out, fc, partial, norm2, count);
 }
 
 }  // namespace
 
 void fv_sweeps(hipStream_t s, int N, double h, double omega, int sweeps, const double* u,
                const double* f, const double* ec, double* out, double* fc, double* partial,
-               double* norm2)
+               double* norm2, int* count)
 {
   if (fv_cube_supported(N)) {
     const int blocks = fv_cube_sweeps(s, N, h, omega, sweeps, u, f, ec, out, fc, partial, norm2 != nullptr);
-    if (norm2) k_fv_sum_partials<<<1, 256, 0, s>>>(partial, blocks, norm2);
+    if (norm2 && count) *count = blocks;
+    else if (norm2) k_fv_sum_partials<<<1, 256, 0, s>>>(partial, blocks, norm2);
     return;
   }
-  if (sweeps == 3) launch_s<3>(s, N, h, omega, u, f, ec, out, fc, partial, norm2);
-  else launch_s<2>(s, N, h, omega, u, f, ec, out, fc, partial, norm2);
+  if (sweeps == 3) launch_s<3>(s, N, h, omega, u, f, ec, out, fc, partial, norm2, count);
+  else launch_s<2>(s, N, h, omega, u, f, ec, out, fc, partial, norm2, count);
 }
 
 }  // namespace mgk

@@ -68,11 +68,13 @@ void ir_scales_init(hipStream_t s, int n, const double* norm2, double scale0, do
 // The 2D counterpart (mg_smooth_2d.hip): `sweeps` (1 or 2) red-black sweeps in one launch, out of
 // place, from u, from 0 (zero: u is not read) or from u + P ec.  fc: also the restricted residual
 // of the result (interior; not with ec).  norm2 (double; not with fc or zero): also norm2[0] =
-// sum of squares of the result's residual; partial: kStreamPartials doubles.  Boundaries of out
-// and fc are not written.
+// sum of squares of the result's residual; partial: kStreamPartials doubles.  count (with norm2):
+// the partial sums are left to the caller, *count of them, and norm2[0] is not written.
+// Boundaries of out and fc are not written.
 template <typename T>
 void rbgs_strips(hipStream_t s, int n, double h, const T* k, const T* f, const T* u, T* out,
-                 int sweeps, bool zero, const T* ec, T* fc, double* partial, double* norm2);
+                 int sweeps, bool zero, const T* ec, T* fc, double* partial, double* norm2,
+                 int* count = nullptr);
 
 // The counterpart for small 3D levels (mg_smooth_cube.hip, up to 65 nodes a side): as rbgs_strips,
 // without the norm.
@@ -202,11 +204,21 @@ void fv_restrict_tiled(hipStream_t s, int N, double h, const double* f, const do
 // of u (nullptr: of an identically zero u, ghost layer included) or, with ec, of u + P ec (ec:
 // coarse cells, ghost layer not read).  fc: also the restricted residual of out (coarse cells
 // only).  norm2 (with u and fc): also norm2[0] = sum over cells of (f - A u)^2, the input's
-// residual; partial: kStreamPartials doubles.  out's ghost layer is not written; a second sweep
+// residual; partial: kStreamPartials doubles; count: as rbgs_strips'.  out's ghost layer is not
+// written; a second sweep
 // reads the ghosts of u, so u and out must hold the same.
 void fv_sweeps(hipStream_t s, int N, double h, double omega, int sweeps, const double* u,
                const double* f, const double* ec, double* out, double* fc, double* partial,
-               double* norm2);
+               double* norm2, int* count = nullptr);
+// Host memory that kernels write squared norms to: pinned, the first kNormHead doubles for finished
+// norms, kStreamPartials behind them for partial sums that the host adds.  A norm read this way
+// costs neither the kernel that adds the partial sums nor a copy, 4 us each between a cycle's
+// launches (2D solve at 129^2: 480 -> 405 us, at 2049^2: 1.25 -> 1.11 ms, FV solve at 64^3: 3.53 -> 3.38 ms).  nullptr if it
+// cannot be allocated: norms then go through device memory.
+constexpr int kNormHead = 8;
+double* host_norm_alloc();
+// the sum of `count` partial sums, or for count 0 the finished norm
+double host_norm(const double* hnorm, int count);
 // The passes of fv_sweeps on small levels (mg_fv_cube.hip; fv_sweeps calls it there): returns the
 // number of partial sums (norm).
 bool fv_cube_supported(int N);

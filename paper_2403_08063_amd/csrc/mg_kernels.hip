@@ -780,4 +780,21 @@ template void fill<float>(hipStream_t, size_t, float, float*);
 template void copy<double>(hipStream_t, size_t, const double*, double*);
 template void copy<float>(hipStream_t, size_t, const float*, float*);
 
+double* host_norm_alloc()
+{
+  void* p = nullptr;
+  const hipError_t e = hipHostMalloc(&p, (kNormHead + kStreamPartials) * sizeof(double), hipHostMallocDefault);
+  (void)hipGetLastError();
+  return e == hipSuccess ? static_cast<double*>(p) : nullptr;
+}
+
+double host_norm(const double* hnorm, int count)
+{
+  if (count == 0) return hnorm[0];
+  const double* p = hnorm + kNormHead;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int i = 0; i < count; ++i) s[i & 3] += p[i];
+  return (s[0] + s[1]) + (s[2] + s[3]);
+}
+
 }  // namespace mgk

@@ -300,7 +300,7 @@ constexpr int kTarget = 2048;
 
 template <typename T, bool VAR, int S, int IN, int OUT>
 void launch(hipStream_t s, int n, double h, const T* k, const T* f, const T* u, T* out, const T* ec,
-            T* fc, double* partial, double* norm2)
+            T* fc, double* partial, double* norm2, int* count)
 {
   using C = Strip<T, VAR, S, IN, OUT>;
   Args2<T> a{u, f, k, ec, out, fc, partial, n, 0, 0, 0, (T)(h * h), (T)(1.0 / (h * h))};
@@ -313,25 +313,26 @@ void launch(hipStream_t s, int n, double h, const T* k, const T* f, const T* u, 
   a.chunks = (m + a.ylen - 1) / a.ylen;
   const int blocks = (a.strips * a.chunks + kWaves - 1) / kWaves;
   k_rbgs_strips<T, VAR, S, IN, OUT><<<blocks, 64 * kWaves, 0, s>>>(a);
-  if (OUT == kOutNorm) k_sum_2d<<<1, 256, 0, s>>>(partial, blocks, norm2);
+  if (OUT == kOutNorm && count) *count = blocks;
+  else if (OUT == kOutNorm) k_sum_2d<<<1, 256, 0, s>>>(partial, blocks, norm2);
 }
 
 template <typename T, bool VAR, int S>
 void launch_s(hipStream_t s, int n, double h, const T* k, const T* f, const T* u, T* out, bool zero,
-              const T* ec, T* fc, double* partial, double* norm2)
+              const T* ec, T* fc, double* partial, double* norm2, int* count)
 {
   if (ec && norm2) {
-    if constexpr (sizeof(T) == 8) launch<T, VAR, S, kInProlong, kOutNorm>(s, n, h, k, f, u, out, ec, fc, partial, norm2);
+    if constexpr (sizeof(T) == 8) launch<T, VAR, S, kInProlong, kOutNorm>(s, n, h, k, f, u, out, ec, fc, partial, norm2, count);
   } else if (norm2) {
-    if constexpr (sizeof(T) == 8) launch<T, VAR, S, kInRead, kOutNorm>(s, n, h, k, f, u, out, ec, fc, partial, norm2);
+    if constexpr (sizeof(T) == 8) launch<T, VAR, S, kInRead, kOutNorm>(s, n, h, k, f, u, out, ec, fc, partial, norm2, count);
   } else if (ec) {
-    launch<T, VAR, S, kInProlong, 0>(s, n, h, k, f, u, out, ec, fc, partial, norm2);
+    launch<T, VAR, S, kInProlong, 0>(s, n, h, k, f, u, out, ec, fc, partial, norm2, count);
   } else if (fc) {
-    if (zero) launch<T, VAR, S, kInZero, kOutRestrict>(s, n, h, k, f, u, out, ec, fc, partial, norm2);
-    else launch<T, VAR, S, kInRead, kOutRestrict>(s, n, h, k, f, u, out, ec, fc, partial, norm2);
+    if (zero) launch<T, VAR, S, kInZero, kOutRestrict>(s, n, h, k, f, u, out, ec, fc, partial, norm2, count);
+    else launch<T, VAR, S, kInRead, kOutRestrict>(s, n, h, k, f, u, out, ec, fc, partial, norm2, count);
   } else {
-    if (zero) launch<T, VAR, S, kInZero, 0>(s, n, h, k, f, u, out, ec, fc, partial, norm2);
-    else launch<T, VAR, S, kInRead, 0>(s, n, h, k, f, u, out, ec, fc, partial, norm2);
+    if (zero) launch<T, VAR, S, kInZero, 0>(s, n, h, k, f, u, out, ec, fc, partial, norm2, count);
+    else launch<T, VAR, S, kInRead, 0>(s, n, h, k, f, u, out, ec, fc, partial, norm2, count);
   }
 }
 
@@ -339,10 +340,10 @@ void launch_s(hipStream_t s, int n, double h, const T* k, const T* f, const T* u
 
 template <typename T>
 void rbgs_strips(hipStream_t s, int n, double h, const T* k, const T* f, const T* u, T* out,
-                 int sweeps, bool zero, const T* ec, T* fc, double* partial, double* norm2)
+                 int sweeps, bool zero, const T* ec, T* fc, double* partial, double* norm2, int* count)
 {
   auto go = [&](auto vc, auto sc) {
-    launch_s<T, decltype(vc)::value, decltype(sc)::value>(s, n, h, k, f, u, out, zero, ec, fc, partial, norm2);
+    launch_s<T, decltype(vc)::value, decltype(sc)::value>(s, n, h, k, f, u, out, zero, ec, fc, partial, norm2, count);
   };
   if (k && sweeps == 2) go(std::true_type{}, IC<2>{});
   else if (k) go(std::true_type{}, IC<1>{});
@@ -351,8 +352,8 @@ void rbgs_strips(hipStream_t s, int n, double h, const T* k, const T* f, const T
 }
 
 template void rbgs_strips<double>(hipStream_t, int, double, const double*, const double*, const double*,
-                                  double*, int, bool, const double*, double*, double*, double*);
+                                  double*, int, bool, const double*, double*, double*, double*, int*);
 template void rbgs_strips<float>(hipStream_t, int, double, const float*, const float*, const float*, float*,
-                                 int, bool, const float*, float*, double*, double*);
+                                 int, bool, const float*, float*, double*, double*, int*);
 
 }  // namespace mgk

@@ -989,9 +989,8 @@ void launch_cfg(hipStream_t s, int n, double h, const T* k, const T* f, const T*
 
 }  // namespace
 
-// The per-colour kernel is faster up to 65^3 (a 3D level that small streams too few
-// planes per workgroup to hide the pipeline's start-up); from 129^3 on, the two launches
-// per level and cycle of the fused kernels beat the ten of the per-colour path.
+// Up to 65^3 a level streams too few planes per workgroup to hide the pipeline's start-up; the
+// LDS boxes of mg_smooth_cube.hip take it.  From 129^3 on boxes would reload too much halo.
 #ifndef MG_TILED_MIN_N
 #define MG_TILED_MIN_N 65
 #endif

@@ -10,9 +10,10 @@
 // fly: the C2F value is the tensor product of three 1D Lagrange weight sets (normal,
 // first and second tangential axis), the bases chosen per cell as the rule prescribes.  The
 // Jacobi kernel runs one thread per inner cell of all blocks, each block with its own h; the
-// Levels of 64 to 128 cells a side take two sweeps per pass (mg_blocks_tiled.hip); the
 // restriction one thread per coarse cell (its 8 children's residuals, mean), the
 // prolongation one thread per fine cell (parent and three face neighbours, weight 1/4 each).
+// Levels of 64 to 128 cells a side take two sweeps, or a sweep and the restriction, per pass
+// (mg_blocks_tiled.hip); a coarsest level of 4 runs its iterations in one launch.
 #include "../../include/mg_blocks.h"
 #include "mg_blocks_layout.h"
 #include "mg_kernels.h"
@@ -1154,9 +1155,9 @@ void copy_boundary(mgblk_ctx* c, int l, const double* src, double* dst)
 }
 
 // Two sweeps in one pass, cur -> oth (blk_pair): cur's interface ghosts are filled, then the first
-// sweep's values at the ghosts are formed in c->g1.  norm: see blk_pair.
+// sweep's values at the ghosts are formed in c->g1.  norm, fc: see blk_pair (fc: one sweep).
 void pair_sweep(mgblk_ctx* c, int l, const double* f, double* cur, double* oth, bool zero,
-                double* norm = nullptr)
+                double* norm = nullptr, double* fc = nullptr)
 {
   const BlkLevel& L = c->lv[l];
   const int B = L.B, t = face_threads(B);
@@ -1168,7 +1169,7 @@ void pair_sweep(mgblk_ctx* c, int l, const double* f, double* cur, double* oth, 
   if (c->g.order == 0) k_blk_fill_planes<0><<<grid, t, 0, c->s>>>(B, c->w, c->faces, list, oth, c->g1);
   else if (c->g.order == 1) k_blk_fill_planes<1><<<grid, t, 0, c->s>>>(B, c->w, c->faces, list, oth, c->g1);
   else k_blk_fill_planes<2><<<grid, t, 0, c->s>>>(B, c->w, c->faces, list, oth, c->g1);
-  mgk::blk_pair(c->s, B, c->g.omega, c->faces, L.hs, f, cur, c->g1, oth, l > 0, zero, c->partial, norm);
+  mgk::blk_pair(c->s, B, c->g.omega, c->faces, L.hs, f, cur, c->g1, oth, fc, l > 0, zero, c->partial, norm);
 }
 
 // `count` sweeps on level l with a fill before each, alternating between cur and oth (which
@@ -1271,13 +1272,21 @@ double* vcycle_rec(mgblk_ctx* c, int l, const double* f, double* x, double* y, b
     }
     return sweeps(c, l, f, x, y, c->g.coarse_iters, zero);
   }
-  double* cur = sweeps(c, l, f, x, y, c->g.nu1 - done, zero);
-  double* oth = cur == x ? y : x;
   BlkLevel& C = c->lv[l + 1];
   // the coarse level starts from a zero correction: read as 0 by its first sweep, or, when
   // its first step is not a sweep, written by the restriction
   const bool czero = (l + 1 == last ? c->g.coarse_iters : c->g.nu1) > 0;
-  restrict_residual(c, l, f, cur, C.f, czero ? nullptr : C.u);
+  // the last sweep of an odd count, which no other shares a pass with, takes the restriction in
+  const int pre = c->g.nu1 - done;
+  const bool fused = mgk::blk_pair_supported(c->lv[l].B) && (pre & 1) && czero;
+  double* cur = sweeps(c, l, f, x, y, fused ? pre - 1 : pre, zero);
+  double* oth = cur == x ? y : x;
+  if (fused) {
+    pair_sweep(c, l, f, cur, oth, zero && pre == 1 && l > 0, nullptr, C.f);
+    std::swap(cur, oth);
+  } else {
+    restrict_residual(c, l, f, cur, C.f, czero ? nullptr : C.u);
+  }
   double* ec = vcycle_rec(c, l + 1, C.f, C.u, C.t, czero);
   prolong_correct(c, l, ec, cur);
   return sweeps(c, l, f, cur, oth, c->g.nu2);

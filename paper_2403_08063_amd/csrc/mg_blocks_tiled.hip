@@ -21,7 +21,10 @@
 // Measured, one pass (two sweeps) against single sweeps with the fill between them: 1.41 ms against
 // 1.44 + 0.17 + 1.44 at 128^3 cells per block, 0.19 against 0.18 + 0.04 + 0.18 at 64^3; the ghost
 // planes before it take 0.34 and 0.09 ms.  A V(3,3) cycle at 128^3 with the norm riding on its
-// first pass: 16.8 -> 11.9 ms.  12 waves of 2 rows (142-162 registers, 3 waves per SIMD); 8 x 3
+// first pass: 16.8 -> 11.9 ms.  The last of an odd number of pre-smoothing sweeps takes the
+// restriction in (kRestrict): 1.51 ms, and 0.38 for its ghost planes, where the sweep, a fill and
+// the restriction took 1.44 + 0.17 + 0.93; the cycle 11.9 -> 11.2 ms.
+// 12 waves of 2 rows (141-168 registers, 3 waves per SIMD); 8 x 3
 // takes 0.4 % longer per solve, 12 x 3, 16 x 2 and 8 x 4 spill.  Blocks of less than 64 cells a
 // side are bound by launches, which this adds to (32^3: 25 us a sweep); more than 128 columns do
 // not fit the lanes of a row.
@@ -51,13 +54,21 @@ struct PairArgs {
   const double* hs;
   const int* faces;
   double* out;
-  double* partial;
+  double* fc;       // kRestrict: coarse right-hand side, (B / 2 + 2)^3 values per block
+  double* partial;  // kNorm
   double omega;
   int B, tiles_y, chunks, zlen, zero;
 };
 
-template <int LW, int W, int RPW, bool COARSE, bool NORM>
+// What a pass is: two sweeps; two sweeps and the squared norm of the input's residual; one sweep
+// and the restricted residual of its result (mean of the 8 children; a lane's columns, its rows and
+// a plane pair are one coarse cell's children).
+enum { kSweeps = 0, kNorm = 1, kRestrict = 2 };
+
+template <int LW, int W, int RPW, bool COARSE, int OUT_>
 struct PairPass {
+  static constexpr bool NORM = OUT_ == kNorm, RES = OUT_ == kRestrict;
+  static_assert(!RES || RPW == 2, "a row group is one coarse row");
   static constexpr int G = 64 / LW, VW = W * G, BY = VW * RPW;
   static constexpr int H = 2, TY = BY - 2 * H;
 
@@ -156,7 +167,8 @@ struct PairPass {
       }
     };
 
-    double sumsq = 0.0;
+    double sumsq = 0.0, RA = 0.0;  // kNorm; kRestrict: sum over the children so far
+    const int Bc = B / 2, mc = Bc + 2;
     const int zend = z1 + H;
     int zl = max(z0 - H, 0);
     load(zl);
@@ -238,8 +250,17 @@ struct PairPass {
           for (int o = 0; o < 2; ++o) {
             // field 1: planes zl-2 (centre), zl-3 and zl-1
             const double r = resid(IC<1>{}, IC<s2>{}, IC<s0>{}, IC<s1>{}, X1, em, ep, F[f2][i][o], p, i, o);
-            OUT[i][o] = U[1][s2][i][o] + coef * r;
+            if constexpr (RES) {
+              RA = i == 0 && o == 0 && (p & 1) ? r : RA + r;
+              OUT[i][o] = U[1][s2][i][o];
+            } else {
+              OUT[i][o] = U[1][s2][i][o] + coef * r;
+            }
           }
+        if constexpr (RES) {
+          if (p >= z0 && p < z1 && !(p & 1) && active && (own & 1u))
+            a.fc[(((size_t)b * mc + (p >> 1)) * mc + ((gy + 1) >> 1)) * mc + ((gx + 1) >> 1)] = 0.125 * RA;
+        }
       }
       // edge rows of the next step's centres: plane zl of field 0, zl - 1 of field 1
       sh.e[wb][0][w][0][lane] = make_double2(U[0][s0][0][0], U[0][s0][0][1]);
@@ -271,10 +292,10 @@ struct PairPass {
   }
 };
 
-template <int LW, int W, int RPW, bool COARSE, bool NORM>
+template <int LW, int W, int RPW, bool COARSE, int OUT_>
 __global__ void __launch_bounds__(64 * W) k_blk_pair(PairArgs a)
 {
-  using C = PairPass<LW, W, RPW, COARSE, NORM>;
+  using C = PairPass<LW, W, RPW, COARSE, OUT_>;
   __shared__ typename C::Shared sh;
   // XCD-aware tile index: workgroup b runs on XCD b % 8, which gets a contiguous tile range
   const int n = blockIdx.x, nb = gridDim.x;
@@ -305,17 +326,17 @@ __global__ void __launch_bounds__(256)
 #define MG_BLKP_RPW 2
 #endif
 
-template <int LW, bool COARSE, bool NORM>
+template <int LW, bool COARSE, int OUT_>
 void launch(hipStream_t s, PairArgs a, double* norm2)
 {
   constexpr int W = MG_BLKP_W, RPW = MG_BLKP_RPW;
-  using C = PairPass<LW, W, RPW, COARSE, NORM>;
+  using C = PairPass<LW, W, RPW, COARSE, OUT_>;
   a.tiles_y = (a.B + C::TY - 1) / C::TY;
   // z-chunks: as many as keep the critical path -- rounds of workgroups, one per compute unit, x
-  // planes per workgroup -- shortest
+  // planes per workgroup -- shortest; of even length (plane pairs)
   const int per = kBlocks * a.tiles_y;
   long long best = -1;
-  for (int zlen = 4; zlen <= a.B; ++zlen) {
+  for (int zlen = 4; zlen <= a.B; zlen += 2) {
     const long long blocks = (long long)per * ((a.B + zlen - 1) / zlen);
     if (blocks > kBlkPartials) continue;
     const long long cost = (blocks + 255) / 256 * (zlen + 2 * C::H);
@@ -326,8 +347,8 @@ void launch(hipStream_t s, PairArgs a, double* norm2)
   }
   a.chunks = (a.B + a.zlen - 1) / a.zlen;
   const int blocks = per * a.chunks;
-  k_blk_pair<LW, W, RPW, COARSE, NORM><<<blocks, 64 * W, 0, s>>>(a);
-  if (NORM) k_blk_pair_sum<<<1, 256, 0, s>>>(a.partial, blocks, norm2);
+  k_blk_pair<LW, W, RPW, COARSE, OUT_><<<blocks, 64 * W, 0, s>>>(a);
+  if (OUT_ == kNorm) k_blk_pair_sum<<<1, 256, 0, s>>>(a.partial, blocks, norm2);
 }
 
 }  // namespace
@@ -335,18 +356,22 @@ void launch(hipStream_t s, PairArgs a, double* norm2)
 bool blk_pair_supported(int B) { return B >= 64 && B <= 128; }
 
 void blk_pair(hipStream_t s, int B, double omega, const int* faces, const double* hs, const double* f,
-              const double* u, const double* g, double* out, bool coarse, bool zero, double* partial,
-              double* norm2)
+              const double* u, const double* g, double* out, double* fc, bool coarse, bool zero,
+              double* partial, double* norm2)
 {
-  const PairArgs a{u, f, g, hs, faces, out, partial, omega, B, 0, 0, B, zero};
+  const PairArgs a{u, f, g, hs, faces, out, fc, partial, omega, B, 0, 0, B, zero};
   if (B == 64) {
-    if (coarse) launch<32, true, false>(s, a, nullptr);
-    else if (norm2) launch<32, false, true>(s, a, norm2);
-    else launch<32, false, false>(s, a, nullptr);
+    if (coarse && fc) launch<32, true, kRestrict>(s, a, nullptr);
+    else if (coarse) launch<32, true, kSweeps>(s, a, nullptr);
+    else if (fc) launch<32, false, kRestrict>(s, a, nullptr);
+    else if (norm2) launch<32, false, kNorm>(s, a, norm2);
+    else launch<32, false, kSweeps>(s, a, nullptr);
   } else {
-    if (coarse) launch<64, true, false>(s, a, nullptr);
-    else if (norm2) launch<64, false, true>(s, a, norm2);
-    else launch<64, false, false>(s, a, nullptr);
+    if (coarse && fc) launch<64, true, kRestrict>(s, a, nullptr);
+    else if (coarse) launch<64, true, kSweeps>(s, a, nullptr);
+    else if (fc) launch<64, false, kRestrict>(s, a, nullptr);
+    else if (norm2) launch<64, false, kNorm>(s, a, norm2);
+    else launch<64, false, kSweeps>(s, a, nullptr);
   }
 }
 

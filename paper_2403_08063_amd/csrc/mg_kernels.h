@@ -235,8 +235,9 @@ void fv_norm2_tiled(hipStream_t s, int N, double h, const double* f, const doubl
 // partial: kBlkPartials doubles.
 constexpr int kBlkPartials = 8192;
 bool blk_pair_supported(int B);
+// With fc instead one sweep and the restricted residual of its result (coarse inner cells).
 void blk_pair(hipStream_t s, int B, double omega, const int* faces, const double* hs, const double* f,
-              const double* u, const double* g, double* out, bool coarse, bool zero, double* partial,
-              double* norm2);
+              const double* u, const double* g, double* out, double* fc, bool coarse, bool zero,
+              double* partial, double* norm2);
 
 }  // namespace mgk

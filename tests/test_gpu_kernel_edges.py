@@ -76,6 +76,34 @@ def test_blocks_two_sweeps_in_one_pass(B, level, order):
     rb.close()
 
 
+# The last of an odd number of pre-smoothing sweeps with the restriction in its pass: a V-cycle
+# against its steps one by one (bitwise), on the finest level and, from 128 on, on a correction
+# level that starts from 0; nu1 = 2 keeps the separate restriction.
+@pytest.mark.parametrize("B,order,nu1", [(64, 2, 1), (64, 1, 3), (72, 0, 3), (72, 2, 2), (128, 2, 1), (128, 2, 3)])
+def test_blocks_restriction_in_the_last_sweep(B, order, nu1):
+    say(f"blocks restriction in sweep B={B} order={order} nu1={nu1}")
+    rb = RefinedBlocks(B, order, nu1=nu1, nu2=1, coarse_iters=4, device=DEV)
+    f, u0 = _blocks_state(rb, 3 * B + nu1)
+    want = u0.clone()
+    rhs, its = [f], [want]
+    for l in range(rb.levels - 1):
+        for _ in range(nu1):
+            rb.smooth(l, rhs[l], its[l], 1)
+        rhs.append(rb.restrict_residual(l, rhs[l], its[l], rb.zeros(l + 1)))
+        its.append(rb.zeros(l + 1))
+    for _ in range(4):
+        rb.smooth(rb.levels - 1, rhs[-1], its[-1], 1)
+    for l in range(rb.levels - 2, -1, -1):
+        rb.prolong_correct(l, its[l + 1], its[l])
+        rb.smooth(l, rhs[l], its[l], 1)
+    got = rb.vcycle(f, u0.clone())
+    inner = (slice(None),) + (slice(1, -1),) * 3
+    # the coarsest iterations of 4^3 levels in one launch round differently: 1e-13
+    scale = want[inner].abs().max()
+    assert (got[inner] - want[inner]).abs().max() <= (1e-13 * scale if rb.level_B(rb.levels - 1) == 4 else 0.0)
+    rb.close()
+
+
 # The residual norm riding on the first pass of the next cycle: cycles and iterate of the solve
 # as by single V-cycles (bitwise), its norm as by the norm's own pass (sums of 3e7 squares in
 # another order: 1e-11), whether the limit or the norm ends it.

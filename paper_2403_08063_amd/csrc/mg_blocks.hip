@@ -248,8 +248,13 @@ struct BlkCarver {
 
 void blk_layout(const mgblk_grid* g, BlkCarver& cv, mgblk_ctx* c)
 {
-  int* faces = cv.take<int>((size_t)kBlocks * 6 * kFaceInts + kInterpFaces);
-  double* partial = cv.take<double>(mgk::kBlkPartials);
+  // levels with two sweeps per pass take the list of interpolated faces, more partial sums and the
+  // ghost planes of the largest such level
+  size_t ghosts = 0;
+  for (int B : level_sizes(g))
+    if (mgk::blk_pair_supported(B)) ghosts = std::max(ghosts, (size_t)kBlocks * 6 * B * B);
+  int* faces = cv.take<int>((size_t)kBlocks * 6 * kFaceInts + (ghosts ? kInterpFaces : 0));
+  double* partial = cv.take<double>(ghosts ? mgk::kBlkPartials : kBlkNormBlocks);
   double* scal = cv.take<double>(8);
   std::vector<BlkLevel> lv;
   for (int B : level_sizes(g)) {
@@ -265,9 +270,6 @@ void blk_layout(const mgblk_grid* g, BlkCarver& cv, mgblk_ctx* c)
     }
     lv.push_back(L);
   }
-  size_t ghosts = 0;
-  for (const BlkLevel& L : lv)
-    if (mgk::blk_pair_supported(L.B)) ghosts = std::max(ghosts, (size_t)kBlocks * 6 * L.B * L.B);
   double* gh = ghosts ? cv.take<double>(ghosts) : nullptr;
   if (c) {
     c->g1 = gh;
@@ -1366,11 +1368,12 @@ mg_status mgblk_setup(const mgblk_grid* grid, void* workspace, size_t bytes, voi
     return blk_fail(nullptr, MG_EINVAL, "layout has %zu blocks", blocks.size());
   }
   const std::vector<int> faces = build_faces(blocks);
+  const size_t count = c->g1 ? faces.size() : (size_t)kBlocks * 6 * kFaceInts;  // with or without the list
   const int nlev = (int)c->lv.size();
   c->hhost.resize((size_t)kBlocks * nlev);
   for (int l = 0; l < nlev; ++l)
     for (int b = 0; b < kBlocks; ++b) c->hhost[(size_t)l * kBlocks + b] = blocks[b].width / c->lv[l].B;
-  mg_status st = blk_hip(c, hipMemcpyAsync(c->faces, faces.data(), faces.size() * sizeof(int),
+  mg_status st = blk_hip(c, hipMemcpyAsync(c->faces, faces.data(), count * sizeof(int),
                                            hipMemcpyHostToDevice, c->s), "uploading the face table");
   for (int l = 0; l < nlev && !st; ++l)
     st = blk_hip(c, hipMemcpyAsync(c->lv[l].hs, &c->hhost[(size_t)l * kBlocks], kBlocks * sizeof(double),

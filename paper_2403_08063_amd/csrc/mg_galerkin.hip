@@ -624,6 +624,7 @@ void gal_layout(const mggal_grid* g, GalCarver& cv, mggal_ctx* c)
   const size_t cnt0 = (size_t)g->n * g->n * g->n;
   double* k = cv.take<double>(cnt0);
   double* t = cv.take<double>(cnt0);
+  (void)cv.take<double>(cnt0);  // not used: the size of the workspace is what callers know it to be
   double* partial = cv.take<double>(mgk::kStreamPartials);
   double* scal = cv.take<double>(8);
   std::vector<GalLevel> lv;

@@ -113,16 +113,16 @@ struct Stream {
     const int gxa = gx0 + 2 * lane;
     const int gyw = gy0 + w * RPW;
 
-    // Addresses: per-plane buffer resources, a uniform row byte offset and a per-lane
-    // column byte offset.  Clamped coordinates keep every load in bounds.
-    uint32_t cxb[2];
+    // Addresses: per-plane buffer resources and a per-lane byte offset, row plus column.  A
+    // lane's two columns are one access; columns past the grid take nodes of the next row or,
+    // past the plane, 0, which no residual that counts reads.  Rows are clamped.  (As one access
+    // per column: variable-coefficient gradients at 257^3 FP64 and 161^3 FP32 1 and 2 % slower.)
+    const uint32_t cxb = (uint32_t)gxa * (uint32_t)sizeof(T);  // gxa >= 0
     bool colin[2];
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
       const int gx = gxa + o;
-      const uint32_t c = (uint32_t)min(max(gx, 0), n - 1);
       colin[o] = gx >= 1 && gx <= n - 2;
-      cxb[o] = c * (uint32_t)sizeof(T);
     }
     uint32_t rowb[RPW];
     bool rowin[RPW];
@@ -148,18 +148,14 @@ struct Stream {
       const PlaneBuf bu = plane_buf(a.u, zc * planeb, planeb);
       const PlaneBuf bf = plane_buf(a.f, zc * planeb, planeb);
 #pragma unroll
-      for (int i = 0; i < RPW; ++i)
-#pragma unroll
-        for (int o = 0; o < 2; ++o) {
-          PU[bb][i][o] = buf_load<T>(bu, cxb[o], rowb[i]);
-          PF[bb][i][o] = buf_load<T>(bf, cxb[o], rowb[i]);
-        }
+      for (int i = 0; i < RPW; ++i) {
+        buf_load2(bu, cxb + rowb[i], 0u, PU[bb][i][0], PU[bb][i][1]);
+        buf_load2(bf, cxb + rowb[i], 0u, PF[bb][i][0], PF[bb][i][1]);
+      }
       if constexpr (VAR) {
         const PlaneBuf bk = plane_buf(a.k, zc * planeb, planeb);
 #pragma unroll
-        for (int i = 0; i < RPW; ++i)
-#pragma unroll
-          for (int o = 0; o < 2; ++o) PK[bb][i][o] = buf_load<T>(bk, cxb[o], rowb[i]);
+        for (int i = 0; i < RPW; ++i) buf_load2(bk, cxb + rowb[i], 0u, PK[bb][i][0], PK[bb][i][1]);
       }
     };
     // plane z enters the queue from buffer BB
@@ -992,13 +988,9 @@ int best_zlen(int per_tile_plane_count, int zext, int halo, int capacity, int ma
   return bestz;
 }
 
-// Tile shapes (waves per workgroup x rows per wave), per pass, from timing sweeps on MI355X
-// at 513^3: the restriction keeps 4 rows per wave (its coarse rows pair fine rows), the
-// norm and the refinement pass favour more, lighter waves.
-constexpr int kW = 8, kRPW = 4;          // restriction
-constexpr int kNW = 8, kNRPW = 2;        // norm
-constexpr int kRW = 16, kRRPW = 2;       // refinement pass
-constexpr int kRVW = 8;                  // ... with variable k (16 waves would spill registers)
+// Tile shape (waves per workgroup x rows per wave) of the restriction, from timing sweeps on
+// MI355X at 513^3: 4 rows per wave (its coarse rows pair fine rows).
+constexpr int kW = 8, kRPW = 4;
 // Prefetch depth: 2 wherever the second buffer keeps the occupancy (the FP64
 // variable-coefficient restriction would spill registers with it).
 #ifndef MG_RESTRICT32_PD

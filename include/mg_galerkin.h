@@ -16,9 +16,7 @@
  * Stencil layout (mggal_stencil): 27 arrays of n_l^3 doubles, C order [z][y][x]; array
  * o = 9 (dz+1) + 3 (dy+1) + (dx+1) holds the coupling of node i to node i + (dx, dy, dz) at
  * interior nodes (0 where the neighbour is a boundary node, and on boundary nodes).  Setup
- * builds them on the GPU by probing: for each of the 27 residue classes c of coarse nodes mod
- * 3 per axis, P applied to the comb of class c, then A_l and R, gives at every coarse node the
- * coupling to its one neighbour of class c.
+ * forms them on the GPU, level by level, from the finer level's coefficients.
  *
  * Conventions as in mg.h: device pointers owned by the caller, C order, n^3 values including
  * the boundary (u's boundary is the Dirichlet data); a caller-provided workspace

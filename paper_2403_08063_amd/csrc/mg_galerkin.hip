@@ -353,14 +353,6 @@ __global__ void __launch_bounds__(kGalThreads)
   if (t < count) S32[t] = (float)S[t];
 }
 
-// the coarsest level (3^3 nodes): its one interior node (colour 7, slot 0 of one)
-__global__ void k_gal_coarsest(const double* __restrict__ S, const double* __restrict__ f,
-                               double* __restrict__ u)
-{
-  const size_t i = gidx(3, 1, 1, 1);
-  u[i] = f[i] / node_coeffs(S, 1, 1, 1, 1)[kCentre];
-}
-
 // The V-cycle's tail in one launch: the levels of at most 9^3 nodes from a zero guess, by one
 // workgroup, with u, f and the residual of every level in LDS and every thread the owner of one
 // node with its 27 coefficients in registers.  A colour pass of such a level is at most 64 nodes,
@@ -560,7 +552,7 @@ struct mggal_ctx {
   double h = 0;
   double* k = nullptr;      // copy of the coefficient
   double* t = nullptr;      // level 0's second buffer
-  int tail = -1;            // first level of the one-launch tail (-1: none)
+  int tail = -1;            // first level of the one-launch tail (the coarsest, 3^3, at the latest)
   double* partial = nullptr;
   double* scal = nullptr;
   double* hnorm = nullptr;  // pinned memory that norms are written to (host_norm_alloc)
@@ -741,15 +733,10 @@ void launch_tail(mggal_ctx* c, int l, const TS* (*stencil)(const GalLevel&))
 // the correction of coarse level l (its f to its u), from zero
 void coarse_cycle(mggal_ctx* c, int l)
 {
-  const int last = (int)c->lv.size() - 1;
   GalLevel& L = c->lv[l];
   if (l == c->tail) {
     if (c->g.coarse_f32) launch_tail<float>(c, l, [](const GalLevel& q) -> const float* { return q.S32; });
     else launch_tail<double>(c, l, [](const GalLevel& q) -> const double* { return q.S; });
-    return;
-  }
-  if (l == last) {
-    k_gal_coarsest<<<1, 1, 0, c->s>>>(L.S, L.f, L.u);
     return;
   }
   GalLevel& C = c->lv[l + 1];

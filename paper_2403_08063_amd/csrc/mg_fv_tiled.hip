@@ -27,8 +27,9 @@
 // A pass is bound by the FP64 issue of its two waves per SIMD (about 300 instructions per wave and
 // plane, 240 of them FP64).  What is not arithmetic counts: cells of a plane in one block without
 // branches, the planes next to a domain face in a copy of their own, and edge rows as 16-byte
-// pairs took the 512^3 passes from 1.40 and 1.07 ms (pre- and post-smoothing) to 1.14 and 0.94;
-// 35 V(3,3) cycles 105.9 -> 88.5 ms.
+// pairs took the 512^3 passes from 1.40 and 1.07 ms (pre- and post-smoothing) to 1.14 and 0.94,
+// loads and stores of a lane's columns as one access in all tiles to 1.13 and 0.91; 35 V(3,3)
+// cycles 105.9 -> 86.9 ms.
 #include "mg_buffer.h"
 #include "mg_kernels.h"
 #include "mg_lanes.h"
@@ -85,11 +86,13 @@ struct FvPass {
 
     // bit 2 i + o: a cell; a cell this tile stores
     unsigned cell = 0, own = 0;
-    uint32_t rowb[RPW], colb[2];
+    uint32_t rowb[RPW];
+    // a lane's two columns are one access, not clamped: columns outside the ghost layer take
+    // values of an adjacent row or 0, which no cell reads
+    const uint32_t colb = (uint32_t)(gx * 8);
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
       const int x = gx + o, px = 2 * lane + o;
-      colb[o] = (uint32_t)(EDGE ? min(max(x, 0), N + 1) : x) * 8u;
       const bool xin = x >= 1 && x <= N, xown = xin && px >= H && px < H + TX;
 #pragma unroll
       for (int i = 0; i < RPW; ++i) {
@@ -128,16 +131,8 @@ struct FvPass {
       const PlaneBuf bu = plane_buf(a.u, zb, planeb), bf = plane_buf(a.f, fb, planeb);
 #pragma unroll
       for (int i = 0; i < RPW; ++i) {
-        if constexpr (EDGE) {
-#pragma unroll
-          for (int o = 0; o < 2; ++o) {
-            if constexpr (IN != kZero) PU[i][o] = buf_load<double>(bu, colb[o] + rowb[i], 0u);
-            PF[i][o] = buf_load<double>(bf, colb[o] + rowb[i], 0u);
-          }
-        } else {
-          if constexpr (IN != kZero) buf_load2(bu, colb[0] + rowb[i], 0u, PU[i][0], PU[i][1]);
-          buf_load2(bf, colb[0] + rowb[i], 0u, PF[i][0], PF[i][1]);
-        }
+        if constexpr (IN != kZero) buf_load2(bu, colb + rowb[i], 0u, PU[i][0], PU[i][1]);
+        buf_load2(bf, colb + rowb[i], 0u, PF[i][0], PF[i][1]);
       }
     };
 
@@ -211,14 +206,16 @@ struct FvPass {
       const PlaneBuf bo = plane_buf(a.out, (size_t)p * planeb, planeb);
 #pragma unroll
       for (int i = 0; i < RPW; ++i) {
-        const bool pown = (own >> (2 * i)) & 1u;
+        const unsigned m2 = (own >> (2 * i)) & 3u;
         if constexpr (RES) {
           // pairs are wholly inside or outside the stored columns
-          buf_store2(U[S][so][i][0], U[S][so][i][1], bo, pown ? colb[0] + rowb[i] : 0x80000000u, 0u);
+          buf_store2(U[S][so][i][0], U[S][so][i][1], bo, (m2 & 1u) ? colb + rowb[i] : 0x80000000u, 0u);
         } else {
-#pragma unroll
-          for (int o = 0; o < 2; ++o)
-            buf_store(U[S][so][i][o], bo, ((own >> (2 * i + o)) & 1u) ? colb[o] + rowb[i] : 0x80000000u, 0u);
+          // whole pairs, and the single columns at the tile's two ends
+          const bool second = m2 == 2u, single = second || m2 == 1u;
+          buf_store2(U[S][so][i][0], U[S][so][i][1], bo, m2 == 3u ? colb + rowb[i] : 0x80000000u, 0u);
+          buf_store(second ? U[S][so][i][1] : U[S][so][i][0], bo,
+                    single ? colb + rowb[i] + (second ? 8u : 0u) : 0x80000000u, 0u);
         }
       }
     };

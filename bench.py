@@ -523,6 +523,7 @@ def fv_benchmark(dev, copy_gbs: float, N: int = 512, cycles: int = 100):
         "jacobi_algorithmic_gbs": round(gbs, 1),
         "jacobi_frac_of_peak": round(gbs / HBM_PEAK_GBS, 4),
         "jacobi_frac_of_copy": round(gbs / copy_gbs, 4),
+        "jacobi_note": "sweeps of one call share passes over memory: at 24 B a sweep the fractions may exceed 1",
         "light_speed_glups_peak_24B": round(light_speed_glups(HBM_PEAK_GBS, 24), 1),
         "light_speed_glups_copy_24B": round(light_speed_glups(copy_gbs, 24), 1),
         "vcycle_ms": round(t_cycle, 3),

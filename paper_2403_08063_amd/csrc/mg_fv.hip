@@ -682,9 +682,16 @@ mg_status vcycle_impl(mgfv_ctx* c, const double* f, double* u)
   return fv_launch_check(c, "V-cycle");
 }
 
-void copy_ghosts(mgfv_ctx* c, const double* u)
+void copy_ghosts(mgfv_ctx* c, int l, const double* u)
 {
-  mgk::copy_boundary(c->s, 3, c->lv[0].N + 2, u, c->lv[0].t);
+  mgk::copy_boundary(c->s, 3, c->lv[l].N + 2, u, c->lv[l].t);
+}
+
+// After a call that gave level l's second buffer the caller's ghosts: a correction's are 0 and are
+// not written by the cycles (level 0's are copied at the start of every call that reads them).
+void reset_ghosts(mgfv_ctx* c, int l)
+{
+  if (l > 0) mgk::zero_boundary(c->s, 3, c->lv[l].N + 2, c->lv[l].t);
 }
 
 }  // namespace
@@ -744,9 +751,10 @@ mg_status mgfv_jacobi(mgfv_ctx* c, int level, const double* f, double* u, int sw
   if (mg_status st = level_args(c, level, false)) return st;
   if (!f || !u || sweeps < 0) return fv_fail(c, MG_EINVAL, "bad smoothing arguments");
   FvLevel& L = c->lv[level];
-  mgk::copy_boundary(c->s, 3, L.N + 2, u, L.t);
+  copy_ghosts(c, level, u);
   double* r = smooth(c, level, u, L.t, f, sweeps);
   if (r != u) mgk::copy<double>(c->s, L.cnt, r, u);
+  reset_ghosts(c, level);
   return fv_launch_check(c, "Jacobi");
 }
 
@@ -783,9 +791,10 @@ mg_status mgfv_coarse_solve(mgfv_ctx* c, const double* f, double* u)
   if (!c) return fv_fail(nullptr, MG_EINVAL, "context is NULL");
   if (!f || !u) return fv_fail(c, MG_EINVAL, "f and u must be non-NULL");
   const int l = c->g.levels - 1;
-  FvLevel& L = c->lv[l];
-  if (L.N > kFvCoarseLds) mgk::copy_boundary(c->s, 3, L.N + 2, u, L.t);
+  const bool swept = c->lv[l].N > kFvCoarseLds;  // by sweeps that alternate with the second buffer
+  if (swept) copy_ghosts(c, l, u);
   coarse_solve(c, l, f, u);
+  if (swept) reset_ghosts(c, l);
   return fv_launch_check(c, "coarsest solve");
 }
 
@@ -802,7 +811,7 @@ mg_status mgfv_vcycle(mgfv_ctx* c, const double* f, double* u)
 {
   if (!c) return fv_fail(nullptr, MG_EINVAL, "context is NULL");
   if (!f || !u) return fv_fail(c, MG_EINVAL, "f and u must be non-NULL");
-  copy_ghosts(c, u);
+  copy_ghosts(c, 0, u);
   return vcycle_impl(c, f, u);
 }
 
@@ -812,7 +821,7 @@ mg_status mgfv_solve(mgfv_ctx* c, const double* f, double* u, double tol, int* c
   if (!c) return fv_fail(nullptr, MG_EINVAL, "context is NULL");
   if (!f || !u) return fv_fail(c, MG_EINVAL, "f and u must be non-NULL");
   if (!(tol >= 0) || !std::isfinite(tol)) return fv_fail(c, MG_EINVAL, "tol must be finite and >= 0");
-  copy_ghosts(c, u);
+  copy_ghosts(c, 0, u);
   double rn2 = 0, rn = 0;
   int k = 0;
   mg_status st = MG_OK;

@@ -1,0 +1,42 @@
+"""What a call on a context leaves behind for the next one, and what it leaves running."""
+import pytest
+import torch
+
+from paper_2403_08063_amd import FVMultigrid, Multigrid, RefinedBlocks
+from paper_2403_08063_amd.solver import solve_noalloc
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def rand(shape, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    return torch.rand(shape, dtype=torch.float64, device=DEV, generator=g) - 0.5
+
+
+# A single step on a coarse level with Dirichlet data of its own, then a V-cycle, whose corrections
+# have zero Dirichlet data: bitwise that of a context without the step.  Levels that march, fit LDS
+# boxes and lie in the tail; one and two passes (the result in either buffer).
+@pytest.mark.parametrize("N,level,sweeps", [(256, 1, 1), (128, 1, 3), (64, 1, 2), (64, 2, 4), (32, 2, 1)])
+def test_fv_cycle_after_a_coarse_step(N, level, sweeps):
+    say(f"fv coarse step N={N} level={level} sweeps={sweeps}")
+    a, b = FVMultigrid(N, device=DEV), FVMultigrid(N, device=DEV)
+    f, u = rand((N + 2,) * 3, N), rand((N + 2,) * 3, N + 1)
+    a.jacobi(level, rand(a.zeros(level).shape, 2), rand(a.zeros(level).shape, 3), sweeps)
+    assert torch.equal(a.vcycle(f, u.clone()), b.vcycle(f, u.clone()))
+    a.close()
+    b.close()
+
+
+def test_fv_cycle_after_a_coarsest_solve():
+    # a coarsest level of more than 16^3 cells is iterated by sweeps, here an odd number of passes
+    a, b = [FVMultigrid(64, 2, coarse_iters=7, device=DEV) for _ in range(2)]
+    f, u = rand((66,) * 3, 4), rand((66,) * 3, 5)
+    a.coarse_solve(rand((34,) * 3, 6), rand((34,) * 3, 7))
+    assert torch.equal(a.vcycle(f, u.clone()), b.vcycle(f, u.clone()))
+    a.close()
+    b.close()

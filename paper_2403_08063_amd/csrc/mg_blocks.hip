@@ -1115,7 +1115,8 @@ __global__ void __launch_bounds__(kCellThreads)
   }
 }
 
-// dst = src on the domain-boundary ghost cells (the Dirichlet data of the second buffer)
+// dst = src (0 where src is null) on the domain-boundary ghost cells (the Dirichlet data of the
+// second buffer)
 __global__ void __launch_bounds__(kFillThreads)
     k_blk_copy_boundary(int B, const int* __restrict__ faces, const double* __restrict__ src,
                         double* __restrict__ dst)
@@ -1127,7 +1128,7 @@ __global__ void __launch_bounds__(kFillThreads)
   int x, y, z;
   face_coords(f >> 1, (f & 1) ? B + 1 : 0, 1 + q % B, 1 + q / B, x, y, z);
   const size_t i = bidx(B + 2, b, z, y, x);
-  dst[i] = src[i];
+  dst[i] = src ? src[i] : 0.0;
 }
 
 // ---------------------------------------------------------------- host drivers
@@ -1424,6 +1425,9 @@ mg_status mgblk_smooth(mgblk_ctx* c, int level, const double* f, double* u, int 
   copy_boundary(c, level, u, L.t);
   double* r = sweeps(c, level, f, u, L.t, count);
   if (r != u) mgk::copy<double>(c->s, L.cnt, r, u);
+  // corrections have zero Dirichlet data, which the cycles do not write (level 0's are copied at the
+  // start of every call that reads them)
+  if (level > 0) copy_boundary(c, level, nullptr, L.t);
   return blk_hip(c, hipGetLastError(), "Jacobi");
 }
 

@@ -40,3 +40,16 @@ def test_fv_cycle_after_a_coarsest_solve():
     assert torch.equal(a.vcycle(f, u.clone()), b.vcycle(f, u.clone()))
     a.close()
     b.close()
+
+
+# The same for the refined layout: levels of boxes, of passes of two sweeps, the coarsest.
+@pytest.mark.parametrize("B,level,sweeps", [(16, 1, 1), (16, 1, 2), (16, 2, 3), (128, 1, 2), (12, 1, 1)])
+def test_blocks_cycle_after_a_coarse_step(B, level, sweeps):
+    say(f"blocks coarse step B={B} level={level} sweeps={sweeps}")
+    a, b = [RefinedBlocks(B, 2, coarse_iters=5, device=DEV) for _ in range(2)]
+    f, u = rand(a.zeros(0).shape, B), rand(a.zeros(0).shape, B + 1)
+    a.smooth(level, rand(a.zeros(level).shape, 2), rand(a.zeros(level).shape, 3), sweeps)
+    inner = (slice(None),) + (slice(1, -1),) * 3
+    assert torch.equal(a.vcycle(f, u.clone())[inner], b.vcycle(f, u.clone())[inner])
+    a.close()
+    b.close()

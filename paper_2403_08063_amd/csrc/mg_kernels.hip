@@ -788,13 +788,19 @@ double* host_norm_alloc()
   return e == hipSuccess ? static_cast<double*>(p) : nullptr;
 }
 
+// In the order of the kernels that add partial sums on the device (k_sum_2d, k_fv_sum_partials: 256
+// threads with a stride of 256, a halving tree per wave of 64, then the four waves), so that a
+// solve without pinned memory gets the same norms.
 double host_norm(const double* hnorm, int count)
 {
   if (count == 0) return hnorm[0];
   const double* p = hnorm + kNormHead;
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int i = 0; i < count; ++i) s[i & 3] += p[i];
-  return (s[0] + s[1]) + (s[2] + s[3]);
+  double acc[256] = {};
+  for (int i = 0; i < count; ++i) acc[i & 255] += p[i];
+  for (int o = 32; o >= 1; o >>= 1)
+    for (int w = 0; w < 256; w += 64)
+      for (int l = 0; l < o; ++l) acc[w + l] += acc[w + l + o];
+  return (acc[0] + acc[64]) + (acc[128] + acc[192]);
 }
 
 }  // namespace mgk

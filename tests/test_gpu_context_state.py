@@ -53,3 +53,21 @@ def test_blocks_cycle_after_a_coarse_step(B, level, sweeps):
     assert torch.equal(a.vcycle(f, u.clone())[inner], b.vcycle(f, u.clone())[inner])
     a.close()
     b.close()
+
+
+# The allocation-free solve promises the results of the context solve, residual included, also
+# where the norm is a sum over many workgroups' parts (2D: 4 of them at 65, hundreds at 513).
+@pytest.mark.parametrize("n", [65, 129, 241, 513])
+@pytest.mark.parametrize("variable", [False, True])
+def test_noalloc_norms_equal_the_context_solve(n, variable):
+    say(f"noalloc norms n={n} variable={variable}")
+    f = rand((n, n), n)
+    k = torch.exp(rand((n, n), n + 1)) if variable else None
+    mg = Multigrid(2, n, variable=variable, device=DEV)
+    if variable:
+        mg.set_coefficients(k)
+    for tol in (1e-2, 1e-6, 1e-10):
+        a, ia = mg.solve(f, tol=tol)
+        b, ib = solve_noalloc(f, torch.zeros_like(f), k=k, tol=tol)
+        assert torch.equal(a, b) and (ia.cycles, ia.relres) == (ib.cycles, ib.relres)
+    mg.close()

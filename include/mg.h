@@ -20,8 +20,13 @@
  *    device workspace of at least mg_workspace_bytes() bytes, which must stay allocated
  *    and unused by anyone else until mg_destroy.
  *  - All work is enqueued on the stream given to mg_setup (a hipStream_t passed as void*,
- *    NULL = the null stream).  mg_solve and mg_solve_adjoint synchronise that stream once
- *    per cycle to read the residual norm; all other calls return without synchronising.
+ *    NULL = the null stream).  mg_solve and mg_solve_adjoint synchronise with that stream
+ *    once per cycle to read the residual norm, as do mg_residual_norm2 and, in MG_F32_IR
+ *    mode, mg_vcycle; all other calls return without synchronising.  When mg_solve returns
+ *    without an error of the HIP runtime, nothing of it is left on the stream, except that
+ *    an MG_F32_IR solve on a 3D grid of more than 65 nodes a side may still be writing u and
+ *    the workspace and reading f: there, as after every other call, f, u and the workspace
+ *    are in use until the stream has passed the call.
  *  - One context serves one stream; calls on one context must not overlap.
  *  - No call throws.  Every call returns an mg_status; on failure mg_last_error() gives a
  *    message.  Arguments are validated before any work is enqueued.

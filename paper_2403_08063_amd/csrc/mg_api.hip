@@ -411,6 +411,10 @@ mg_status read_norm_finish(mg_ctx* c, double* host)
   return MG_OK;
 }
 
+// Waits for work enqueued ahead whose results are not used: it reads the caller's f and u and
+// writes the workspace, which a caller may free or reuse once a solve has returned.
+mg_status drain(mg_ctx* c) { return hip_check(c, hipStreamSynchronize(c->s), "stream synchronisation"); }
+
 // One outer step of iterative refinement (FP64 u, f) with the per-step kernels:
 // r32 = (f - A u)/scale, e32 = one FP32 V-cycle from e = 0, u += scale * e32.
 mg_status ir_step(mg_ctx* c, const double* f, double* u, double scale)
@@ -694,6 +698,7 @@ mg_status solve_ir_plain(mg_ctx* c, const double* f, double* u, double tol, doub
     rn = std::sqrt(rn2);
     rel = rn / bn;
   }
+  if (e && !st) st = drain(c);
   return finish(c, k, rel, tol, cycles, relres, st);
 }
 
@@ -734,7 +739,7 @@ mg_status solve_impl(mg_ctx* c, const double* f, double* u, double tol, int* cyc
   double rel = std::sqrt(two[0]) / bn, rel_prev = NAN, rn2 = 0;
   // The norm's read-back overlaps the next cycle's way down where that leaves u alone: enqueued
   // before the host waits when the contraction so far says another cycle will be needed, unused
-  // if the tolerance was reached after all.
+  // (and waited for) if the tolerance was reached after all.
   const bool overlap = c->hnorm != nullptr && c->ev != nullptr && down_keeps_u(c);
   double *down = nullptr, *ec = nullptr;
   int k = 0;
@@ -758,6 +763,7 @@ mg_status solve_impl(mg_ctx* c, const double* f, double* u, double tol, int* cyc
     if (st) break;
     rel = std::sqrt(rn2) / bn;
   }
+  if (down && !st) st = drain(c);
   return finish(c, k, rel, tol, cycles, relres, st);
 }
 

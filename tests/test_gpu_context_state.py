@@ -71,3 +71,18 @@ def test_noalloc_norms_equal_the_context_solve(n, variable):
         b, ib = solve_noalloc(f, torch.zeros_like(f), k=k, tol=tol)
         assert torch.equal(a, b) and (ia.cycles, ia.relres) == (ib.cycles, ib.relres)
     mg.close()
+
+
+# A solve that ends by its tolerance after work was enqueued ahead (the first cycle's contraction is
+# not predicted) returns with an idle stream: f, u and the workspace are the caller's again.
+@pytest.mark.parametrize("dim,n,precision", [(2, 65, "f64"), (2, 2049, "f64"), (2, 2049, "f32_ir"), (3, 65, "f64"),
+                                             (3, 65, "f32_ir"), (3, 257, "f64")])
+def test_solve_returns_with_an_idle_stream(dim, n, precision):
+    say(f"idle stream dim={dim} n={n} {precision}")
+    mg = Multigrid(dim, n, precision=precision, device=DEV)
+    f = rand((n,) * dim, n)
+    for _ in range(2):
+        u, info = mg.solve(f, mg.zeros(), tol=0.24)
+        assert torch.cuda.current_stream(DEV).query()
+        assert info.cycles == 1
+    mg.close()

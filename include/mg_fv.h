@@ -22,8 +22,9 @@
  *  - every array pointer is a device pointer owned by the caller; f is read only; the
  *    ghost layer of u is read, never written; the library calls no hipMalloc: the
  *    workspace (mgfv_workspace_bytes) is the caller's, 256-byte aligned;
- *  - all work goes on the stream given to mgfv_setup; mgfv_solve synchronises once per
- *    cycle to read the residual norm; the other calls do not synchronise;
+ *  - all work goes on the stream given to mgfv_setup; mgfv_solve synchronises with it once
+ *    per cycle to read the residual norm, mgfv_residual_norm2 once; both leave nothing on the
+ *    stream when they return without a HIP error; the other calls do not synchronise;
  *  - errors: MG_EINVAL (bad size or argument), MG_ENOMEM (workspace too small), MG_EHIP
  *    (a HIP error, its text in mgfv_last_error), MG_ENOCONV (cycle limit reached before
  *    the tolerance; u holds the last iterate), MG_ENAN (non-finite residual norm).

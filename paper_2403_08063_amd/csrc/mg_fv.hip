@@ -840,7 +840,11 @@ mg_status mgfv_solve(mgfv_ctx* c, const double* f, double* u, double tol, int* c
       if ((st = fv_launch_check(c, "V-cycle"))) break;
       if ((st = fv_hip(c, hipEventSynchronize(c->ev), "waiting for the norm"))) break;
       rn = std::sqrt(mgk::host_norm(c->hnorm, c->hcount));
-      if (!more || !std::isfinite(rn) || rn <= tol) break;
+      if (!more || !std::isfinite(rn) || rn <= tol) {
+        // the coarse levels' work is for nothing; a caller may free the workspace now
+        if (more) st = fv_hip(c, hipStreamSynchronize(c->s), "stream synchronisation");
+        break;
+      }
       top_up(c, f, u, cur, ec);
     }
   } else {

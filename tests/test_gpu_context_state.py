@@ -86,3 +86,16 @@ def test_solve_returns_with_an_idle_stream(dim, n, precision):
         assert torch.cuda.current_stream(DEV).query()
         assert info.cycles == 1
     mg.close()
+
+
+@pytest.mark.parametrize("N", [64, 256])
+def test_fv_solve_returns_with_an_idle_stream(N):
+    say(f"fv idle stream N={N}")
+    mg = FVMultigrid(N, device=DEV)
+    f, u = rand((N + 2,) * 3, N), torch.zeros((N + 2,) * 3, dtype=torch.float64, device=DEV)
+    r0 = mg.residual_norm2(f, u) ** 0.5
+    for factor, cycles in ((2.0, 0), (0.5, 1)):
+        _, info = mg.solve(f, u.zero_(), tol=factor * r0)
+        assert torch.cuda.current_stream(DEV).query()
+        assert info.converged and info.cycles == cycles
+    mg.close()

@@ -829,23 +829,32 @@ mg_status mgfv_solve(mgfv_ctx* c, const double* f, double* u, double tol, int* c
     // The first sweep of a cycle forms the residual of the iterate it starts from: the iterate's
     // norm comes out of the next cycle's pre-smoothing, which writes the second buffer only, so
     // the iterate is still there when the norm ends the solve.  The coarse levels run while the
-    // host waits for it; after the last cycle allowed the norm is a pass of its own.
+    // host waits for it.  The norm is a pass of its own before the first cycle, after the last one
+    // allowed and where the contraction so far says that it will end the solve: a way down for
+    // nothing costs more (a solve from a converged iterate at 256^3 cells 388 us, 97 so).
+    double predicted = 0.0, rn_prev = NAN;
     for (;; ++k) {
-      const bool more = k < c->g.max_cycles;
+      const bool more = k < c->g.max_cycles, ride = more && predicted > 4.0 * tol;
       double *cur = nullptr, *ec = nullptr;
-      if (more) cur = top_down(c, f, u, norm_place(c));
+      if (ride) cur = top_down(c, f, u, norm_place(c));
       else norm2(c, f, u);
       if ((st = fv_hip(c, hipEventRecord(c->ev, c->s), "recording the norm event"))) break;
-      if (more) ec = coarse_cycle(c, 1);
+      if (ride) ec = coarse_cycle(c, 1);
       if ((st = fv_launch_check(c, "V-cycle"))) break;
       if ((st = fv_hip(c, hipEventSynchronize(c->ev), "waiting for the norm"))) break;
       rn = std::sqrt(mgk::host_norm(c->hnorm, c->hcount));
       if (!more || !std::isfinite(rn) || rn <= tol) {
         // the coarse levels' work is for nothing; a caller may free the workspace now
-        if (more) st = fv_hip(c, hipStreamSynchronize(c->s), "stream synchronisation");
+        if (ride) st = fv_hip(c, hipStreamSynchronize(c->s), "stream synchronisation");
         break;
       }
+      if (!ride) {
+        cur = top_down(c, f, u, nullptr);
+        ec = coarse_cycle(c, 1);
+      }
       top_up(c, f, u, cur, ec);
+      predicted = rn_prev > 0 ? rn * (rn / rn_prev) : rn;
+      rn_prev = rn;
     }
   } else {
     norm2(c, f, u);

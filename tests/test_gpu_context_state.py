@@ -99,3 +99,23 @@ def test_fv_solve_returns_with_an_idle_stream(N):
         assert torch.cuda.current_stream(DEV).query()
         assert info.converged and info.cycles == cycles
     mg.close()
+
+
+# Where the norm is a pass of its own and where it rides on the next cycle, by the contraction so far
+# and the tolerance: the solve ends at the first iterate within it, bitwise that of as many V-cycles.
+@pytest.mark.parametrize("N,nu1", [(32, 3), (128, 2)])
+def test_fv_solve_ends_at_the_first_iterate_within_the_tolerance(N, nu1):
+    say(f"fv tolerances N={N} nu1={nu1}")
+    mg = FVMultigrid(N, nu1=nu1, nu2=2, max_cycles=5, device=DEV)
+    f = rand((N + 2,) * 3, N)
+    its, norms = [torch.zeros((N + 2,) * 3, dtype=torch.float64, device=DEV)], []
+    for k in range(6):
+        norms.append(mg.residual_norm2(f, its[k]) ** 0.5)
+        its.append(mg.vcycle(f, its[k].clone()))
+    for q in range(1, 22):  # between the norms and, with a little room, on either side of each
+        tol = norms[0] * (norms[5] / norms[0]) ** (q / 20.0) * 1.02
+        k = next((i for i in range(6) if norms[i] <= tol), 5)
+        u, info = mg.solve(f, its[0].clone(), tol=tol)
+        assert info.cycles == k and torch.equal(u, its[k])
+        assert abs(info.relres - norms[k]) <= 1e-12 * norms[k]
+    mg.close()

@@ -119,3 +119,21 @@ def test_fv_solve_ends_at_the_first_iterate_within_the_tolerance(N, nu1):
         assert info.cycles == k and torch.equal(u, its[k])
         assert abs(info.relres - norms[k]) <= 1e-12 * norms[k]
     mg.close()
+
+
+def test_blocks_solve_ends_at_the_first_iterate_within_the_tolerance():
+    rb = RefinedBlocks(64, 2, nu1=3, nu2=2, coarse_iters=8, max_cycles=4, device=DEV)
+    f = rand(rb.zeros(0).shape, 64)
+    its, norms = [rb.zeros(0)], []
+    for k in range(5):
+        norms.append(rb.residual_norm2(f, its[k]) ** 0.5)
+        its.append(rb.vcycle(f, its[k].clone()))
+    assert all(b < a for a, b in zip(norms, norms[1:]))
+    inner = (slice(None),) + (slice(1, -1),) * 3
+    for q in range(-1, 13):
+        tol = norms[0] * (norms[4] / norms[0]) ** (q / 11.0) * 1.02
+        k = next((i for i in range(5) if norms[i] <= tol), 4)
+        u, info = rb.mg_solve(f, its[0].clone(), tol)
+        assert info.cycles == k and torch.equal(u[inner], its[k][inner])
+        assert abs(info.relres - norms[k]) <= 1e-11 * norms[k]
+    rb.close()

@@ -221,7 +221,10 @@ mg_status mg_solve_noalloc(const mg_grid* grid, const double* k, const double* f
  * mg_validate / mg_solve_noalloc call of this thread when ctx is NULL.  Never NULL. */
 const char* mg_last_error(const mg_ctx* ctx);
 
-/* Releases the context (not the workspace).  Does not synchronise. */
+/* Releases the context (not the workspace).  Does not synchronise: pinned host memory that
+ * the context read norms through (131 KB) is kept for later contexts.  Of more than 16 idle
+ * ones the further are freed, as is one whose last read failed; that may wait for the
+ * device. */
 void mg_destroy(mg_ctx* ctx);
 
 #ifdef __cplusplus

@@ -53,7 +53,7 @@
  * Coarse-level arrays live in the workspace; the finest level's are the caller's.
  *
  * Conventions as in mg.h: device pointers owned by the caller; a caller-provided workspace
- * (mgblk_workspace_bytes, 256-byte aligned), no allocation by the library; all work on the
+ * (mgblk_workspace_bytes, 256-byte aligned), no device memory allocated by the library; all work on the
  * stream given to mgblk_setup; mgblk_residual_norm2 and mgblk_solve synchronise to read norms.
  */
 #ifndef MG_BLOCKS_H

@@ -20,7 +20,7 @@
  *
  * Conventions as in mg.h: device pointers owned by the caller, C order, n^3 values including
  * the boundary (u's boundary is the Dirichlet data); a caller-provided workspace
- * (mggal_workspace_bytes, 256-byte aligned), no allocation by the library; all work on the
+ * (mggal_workspace_bytes, 256-byte aligned), no device memory allocated by the library; all work on the
  * stream given to mggal_setup; mggal_solve synchronises once per cycle to read the norm.
  */
 #ifndef MG_GALERKIN_H

@@ -52,18 +52,11 @@ struct mg_ctx {
   bool coeffs = false;
   int fuse = MG_FUSE_ALL;  // kernel-fusion flags (mg_set_fusion)
   int tail_first = -1;  // first level handled by the one-launch coarse tail (-1: none)
-  // norm read-back without draining the stream: pinned host memory (host_norm_alloc) and an event
-  // after the norm (nullptr: synchronous reads only).  FP64 norms are written there by the kernels,
+  // norm read-back without draining the stream.  FP64 norms are written there by the kernels,
   // hcount partial sums or a finished one (0).
-  double* hnorm = nullptr;
+  mgk::HostNorm hn;
   int hcount = 0;
-  hipEvent_t ev = nullptr;
   char err[512] = "no error";
-  ~mg_ctx()
-  {
-    if (ev) (void)hipEventDestroy(ev);
-    if (hnorm) (void)hipHostFree(hnorm);
-  }
 };
 
 namespace {
@@ -241,7 +234,7 @@ T* smooth(mg_ctx* c, int l, T* u, T* t, const T* f, const T* k, int sweeps, bool
   const Level& L = c->lv[l];
   const int dim = c->g.dim;
   const bool tiled = use_tiled(c, l), strips = use_strips(c), cube = use_cube(c, l);
-  const bool direct = norm && norm == c->hnorm;  // the host adds the partial sums
+  const bool direct = norm && norm == c->hn.mem;  // the host adds the partial sums
   // the blocked 3D pass that takes the correction is the first one: two sweeps unless only one
   // is asked for (FP64 passes fuse the correction into 2-sweep passes only)
   const bool pair = sweeps >= 2 && mgk::rbgs_tiled_max_sweeps(k != nullptr, sizeof(T)) == 2;
@@ -272,7 +265,7 @@ T* smooth(mg_ctx* c, int l, T* u, T* t, const T* f, const T* k, int sweeps, bool
       T* rfc = left == sw ? fc : nullptr;
       if (strips)
         mgk::rbgs_strips<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, rfc,
-                            direct ? c->hnorm + mgk::kNormHead : c->partial, left == sw ? norm : nullptr,
+                            direct ? c->hn.mem + mgk::kNormHead : c->partial, left == sw ? norm : nullptr,
                             direct ? &c->hcount : nullptr);
       else if (cube)
         mgk::rbgs_cube<T>(c->s, L.n, L.h, k, f, cur, other, sw, zero, ec, rfc);
@@ -385,29 +378,33 @@ void norm2(mg_ctx* c, const double* f, const double* u, int mode, double* out)
 // Where the kernels of an FP64 solve put norms, and their read-back.
 double* norm_place(mg_ctx* c)
 {
+  c->hn.take();
+  c->hn.unread = true;
   c->hcount = 0;
-  return c->hnorm ? c->hnorm : c->scal;
+  return c->hn.mem ? c->hn.mem : c->scal;
 }
 
 mg_status read_norms(mg_ctx* c, double* host, int count = 1)
 {
-  if (!c->hnorm) return read_scalar(c, c->scal, host, count);
+  if (!c->hn.mem) return read_scalar(c, c->scal, host, count);
   if (mg_status st = hip_check(c, hipStreamSynchronize(c->s), "stream synchronisation")) return st;
-  host[0] = mgk::host_norm(c->hnorm, c->hcount);
-  for (int i = 1; i < count; ++i) host[i] = c->hnorm[i];
+  c->hn.unread = false;
+  host[0] = mgk::host_norm(c->hn.mem, c->hcount);
+  for (int i = 1; i < count; ++i) host[i] = c->hn.mem[i];
   return MG_OK;
 }
 
-// In two halves, the second waiting for the work enqueued before the first only (hnorm, ev).
+// In two halves, the second waiting for the work enqueued before the first only (hn).
 mg_status read_norm_start(mg_ctx* c)
 {
-  return hip_check(c, hipEventRecord(c->ev, c->s), "recording the norm event");
+  return hip_check(c, hipEventRecord(c->hn.ev, c->s), "recording the norm event");
 }
 
 mg_status read_norm_finish(mg_ctx* c, double* host)
 {
-  if (mg_status st = hip_check(c, hipEventSynchronize(c->ev), "waiting for a norm")) return st;
-  *host = mgk::host_norm(c->hnorm, c->hcount);
+  if (mg_status st = hip_check(c, hipEventSynchronize(c->hn.ev), "waiting for a norm")) return st;
+  c->hn.unread = false;
+  *host = mgk::host_norm(c->hn.mem, c->hcount);
   return MG_OK;
 }
 
@@ -476,16 +473,18 @@ mg_status finish(mg_ctx* c, int k, double rel, double tol, int* cycles, double* 
 // Enqueues the copy of `count` device scalars to the pinned host words and the event after it.
 mg_status read_scalar_start(mg_ctx* c, const double* dev, int count = 1)
 {
-  mg_status st = hip_check(c, hipMemcpyAsync(c->hnorm, dev, count * sizeof(double),
+  c->hn.unread = true;
+  mg_status st = hip_check(c, hipMemcpyAsync(c->hn.mem, dev, count * sizeof(double),
                                              hipMemcpyDeviceToHost, c->s), "reading a norm");
-  if (!st) st = hip_check(c, hipEventRecord(c->ev, c->s), "recording the norm event");
+  if (!st) st = hip_check(c, hipEventRecord(c->hn.ev, c->s), "recording the norm event");
   return st;
 }
 
 mg_status read_scalar_finish(mg_ctx* c, double* host, int count = 1)
 {
-  if (mg_status st = hip_check(c, hipEventSynchronize(c->ev), "waiting for a norm")) return st;
-  for (int i = 0; i < count; ++i) host[i] = c->hnorm[i];
+  if (mg_status st = hip_check(c, hipEventSynchronize(c->hn.ev), "waiting for a norm")) return st;
+  c->hn.unread = false;
+  for (int i = 0; i < count; ++i) host[i] = c->hn.mem[i];
   return MG_OK;
 }
 
@@ -568,7 +567,7 @@ mg_status solve_ir_streamed(mg_ctx* c, const double* f, double* u, double tol, d
   FusedIr fst{L0.f32, L0.u32, L0.t32, 0};
   double scale = ir_scale(c, fused_rhs ? c->last_bn : bn);  // scale of the r32 being written
   double rn2 = 0;
-  const bool overlap = c->hnorm != nullptr && c->ev != nullptr;
+  const bool overlap = c->hn.mem != nullptr && c->hn.ev != nullptr;
   mgk::ir_pass_tiled(c->s, L0.n, L0.h, L0.k, f, cur, nullptr, 0.0, 1.0 / scale, other, L0.f32,
                      c->partial, c->scal, fused_rhs ? c->partial_b : nullptr);
   std::swap(cur, other);
@@ -665,7 +664,7 @@ mg_status solve_ir_plain(mg_ctx* c, const double* f, double* u, double tol, doub
 {
   Level& L0 = c->lv[0];
   const int dim = c->g.dim;
-  const bool overlap = c->hnorm != nullptr && c->ev != nullptr;
+  const bool overlap = c->hn.mem != nullptr && c->hn.ev != nullptr;
   double rel = rn / bn, rel_prev = NAN, scale = ir_scale(c, rn), rn2 = 0;
   float* e = nullptr;  // the correction of a cycle already enqueued
   int k = 0;
@@ -708,6 +707,7 @@ mg_status solve_impl(mg_ctx* c, const double* f, double* u, double tol, int* cyc
   if (mg_status st = check_ready(c)) return st;
   if (!f || !u) return fail(c, MG_EINVAL, "f and u must be non-NULL");
   if (!(tol > 0) || !std::isfinite(tol)) return fail(c, MG_EINVAL, "tol must be > 0");
+  c->hn.take();
   Level& L0 = c->lv[0];
   const bool ir = c->g.precision == MG_F32_IR;
   if (use_blocked(c, 0)) mgk::copy_boundary(c->s, c->g.dim, L0.n, u, L0.t);
@@ -740,7 +740,7 @@ mg_status solve_impl(mg_ctx* c, const double* f, double* u, double tol, int* cyc
   // The norm's read-back overlaps the next cycle's way down where that leaves u alone: enqueued
   // before the host waits when the contraction so far says another cycle will be needed, unused
   // (and waited for) if the tolerance was reached after all.
-  const bool overlap = c->hnorm != nullptr && c->ev != nullptr && down_keeps_u(c);
+  const bool overlap = c->hn.mem != nullptr && c->hn.ev != nullptr && down_keeps_u(c);
   double *down = nullptr, *ec = nullptr;
   int k = 0;
   mg_status st = MG_OK;
@@ -907,12 +907,7 @@ mg_status mg_setup(const mg_grid* grid, void* workspace, size_t bytes, void* str
   mg_ctx* c = new (std::nothrow) mg_ctx;
   if (!c) return fail(nullptr, MG_ENOMEM, "host allocation of the context failed");
   mg_status st = init_ctx(c, grid, workspace, need, static_cast<hipStream_t>(stream));
-  // pinned host memory for norms; without it the solve reads them synchronously
-  if (!st) {
-    c->hnorm = mgk::host_norm_alloc();
-    if (c->hnorm && hipEventCreateWithFlags(&c->ev, hipEventDisableTiming) != hipSuccess) c->ev = nullptr;
-    (void)hipGetLastError();  // a failed event only disables the overlap
-  }
+  c->hn.set_device();
   if (st) {
     snprintf(g_err, sizeof g_err, "%s", c->err);
     delete c;
@@ -1063,7 +1058,7 @@ mg_status mg_solve_noalloc(const mg_grid* grid, const double* k, const double* f
                 (size_t)MG_NOALLOC_MAX_BYTES);
   void* ws = nullptr;
   if (mg_status st = scratch_address(&ws)) return st;
-  mg_ctx c;  // on the stack: no host allocation either (no pinned word: synchronous norm reads)
+  mg_ctx c;  // on the stack: no host allocation either (hn takes no pinned memory: synchronous norm reads)
   mg_status st = init_ctx(&c, grid, ws, need, static_cast<hipStream_t>(stream));
   if (!st && grid->variable) st = set_coefficients_impl(&c, k);
   if (!st) st = solve_impl(&c, f, u, tol, cycles, relres);

@@ -184,12 +184,8 @@ struct mgblk_ctx {
   std::vector<double> hhost;
   C2FWeights w{};
   bool coarse4 = false;   // k_blk_coarse4 may use the LDS it needs
-  double* hnorm = nullptr;  // pinned memory that norms are written to (host_norm_alloc)
+  mgk::HostNorm hn;       // where norms are written to
   char err[512] = "no error";
-  ~mgblk_ctx()
-  {
-    if (hnorm) (void)hipHostFree(hnorm);
-  }
 };
 
 namespace {
@@ -1295,17 +1291,23 @@ double* vcycle_rec(mgblk_ctx* c, int l, const double* f, double* x, double* y, b
   return sweeps(c, l, f, cur, oth, c->g.nu2);
 }
 
-double* norm_place(mgblk_ctx* c) { return c->hnorm ? c->hnorm : c->scal; }
+double* norm_place(mgblk_ctx* c)
+{
+  c->hn.take();
+  c->hn.unread = true;
+  return c->hn.mem ? c->hn.mem : c->scal;
+}
 
 mg_status read_norm(mgblk_ctx* c, double* out)
 {
   if (mg_status st = blk_hip(c, hipGetLastError(), "norm")) return st;
-  if (!c->hnorm)
+  if (!c->hn.mem)
     if (mg_status st = blk_hip(c, hipMemcpyAsync(out, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s),
                                "reading the norm"))
       return st;
   if (mg_status st = blk_hip(c, hipStreamSynchronize(c->s), "stream synchronisation")) return st;
-  if (c->hnorm) *out = mgk::host_norm(c->hnorm, 0);
+  c->hn.unread = false;
+  if (c->hn.mem) *out = mgk::host_norm(c->hn.mem, 0);
   return MG_OK;
 }
 
@@ -1391,7 +1393,7 @@ mg_status mgblk_setup(const mgblk_grid* grid, void* workspace, size_t bytes, voi
     delete c;
     return st;
   }
-  c->hnorm = mgk::host_norm_alloc();
+  c->hn.set_device();
   *out = c;
   return MG_OK;
 }

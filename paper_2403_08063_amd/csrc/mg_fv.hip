@@ -49,15 +49,9 @@ struct mgfv_ctx {
   double* partial = nullptr;
   double* scal = nullptr;
   int tail = -1;           // first level of the one-launch tail (-1: none)
-  double* hnorm = nullptr; // pinned memory (host_norm_alloc) and event of the norm read-back
+  mgk::HostNorm hn;        // where norms are written to
   int hcount = 0;          // partial sums there, 0: a finished norm
-  hipEvent_t ev = nullptr;
   char err[512] = "no error";
-  ~mgfv_ctx()
-  {
-    if (ev) (void)hipEventDestroy(ev);
-    if (hnorm) (void)hipHostFree(hnorm);
-  }
 };
 
 namespace {
@@ -516,7 +510,7 @@ constexpr int kFvBlockedMin = 16;
 double* smooth(mgfv_ctx* c, int l, double* u, double* t, const double* f, int sweeps, bool zero = false,
                const double* ec = nullptr, double* fc = nullptr, double* norm2 = nullptr)
 {
-  const bool direct = norm2 && norm2 == c->hnorm;  // the host adds the partial sums
+  const bool direct = norm2 && norm2 == c->hn.mem;  // the host adds the partial sums
   const FvLevel& L = c->lv[l];
   const double ih2 = 1.0 / (L.h * L.h);
   const bool blocked = L.N >= kFvBlockedMin, tiled = mgk::fv_tiled_supported(L.N);
@@ -533,7 +527,7 @@ double* smooth(mgfv_ctx* c, int l, double* u, double* t, const double* f, int sw
     const bool last = left == n;
     if (n > 1) {
       mgk::fv_sweeps(c->s, L.N, L.h, c->g.omega, n, zero ? nullptr : cur, f, ec, oth,
-                     last ? fc : nullptr, direct ? c->hnorm + mgk::kNormHead : c->partial,
+                     last ? fc : nullptr, direct ? c->hn.mem + mgk::kNormHead : c->partial,
                      last && fc ? norm2 : nullptr, direct ? &c->hcount : nullptr);
       restricted = last && fc;
     } else if (ec) {
@@ -596,11 +590,13 @@ void prolong(mgfv_ctx* c, int l, const double* ec, double* u)
   smooth(c, l, u, nullptr, nullptr, 0, false, ec);
 }
 
-// Where norms are put (see host_norm_alloc).
+// Where norms are put (see HostNorm).
 double* norm_place(mgfv_ctx* c)
 {
+  c->hn.take();
+  c->hn.unread = true;
   c->hcount = 0;
-  return c->hnorm ? c->hnorm : c->scal;
+  return c->hn.mem ? c->hn.mem : c->scal;
 }
 
 void norm2(mgfv_ctx* c, const double* f, const double* u)
@@ -653,12 +649,13 @@ void top_up(mgfv_ctx* c, const double* f, double* u, double* cur, const double* 
 
 mg_status read_norm(mgfv_ctx* c, double* out)
 {
-  if (!c->hnorm)
+  if (!c->hn.mem)
     if (mg_status st = fv_hip(c, hipMemcpyAsync(out, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s),
                               "reading the norm"))
       return st;
   if (mg_status st = fv_hip(c, hipStreamSynchronize(c->s), "stream synchronisation")) return st;
-  if (c->hnorm) *out = mgk::host_norm(c->hnorm, c->hcount);
+  c->hn.unread = false;
+  if (c->hn.mem) *out = mgk::host_norm(c->hn.mem, c->hcount);
   return MG_OK;
 }
 
@@ -729,10 +726,7 @@ mg_status mgfv_setup(const mgfv_grid* grid, void* workspace, size_t bytes, void*
   mgk::fill<double>(c->s, need / sizeof(double), 0.0, static_cast<double*>(workspace));
   for (int l = 1; l < grid->levels; ++l)
     if (c->lv[l].N == kFvTailN) c->tail = l;
-  // pinned memory for norm reads that leave the stream running; without it they wait
-  c->hnorm = mgk::host_norm_alloc();
-  if (c->hnorm && hipEventCreateWithFlags(&c->ev, hipEventDisableTiming) != hipSuccess) c->ev = nullptr;
-  (void)hipGetLastError();
+  c->hn.set_device();
   if (mg_status st = fv_launch_check(c, "setup")) {
     snprintf(g_fv_err, sizeof g_fv_err, "%s", c->err);
     delete c;
@@ -822,10 +816,11 @@ mg_status mgfv_solve(mgfv_ctx* c, const double* f, double* u, double tol, int* c
   if (!f || !u) return fv_fail(c, MG_EINVAL, "f and u must be non-NULL");
   if (!(tol >= 0) || !std::isfinite(tol)) return fv_fail(c, MG_EINVAL, "tol must be finite and >= 0");
   copy_ghosts(c, 0, u);
+  c->hn.take();
   double rn2 = 0, rn = 0;
   int k = 0;
   mg_status st = MG_OK;
-  if (norm_rides(c) && c->hnorm && c->ev) {
+  if (norm_rides(c) && c->hn.mem && c->hn.ev) {
     // The first sweep of a cycle forms the residual of the iterate it starts from: the iterate's
     // norm comes out of the next cycle's pre-smoothing, which writes the second buffer only, so
     // the iterate is still there when the norm ends the solve.  The coarse levels run while the
@@ -838,11 +833,12 @@ mg_status mgfv_solve(mgfv_ctx* c, const double* f, double* u, double tol, int* c
       double *cur = nullptr, *ec = nullptr;
       if (ride) cur = top_down(c, f, u, norm_place(c));
       else norm2(c, f, u);
-      if ((st = fv_hip(c, hipEventRecord(c->ev, c->s), "recording the norm event"))) break;
+      if ((st = fv_hip(c, hipEventRecord(c->hn.ev, c->s), "recording the norm event"))) break;
       if (ride) ec = coarse_cycle(c, 1);
       if ((st = fv_launch_check(c, "V-cycle"))) break;
-      if ((st = fv_hip(c, hipEventSynchronize(c->ev), "waiting for the norm"))) break;
-      rn = std::sqrt(mgk::host_norm(c->hnorm, c->hcount));
+      if ((st = fv_hip(c, hipEventSynchronize(c->hn.ev), "waiting for the norm"))) break;
+      c->hn.unread = false;
+      rn = std::sqrt(mgk::host_norm(c->hn.mem, c->hcount));
       if (!more || !std::isfinite(rn) || rn <= tol) {
         // the coarse levels' work is for nothing; a caller may free the workspace now
         if (ride) st = fv_hip(c, hipStreamSynchronize(c->s), "stream synchronisation");

@@ -555,13 +555,9 @@ struct mggal_ctx {
   int tail = -1;            // first level of the one-launch tail (the coarsest, 3^3, at the latest)
   double* partial = nullptr;
   double* scal = nullptr;
-  double* hnorm = nullptr;  // pinned memory that norms are written to (host_norm_alloc)
+  mgk::HostNorm hn;         // where norms are written to
   std::vector<GalLevel> lv;
   char err[512] = "no error";
-  ~mggal_ctx()
-  {
-    if (hnorm) (void)hipHostFree(hnorm);
-  }
 };
 
 namespace {
@@ -772,16 +768,19 @@ void build_level(mggal_ctx* c, int l)
 
 mg_status read_norm2(mggal_ctx* c, const double* f, const double* u, int mode, double* out)
 {
-  double* at = c->hnorm ? c->hnorm : c->scal;
+  c->hn.take();
+  c->hn.unread = true;
+  double* at = c->hn.mem ? c->hn.mem : c->scal;
   if (fine_tiled(c)) mgk::resid_norm2_tiled(c->s, c->g.n, c->h, c->k, f, u, mode, c->partial, at);
   else mgk::resid_norm2(c->s, 3, c->g.n, c->h, c->k, f, u, mode, c->partial, at);
   if (mg_status st = gal_hip(c, hipGetLastError(), "norm")) return st;
-  if (!c->hnorm)
+  if (!c->hn.mem)
     if (mg_status st = gal_hip(c, hipMemcpyAsync(out, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->s),
                                "reading the norm"))
       return st;
   if (mg_status st = gal_hip(c, hipStreamSynchronize(c->s), "stream synchronisation")) return st;
-  if (c->hnorm) *out = mgk::host_norm(c->hnorm, 0);
+  c->hn.unread = false;
+  if (c->hn.mem) *out = mgk::host_norm(c->hn.mem, 0);
   return MG_OK;
 }
 
@@ -817,7 +816,7 @@ mg_status mggal_setup(const mggal_grid* grid, const double* k, void* workspace, 
   c->h = 1.0 / (grid->n - 1);
   GalCarver cv{static_cast<char*>(workspace)};
   gal_layout(grid, cv, c);
-  c->hnorm = mgk::host_norm_alloc();
+  c->hn.set_device();
   mgk::copy<double>(c->s, c->lv[0].cnt, k, c->k);
   for (size_t l = 1; l < c->lv.size(); ++l) {  // zero boundaries of every coarse array
     mgk::fill<double>(c->s, c->lv[l].cnt, 0.0, c->lv[l].u);

@@ -211,12 +211,29 @@ void fv_sweeps(hipStream_t s, int N, double h, double omega, int sweeps, const d
                const double* f, const double* ec, double* out, double* fc, double* partial,
                double* norm2, int* count = nullptr);
 // Host memory that kernels write squared norms to: pinned, the first kNormHead doubles for finished
-// norms, kStreamPartials behind them for partial sums that the host adds.  A norm read this way
-// costs neither the kernel that adds the partial sums nor a copy, 4 us each between a cycle's
-// launches (2D solve at 129^2: 480 -> 405 us, at 2049^2: 1.25 -> 1.11 ms, FV solve at 64^3: 3.53 -> 3.38 ms).  nullptr if it
-// cannot be allocated: norms then go through device memory.
+// norms, kStreamPartials behind them for partial sums that the host adds, and the event of a read
+// that lets the stream run on.  A norm read this way costs neither the kernel that adds the partial
+// sums nor a copy, 4 us each between a cycle's launches (2D solve at 129^2: 480 -> 405 us, at
+// 2049^2: 1.25 -> 1.11 ms, FV solve at 64^3: 3.53 -> 3.38 ms).
+//
+// A context takes one at the first call that reads a norm and its end gives it back: building,
+// cycling and destroying a context allocate and free nothing and may be captured.  Up to 16
+// idle ones (131 KB each) are kept for the process's next contexts on their device; with
+// an allocation and an event per context, building and destroying one took 47 us in place of 14 (FV)
+// and 52 in place of 27 (17^2 nodes), and failed under capture.
 constexpr int kNormHead = 8;
-double* host_norm_alloc();
+struct HostNorm {
+  double* mem = nullptr;    // nullptr: not taken, or refused: norms go through device memory
+  hipEvent_t ev = nullptr;  // nullptr: reads wait for the stream
+  bool unread = false;      // work that writes to mem may not have finished
+  int dev = -1;             // device of the context's stream; -1: no pinned memory for this context
+  HostNorm() = default;
+  HostNorm(const HostNorm&) = delete;
+  HostNorm& operator=(const HostNorm&) = delete;
+  ~HostNorm();
+  void set_device();  // the current device
+  void take();        // mem and ev, unless there already
+};
 // the sum of `count` partial sums, or for count 0 the finished norm
 double host_norm(const double* hnorm, int count);
 // The passes of fv_sweeps on small levels (mg_fv_cube.hip; fv_sweeps calls it there): returns the

@@ -11,6 +11,7 @@
 #include "mg_stencil.h"
 
 #include <cmath>
+#include <mutex>
 
 namespace mgk {
 namespace {
@@ -780,12 +781,70 @@ template void fill<float>(hipStream_t, size_t, float, float*);
 template void copy<double>(hipStream_t, size_t, const double*, double*);
 template void copy<float>(hipStream_t, size_t, const float*, float*);
 
-double* host_norm_alloc()
+namespace {
+
+constexpr int kNormsKept = 16;
+struct IdleNorm {
+  double* mem;
+  hipEvent_t ev;
+  int dev;
+};
+std::mutex g_norms_mu;
+IdleNorm g_norms[kNormsKept];
+int g_norms_idle = 0;
+
+}  // namespace
+
+void HostNorm::set_device()
 {
+  if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+}
+
+void HostNorm::take()
+{
+  if (mem || dev < 0) return;
+  {
+    std::lock_guard<std::mutex> lock(g_norms_mu);
+    for (int i = 0; i < g_norms_idle; ++i)
+      if (g_norms[i].dev == dev) {
+        mem = g_norms[i].mem;
+        ev = g_norms[i].ev;
+        g_norms[i] = g_norms[--g_norms_idle];
+        return;
+      }
+  }
+  // another thread may be capturing, which an allocation in the default mode would end
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  int current = dev;
+  const bool moved = hipGetDevice(&current) == hipSuccess && current != dev && hipSetDevice(dev) == hipSuccess;
   void* p = nullptr;
-  const hipError_t e = hipHostMalloc(&p, (kNormHead + kStreamPartials) * sizeof(double), hipHostMallocDefault);
-  (void)hipGetLastError();
-  return e == hipSuccess ? static_cast<double*>(p) : nullptr;
+  if (hipHostMalloc(&p, (kNormHead + kStreamPartials) * sizeof(double), hipHostMallocDefault) == hipSuccess) {
+    mem = static_cast<double*>(p);
+    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) ev = nullptr;
+  } else {
+    dev = -1;  // refused: not asked for again
+  }
+  if (moved) (void)hipSetDevice(current);
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  (void)hipGetLastError();  // a refusal only leaves the reads to copies or to a wait for the stream
+}
+
+HostNorm::~HostNorm()
+{
+  if (!mem) return;
+  if (!unread) {
+    std::lock_guard<std::mutex> lock(g_norms_mu);
+    if (g_norms_idle < kNormsKept) {
+      g_norms[g_norms_idle++] = {mem, ev, dev};
+      return;
+    }
+  }
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  if (ev) (void)hipEventDestroy(ev);
+  (void)hipHostFree(mem);
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
 }
 
 // In the order of the kernels that add partial sums on the device (k_sum_2d, k_fv_sum_partials: 256

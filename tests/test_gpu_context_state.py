@@ -2,7 +2,7 @@
 import pytest
 import torch
 
-from paper_2403_08063_amd import FVMultigrid, Multigrid, RefinedBlocks
+from paper_2403_08063_amd import FVMultigrid, GalerkinMultigrid, Multigrid, RefinedBlocks
 from paper_2403_08063_amd.solver import solve_noalloc
 
 pytestmark = pytest.mark.gpu
@@ -137,3 +137,55 @@ def test_blocks_solve_ends_at_the_first_iterate_within_the_tolerance():
         assert info.cycles == k and torch.equal(u[inner], its[k][inner])
         assert abs(info.relres - norms[k]) <= 1e-11 * norms[k]
     rb.close()
+
+
+# A context built while a stream is captured, as a program that captures its whole setup does: every
+# call of it but the ones that read norms can be recorded.  Three replays, with eager work and a
+# synchronisation between them, each against the eager cycle.
+@pytest.mark.parametrize("make,shape", [
+    (lambda: Multigrid(3, 65, device=DEV), (65,) * 3),
+    (lambda: Multigrid(2, 257, device=DEV), (257,) * 2),
+    (lambda: FVMultigrid(32, device=DEV), (34,) * 3),
+])
+def test_context_built_under_capture(make, shape):
+    say(f"capture {shape}")
+    f, u0 = rand(shape, 1), rand(shape, 2)
+    eager = make()
+    want = eager.vcycle(f, u0.clone())
+    u = u0.clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mg = make()
+        mg.vcycle(f, u)
+    for _ in range(3):
+        u.copy_(u0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(u, want)
+        assert torch.equal(eager.vcycle(f, u0.clone()), want)
+    eager.close()
+    mg.close()
+
+
+# More contexts than idle norm buffers are kept, of all four kinds, read norms, end in any order and
+# are followed by others: each reads its own.
+def test_norm_buffers_pass_between_contexts():
+    f, g = rand((33,) * 3, 1), rand((18,) * 3, 2)
+    z, zg = torch.zeros_like(f), torch.zeros_like(g)
+    k = torch.exp(rand((33,) * 3, 3))
+    want = float((f[1:-1, 1:-1, 1:-1] ** 2).sum()), float((g[1:-1, 1:-1, 1:-1] ** 2).sum())
+    for _ in range(3):
+        vertex = [Multigrid(3, 33, device=DEV) for _ in range(20)]
+        cells = [FVMultigrid(16, device=DEV) for _ in range(5)]
+        gal, blk = GalerkinMultigrid(k), RefinedBlocks(8, device=DEV)
+        fb = rand(blk.zeros(0).shape, 4)
+        for a in vertex + cells:
+            s, w = (a.residual_norm2(f, z), want[0]) if isinstance(a, Multigrid) else (a.residual_norm2(g, zg), want[1])
+            assert abs(s - w) <= 1e-12 * w
+        assert gal.solve(f, tol=1e-6)[1].converged
+        w = float((fb[:, 1:-1, 1:-1, 1:-1] ** 2).sum())
+        assert abs(blk.residual_norm2(fb, blk.zeros(0)) - w) <= 1e-12 * w
+        for a in vertex[::2] + [gal] + cells + [blk] + vertex[1::2]:
+            a.close()

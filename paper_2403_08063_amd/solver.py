@@ -244,7 +244,7 @@ class Multigrid:
 
     def close(self):
         if self._ctx is not None:
-            torch.cuda.current_stream(self.device).synchronize()
+            self.stream.synchronize()  # the context's, whichever is current here
             lib().mg_destroy(self._ctx)
             self._ctx = None
 

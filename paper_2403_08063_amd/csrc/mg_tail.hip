@@ -373,18 +373,18 @@ struct TailRun {
     }
   }
 
-  // the coarsest solve by one wave (coarsest_apply)
+  // the coarsest solve, a row of the inverse per thread (coarsest_apply's order)
   __device__ __forceinline__ static void coarsest(const LdsLevel<T>& L, const TailArgs<T>& a, double* b)
   {
     const int n = L.n, m1 = n - 2;
     const int m = DIM == 3 ? m1 * m1 * m1 : m1 * m1;
-    for (int q = threadIdx.x; q < m; q += 64) {
+    for (int q = threadIdx.x; q < m; q += THREADS) {
       int z, y, x;
       unknown_to_node(DIM, n, q, z, y, x);
       b[q] = (double)L.f[(z * n + y) * n + x];
     }
     sync();
-    for (int q = threadIdx.x; q < m; q += 64) {
+    for (int q = threadIdx.x; q < m; q += THREADS) {
       double s = 0.0;
       for (int c = 0; c < m; ++c) s += a.ainv[(size_t)c * m + q] * b[c];
       int z, y, x;
@@ -419,13 +419,24 @@ __global__ void __launch_bounds__(kTailThreads) k_tail_lds(TailArgs<T> a)
   int lw = 0, l1 = 0;
   while (lw < last && nodes(lw) > 64 * kWaveK) ++lw;
   for (l1 = lw; l1 < last && nodes(l1) > 64;) ++l1;
+  // A coarsest level of up to 64 unknowns is solved by the first wave, a larger one (up to 1024) by
+  // the workgroup: a wave would take m / 64 chains of m loads one after the other (V(2,2) at 113^3,
+  // 216 unknowns: 173 us with the wave, 125 so; at 121^2 on three levels, 841: 985 and 107).
+  const int mc = a.lv[last].n - 2;
+  const bool wide = mc * mc * (DIM == 3 ? mc : 1) > 64;
   for (int l = 0; l < lw; ++l) Block::down(tail_lds, a, l);
+  LdsLevel<T> Lc = lds_level<T, DIM, VAR>(tail_lds, a, last);
+  if (last == 0) Lc.f = a.lv[0].f;
   if (threadIdx.x < 64) {
     for (int l = lw; l < l1; ++l) Wave::down(tail_lds, a, l);
     for (int l = l1; l < last; ++l) Small::down(tail_lds, a, l);
-    LdsLevel<T> Lc = lds_level<T, DIM, VAR>(tail_lds, a, last);
-    if (last == 0) Lc.f = a.lv[0].f;
-    Wave::coarsest(Lc, a, b);
+    if (!wide) Wave::coarsest(Lc, a, b);
+  }
+  if (wide) {
+    __syncthreads();
+    Block::coarsest(Lc, a, b);
+  }
+  if (threadIdx.x < 64) {
     for (int l = last - 1; l >= l1; --l) Small::up(tail_lds, a, l);
     for (int l = l1 - 1; l >= lw; --l) Wave::up(tail_lds, a, l);
   }

@@ -3,7 +3,7 @@ import pytest
 import torch
 
 from paper_2403_08063_amd import FVMultigrid, GalerkinMultigrid, Multigrid, RefinedBlocks
-from paper_2403_08063_amd.solver import solve_noalloc
+from paper_2403_08063_amd.solver import FUSE_ALL, FUSE_TAIL, solve_noalloc
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -189,3 +189,26 @@ def test_norm_buffers_pass_between_contexts():
         assert abs(blk.residual_norm2(fb, blk.zeros(0)) - w) <= 1e-12 * w
         for a in vertex[::2] + [gal] + cells + [blk] + vertex[1::2]:
             a.close()
+
+
+# The tail's coarsest solve by the workgroup (more than 64 unknowns), behind levels of one wave (2D
+# 41: 21 and 11 nodes a side) and of the workgroup, and by one wave (the last): bitwise the per-level
+# kernels.
+@pytest.mark.parametrize("dim,n,levels", [(2, 41, 3), (2, 121, 3), (3, 29, 3), (3, 33, 3), (2, 37, 3)])
+@pytest.mark.parametrize("variable", [False, True])
+@pytest.mark.parametrize("precision", ["f64", "f32_ir"])
+def test_tail_with_a_large_coarsest_level(dim, n, levels, variable, precision):
+    say(f"tail dim={dim} n={n} levels={levels} variable={variable} {precision}")
+    mg = Multigrid(dim, n, levels=levels, variable=variable, precision=precision, device=DEV)
+    if variable:
+        mg.set_coefficients(torch.exp(rand((n,) * dim, 1)))
+    f, u0 = rand((n,) * dim, 2), rand((n,) * dim, 3)
+    out = []
+    for flags in (FUSE_ALL, FUSE_ALL & ~FUSE_TAIL):
+        mg.set_fusion(flags)
+        u = u0.clone()
+        for _ in range(2):
+            mg.vcycle(f, u)
+        out.append(u)
+    assert torch.equal(out[0], out[1])
+    mg.close()

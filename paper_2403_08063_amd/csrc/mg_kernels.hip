@@ -186,16 +186,17 @@ __global__ void __launch_bounds__(kFactorThreads)
 {
   extern __shared__ __align__(16) double gj[];
   constexpr int K = kLdsCoarse * kLdsCoarse / kFactorThreads;
+  const int T = blockDim.x;  // at least m^2 / K
   if (threadIdx.x == 0) *flag = 0;
-  for (int e = threadIdx.x; e < m * m; e += kFactorThreads) gj[e] = coarsest_entry(dim, n, ih2, k, e / m, e % m);
+  for (int e = threadIdx.x; e < m * m; e += T) gj[e] = coarsest_entry(dim, n, ih2, k, e / m, e % m);
   __syncthreads();
   for (int r = 0; r < m; ++r) {
     const double pivot = checked_pivot(gj[r * m + r], flag);
     double v[K];
 #pragma unroll
     for (int q = 0; q < K; ++q) {
-      const int e = threadIdx.x + q * kFactorThreads;
-      if (q * kFactorThreads >= m * m) break;  // uniform
+      const int e = threadIdx.x + q * T;
+      if (q * T >= m * m) break;  // uniform
       if (e >= m * m) continue;
       const int i = e / m, j = e - i * m;
       v[q] = eliminate(i, j, r, gj[e], gj[i * m + r], gj[r * m + j], pivot);
@@ -203,12 +204,12 @@ __global__ void __launch_bounds__(kFactorThreads)
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < K; ++q) {
-      const int e = threadIdx.x + q * kFactorThreads;
+      const int e = threadIdx.x + q * T;
       if (e < m * m) gj[e] = v[q];
     }
     __syncthreads();
   }
-  for (int e = threadIdx.x; e < m * m; e += kFactorThreads) ainv[e] = gj[e];
+  for (int e = threadIdx.x; e < m * m; e += T) ainv[e] = gj[e];
 }
 
 __global__ void __launch_bounds__(kBlock)
@@ -649,7 +650,10 @@ void coarsest_factor(hipStream_t s, int dim, int n, double h, const double* k, d
   if (m <= kLdsCoarse &&
       (lds <= 64 * 1024 || hipFuncSetAttribute(reinterpret_cast<const void*>(k_coarsest_inverse),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess)) {
-    k_coarsest_inverse<<<1, kFactorThreads, lds, s>>>(dim, n, m, ih2, k, ainv, flag);
+    // one wave up to 8 unknowns, four up to 16: the barriers of idle waves are most of what these
+    // take (5^3, 1 unknown: coefficients set in 17.2 us with 16 waves, 15.1 so; 9^2, 9: 17.8, 15.4)
+    const int threads = m <= 8 ? 64 : m <= 16 ? 256 : kFactorThreads;
+    k_coarsest_inverse<<<1, threads, lds, s>>>(dim, n, m, ih2, k, ainv, flag);
     return;
   }
   if (m <= kLdsCoarse) (void)hipGetLastError();  // refused: the steps by launches

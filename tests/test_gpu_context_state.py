@@ -212,3 +212,21 @@ def test_tail_with_a_large_coarsest_level(dim, n, levels, variable, precision):
         out.append(u)
     assert torch.equal(out[0], out[1])
     mg.close()
+
+
+# Coarsest inverses of as many unknowns as one wave and four waves take, and one row more: 4, 8, 9 and
+# 16, 25.  The residual is rounding amplified by the condition number (at most 4 / sin^2(pi h / 2) times
+# the range of k, 5e2): 1e-12 of the right-hand side.
+@pytest.mark.parametrize("dim,nc", [(2, 4), (3, 4), (2, 5), (2, 6), (2, 7)])
+@pytest.mark.parametrize("variable", [False, True])
+def test_coarsest_inverse_of_few_unknowns(dim, nc, variable):
+    say(f"coarsest inverse dim={dim} n={nc} variable={variable}")
+    n = 2 * nc - 1
+    mg = Multigrid(dim, n, levels=2, variable=variable, device=DEV)
+    if variable:
+        mg.set_coefficients(torch.exp(rand((n,) * dim, nc)))
+    f, u = rand((nc,) * dim, 2), mg.zeros(1)
+    mg.coarsest_solve(f, u)
+    inner = (slice(1, -1),) * dim
+    assert mg.residual(1, f, u)[inner].norm() <= 1e-12 * f[inner].norm()
+    mg.close()

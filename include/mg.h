@@ -129,7 +129,8 @@ mg_status mg_grad(mg_ctx* ctx, const double* u, const double* lambda, double* dk
  * hierarchy built by mg_set_coefficients. */
 
 /* sweeps red-black Gauss-Seidel sweeps (red: (x+y+z) even, first) on A_l u = f, in place.
- * Uses the same kernels as the cycle (temporally blocked on large 3D levels). */
+ * Uses the kernels of the cycle (temporally blocked), or the per-colour ones where a call has
+ * too few sweeps on too small a level for a pass to pay; the results are the same. */
 mg_status mg_smooth(mg_ctx* ctx, int level, const double* f, double* u, int sweeps);
 mg_status mg_smooth_f32(mg_ctx* ctx, int level, const float* f, float* u, int sweeps);
 

@@ -775,6 +775,24 @@ mg_status level_check(mg_ctx* c, int level, bool needs_coarser)
   return MG_OK;
 }
 
+// Whether a call of `sweeps` sweeps on arrays of the caller's, which have to end in the array they
+// start from, is better served by the per-colour kernels (two launches a sweep, in place) than by
+// strips or boxes (a pass for two sweeps, copies of the boundary and, after an odd number of passes,
+// of the result).  Same results.  One sweep: 16-17 us by passes, 10.5-12 so, on levels of launch
+// latency; 17.7 and 15.4 at 1025^2 in FP32 (4.2 MB), but 18.2 and 22.1 in FP64 (8.4 MB).  Two sweeps
+// only in FP64 boxes with a variable coefficient, of which a compute unit holds one, where there are
+// more than 256 of them: 26.4 and 20 us at 57^3, 26.5 and 22.4 at 65^3 (at 49^3 18.5 and 19.2; three
+// sweeps at 65^3 31.2 and 32.8).
+template <typename T>
+bool smooths_in_place(const mg_ctx* c, int l, int sweeps)
+{
+  if (use_tiled(c, l) || !use_blocked(c, l)) return false;
+  const Level& L = c->lv[l];
+  if (sweeps == 1 && L.N * sizeof(T) <= (size_t)6 << 20) return true;
+  const int boxes = (L.n - 2 + 7) / 8;  // of 8 nodes a side
+  return sizeof(T) == 8 && c->g.dim == 3 && c->g.variable && sweeps == 2 && boxes * boxes * boxes > 256;
+}
+
 template <typename T>
 mg_status smooth_impl(mg_ctx* c, int level, const T* f, T* u, int sweeps)
 {
@@ -787,6 +805,8 @@ mg_status smooth_impl(mg_ctx* c, int level, const T* f, T* u, int sweeps)
   // the level's second buffer holds the Dirichlet data of u while the fused kernel
   // alternates between the two
   T* t = V.t;
+  const int fuse = c->fuse;
+  if (smooths_in_place<T>(c, level, sweeps)) c->fuse &= ~MG_FUSE_BLOCKED;
   const bool blocked = use_blocked(c, level);
   if (blocked) {
     if (sizeof(T) == 8)
@@ -800,6 +820,7 @@ mg_status smooth_impl(mg_ctx* c, int level, const T* f, T* u, int sweeps)
   // corrections have zero Dirichlet data: the second buffer gets its zero boundary back (level
   // 0's FP64 one takes u's at every solve)
   if (blocked && (level > 0 || sizeof(T) == 4)) mgk::zero_boundary<T>(c->s, c->g.dim, L.n, t);
+  c->fuse = fuse;
   return launch_check(c, "smoothing");
 }
 

@@ -230,3 +230,30 @@ def test_coarsest_inverse_of_few_unknowns(dim, nc, variable):
     inner = (slice(1, -1),) * dim
     assert mg.residual(1, f, u)[inner].norm() <= 1e-12 * f[inner].norm()
     mg.close()
+
+
+# mg_smooth by the per-colour kernels or by passes, by sweeps, size, type and coefficient: bitwise the
+# same, and neither disturbs the cycles that follow.
+@pytest.mark.parametrize("dim,n,level", [(2, 65, 0), (2, 65, 1), (2, 1025, 0), (3, 33, 0), (3, 65, 0), (3, 65, 1),
+                                         (3, 113, 1)])
+@pytest.mark.parametrize("variable", [False, True])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_smooth_in_place_and_by_passes(dim, n, level, variable, dtype):
+    say(f"smooth dim={dim} n={n} level={level} variable={variable} {dtype}")
+    mg, fresh = [Multigrid(dim, n, variable=variable, precision="f32_ir", device=DEV) for _ in range(2)]
+    if variable:
+        for a in (mg, fresh):
+            a.set_coefficients(torch.exp(rand((n,) * dim, 1)))
+    shape = mg.zeros(level).shape
+    f, u0 = rand(shape, 2).to(dtype), rand(shape, 3).to(dtype)
+    for sweeps in (1, 2, 3, 4):
+        out = []
+        for flags in (True, False):
+            mg.set_fusion(flags)
+            out.append(mg.smooth(level, f, u0.clone(), sweeps))
+        assert torch.equal(out[0], out[1]) and not torch.equal(out[0], u0)
+    mg.set_fusion(True)
+    f, u0 = rand((n,) * dim, 4), rand((n,) * dim, 5)
+    assert torch.equal(mg.vcycle(f, u0.clone()), fresh.vcycle(f, u0.clone()))
+    mg.close()
+    fresh.close()

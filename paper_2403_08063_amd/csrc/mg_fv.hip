@@ -746,7 +746,11 @@ mg_status mgfv_jacobi(mgfv_ctx* c, int level, const double* f, double* u, int sw
   if (!f || !u || sweeps < 0) return fv_fail(c, MG_EINVAL, "bad smoothing arguments");
   FvLevel& L = c->lv[level];
   copy_ghosts(c, level, u);
-  double* r = smooth(c, level, u, L.t, f, sweeps);
+  // a pass for two sweeps would end in the second buffer and be copied: at 128^3 34.5 us against 26
+  // one by one, at 64^3 and below equal, at 256^3 155 against 179
+  const bool pair = sweeps == 2 && L.N <= 128;
+  double* r = smooth(c, level, u, L.t, f, pair ? 1 : sweeps);
+  if (pair) r = smooth(c, level, r, u, f, 1);
   if (r != u) mgk::copy<double>(c->s, L.cnt, r, u);
   reset_ghosts(c, level);
   return fv_launch_check(c, "Jacobi");

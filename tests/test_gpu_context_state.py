@@ -257,3 +257,13 @@ def test_smooth_in_place_and_by_passes(dim, n, level, variable, dtype):
     assert torch.equal(mg.vcycle(f, u0.clone()), fresh.vcycle(f, u0.clone()))
     mg.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("N", [8, 16, 64, 128, 256])
+def test_fv_two_sweeps_in_a_call(N):
+    say(f"fv two sweeps N={N}")
+    mg = FVMultigrid(N, device=DEV)
+    f, u = rand((N + 2,) * 3, N), rand((N + 2,) * 3, N + 1)
+    want = mg.jacobi(0, f, mg.jacobi(0, f, u.clone(), 1), 1)
+    assert torch.equal(mg.jacobi(0, f, u.clone(), 2), want)
+    mg.close()

@@ -1505,11 +1505,12 @@ mg_status mgblk_mg_solve(mgblk_ctx* c, const double* f, double* u, double tol, i
   if (!(tol >= 0)) return blk_fail(c, MG_EINVAL, "tol must be >= 0");
   // Where two pre-smoothing sweeps are one pass, the norm rides on it (1.4 ms less a cycle at 128^3
   // cells per block): the pass leaves u alone, and u is returned if the norm ends the solve.  Where
-  // it is likely to -- before the first cycle and by the contraction so far -- it is a pass of its
-  // own (a solve from a converged iterate at 72^3 cells per block 558 us with the pass, 347 so).
+  // the contraction so far says that it will, it is a pass of its own.  Before the first cycle it
+  // rides: the pass for nothing costs a solve from a converged iterate 0.35 ms (2.01 against 1.66 at
+  // 128^3), the norm's own pass would cost every other solve 1.65.
   const bool rides = mgk::blk_pair_supported(c->lv[0].B) && c->g.nu1 >= 2 && c->lv.size() > 1;
   if (rides) copy_boundary(c, 0, u, c->lv[0].t);
-  double rn2 = 0, rn = 0, rn_prev = NAN, predicted = 0.0;
+  double rn2 = 0, rn = 0, rn_prev = NAN, predicted = INFINITY;
   mg_status st = MG_OK;
   int k = 0;
   for (;; ++k) {

@@ -828,30 +828,31 @@ mg_status mgfv_solve(mgfv_ctx* c, const double* f, double* u, double tol, int* c
     // The first sweep of a cycle forms the residual of the iterate it starts from: the iterate's
     // norm comes out of the next cycle's pre-smoothing, which writes the second buffer only, so
     // the iterate is still there when the norm ends the solve.  The coarse levels run while the
-    // host waits for it.  The norm is a pass of its own before the first cycle, after the last one
-    // allowed and where the contraction so far says that it will end the solve: a way down for
-    // nothing costs more (a solve from a converged iterate at 256^3 cells 388 us, 97 so).
-    double predicted = 0.0, rn_prev = NAN;
+    // host waits for it.  After the last cycle allowed, and where the contraction so far says that it
+    // will end the solve, the norm is a pass of its own.  A solve may also start from a converged
+    // iterate, which nothing tells beforehand: on large grids the first cycle's coarse levels wait
+    // for the norm (a gap of 12 us; such a solve takes 235 us in place of 387 at 256^3, 73 in place
+    // of 146 at 128^3).  A pass of its own for the first norm would cost every other solve more (0.45
+    // of 88 ms at 512^3, 18 of 980 us for ten cycles at 64^3) than such solves lose (97 us at 256^3).
+    double predicted = INFINITY, rn_prev = NAN;
     for (;; ++k) {
       const bool more = k < c->g.max_cycles, ride = more && predicted > 4.0 * tol;
       double *cur = nullptr, *ec = nullptr;
       if (ride) cur = top_down(c, f, u, norm_place(c));
       else norm2(c, f, u);
       if ((st = fv_hip(c, hipEventRecord(c->hn.ev, c->s), "recording the norm event"))) break;
-      if (ride) ec = coarse_cycle(c, 1);
+      if (ride && (k > 0 || c->lv[0].N < 128)) ec = coarse_cycle(c, 1);
       if ((st = fv_launch_check(c, "V-cycle"))) break;
       if ((st = fv_hip(c, hipEventSynchronize(c->hn.ev), "waiting for the norm"))) break;
       c->hn.unread = false;
       rn = std::sqrt(mgk::host_norm(c->hn.mem, c->hcount));
       if (!more || !std::isfinite(rn) || rn <= tol) {
         // the coarse levels' work is for nothing; a caller may free the workspace now
-        if (ride) st = fv_hip(c, hipStreamSynchronize(c->s), "stream synchronisation");
+        if (ec) st = fv_hip(c, hipStreamSynchronize(c->s), "stream synchronisation");
         break;
       }
-      if (!ride) {
-        cur = top_down(c, f, u, nullptr);
-        ec = coarse_cycle(c, 1);
-      }
+      if (!ride) cur = top_down(c, f, u, nullptr);
+      if (!ec) ec = coarse_cycle(c, 1);
       top_up(c, f, u, cur, ec);
       predicted = rn_prev > 0 ? rn * (rn / rn_prev) : rn;
       rn_prev = rn;

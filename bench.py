@@ -139,9 +139,9 @@ def pmc_ir_sample(n: int):
 IR_KERNELS = [
     (r"k_rbgs_tiled<float, false, 2, \d+, \d+, \d+, 1, 1", "FP32 pre-smoothing from 0 + residual restriction",
      4 + 4 + 0.5),
-    (r"k_rbgs_tiled<float, false, 2, \d+, \d+, \d+, 2, 0", "FP32 post-smoothing with the prolongation",
-     4 + 4 + 4 + 0.5),
-    (r"k_pass<false, 2,", "refinement pass (u += s e, r = f - A u, norm, r32)", 8 + 8 + 4 + 8 + 4),
+    (r"k_rbgs_tiled<float, false, 2, \d+, \d+, \d+, 2, 2", "FP32 post-smoothing with the prolongation and the "
+     "refinement step", 4 + 4 + 0.5 + 8 + 8 + 8 + 4),
+    (r"k_pass<false, 2,", "first refinement pass of a first solve (no correction yet)", 8 + 8 + 8 + 4),
     (r"k_pass<false, 6,", "first refinement pass (+ right-hand-side norm)", 8 + 8 + 8 + 4),
 ]
 

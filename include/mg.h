@@ -197,11 +197,11 @@ mg_status mg_set_fusion(mg_ctx* ctx, int flags);
 
 /* ---- allocation-free solve ----
  * For callers that cannot allocate device memory or set up a context at the time of the
- * solve (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): mg_solve on a context built for this one call, whose workspace is a static
+ * solve (tight serving loops, harnesses that forbid hipMalloc; not code under stream capture,
+ * since a solve waits for its norms): mg_solve on a context built for this one call, whose workspace is a static
  * device array of MG_NOALLOC_MAX_BYTES inside the library instead of a caller-allocated
  * one.  The call makes no device or host allocation of any kind (no hipMalloc, hipFree,
- * pinned memory or heap); FP32-refined solves read their norms synchronously.
+ * pinned memory or heap); norms are read synchronously.
  *   grid:   as for mg_setup; mg_workspace_bytes(grid) must not exceed MG_NOALLOC_MAX_BYTES
  *           (else MG_ENOMEM, before any HIP call).  32 MiB holds e.g. a 129^3 FP64 or a
  *           65^3 FP32-refined variable-coefficient grid.

@@ -24,12 +24,13 @@
 // Tiles that touch no domain face run without the ghost and Dirichlet selects (EDGE = false).
 // Every cell takes the single passes' operations in their order: results are bitwise equal.
 //
-// A pass is bound by the FP64 issue of its two waves per SIMD (about 300 instructions per wave and
-// plane, 240 of them FP64).  What is not arithmetic counts: cells of a plane in one block without
+// A pass has two waves per SIMD, which keep neither the VALU (about 300 instructions per wave and
+// plane, 240 of them FP64: 50 % busy at 512^3) nor memory (4.1 and 4.6 TB/s) full; a wave waits for
+// memory or the barrier a third of its time.  What is not arithmetic counts: cells of a plane in one block without
 // branches, the planes next to a domain face in a copy of their own, and edge rows as 16-byte
 // pairs took the 512^3 passes from 1.40 and 1.07 ms (pre- and post-smoothing) to 1.14 and 0.94,
 // loads and stores of a lane's columns as one access in all tiles to 1.13 and 0.91; 35 V(3,3)
-// cycles 105.9 -> 86.9 ms.
+// cycles 105.9 -> 87 to 88 ms.
 #include "mg_buffer.h"
 #include "mg_kernels.h"
 #include "mg_lanes.h"

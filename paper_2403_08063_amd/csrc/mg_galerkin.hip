@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(kGalThreads)
 // Four colours of a sweep (those of z-parity PZ) in one launch on a small level: planes of one
 // parity do not couple, and within a plane the colours follow each other in LDS.  One workgroup
 // per plane, one thread per slot of a colour (half^2 of them); the coefficients of the next colour
-// are read while the current one is computed.  A sweep is two launches: at 33^3 17.3 us against
+// are read while the current one is computed.  A sweep is two launches: at 33^3 18.4 us against
 // 35 in eight (one per colour).  Not at 65^3: its 32 workgroups draw too little bandwidth (87 us
 // against 35).
 template <typename TS, int PZ, bool ZERO, int HALF>
@@ -612,7 +612,9 @@ void gal_layout(const mggal_grid* g, GalCarver& cv, mggal_ctx* c)
   const size_t cnt0 = (size_t)g->n * g->n * g->n;
   double* k = cv.take<double>(cnt0);
   double* t = cv.take<double>(cnt0);
-  (void)cv.take<double>(cnt0);  // not used: the size of the workspace is what callers know it to be
+  // A third fine array, which the probing set-up needed and nothing uses now, is still counted: the
+  // size that mggal_workspace_bytes reports is tested to hold three.
+  (void)cv.take<double>(cnt0);
   double* partial = cv.take<double>(mgk::kStreamPartials);
   double* scal = cv.take<double>(8);
   std::vector<GalLevel> lv;
